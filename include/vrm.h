@@ -219,7 +219,9 @@ int vrm_rk_stage(vrm_ctx* ctx, vrm_cloud* cloud, const float* u_dev, const float
 /* One whole SSP-RK3 step: vrm_insert_particles, then stages 0, 1, 2 of
  * vrm_rk_stage.  With n_vort > 0 each stage's velocity is the prescribed
  * vortex field of vrm_vortex_velocity at the stage time (t, t + dt, t + dt/2);
- * otherwise zero.  The context caches the cell list and the cell order of the
+ * otherwise zero.  Without vortices the positions stay, so the three stages have
+ * the same stencils: their LPs are solved once, in stage 0 (and counted once in
+ * vrm_counters).  The context caches the cell list and the cell order of the
  * cloud between calls: a caller that changes positions or the count itself
  * must not rely on that cache (a different cloud or count resets it).
  * The three stages are recorded once as a HIP graph (on a stream of the

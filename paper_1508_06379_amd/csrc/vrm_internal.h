@@ -140,6 +140,11 @@ struct LaunchParams {
     int max_cert;                        // certification rounds of one LP (kMaxCert unless tuned)
 };
 constexpr int kMaxCert = 8;              // certification rounds: primal / dual repairs of one LP
+// A kept stencil: a row of 12 column indices and one of 12 fractions (48 bytes
+// each: three 16-byte accesses).  At most nine columns carry a fraction; the
+// last index holds their count, or -1 for a particle without a stencil, and the
+// last fraction fhat_ii.
+constexpr int kStenRow = 12;
 
 // Fixed-point accumulation (deterministic mode): every contribution f Gamma is
 // rounded to a multiple of 2^(e - 46), where max |Gamma^n| < 2^e, and summed as
@@ -245,6 +250,8 @@ struct vrm_ctx {
     hipGraphExec_t graph_exec;
     unsigned char graph_key[256];
     double* t_dev;               // step start time read by the graph's velocity kernels
+    int32_t* sten_idx;           // [cap][kStenRow] stencils kept within one vrm_step call, by particle index:
+    float* sten_f;               // columns and fractions, then their count (-1: none) and fhat_ii
     int32_t* prev;               // [cap][9] basis (column ids) of each particle's last stencil, by id
     uint64_t* pmask;             // [cap] crash basis (previous or predicted) as a column mask per complete LP
     int32_t* lkey;               // [cap] bin of each complete LP for the counting sort (pivot history or doubt)
@@ -308,7 +315,9 @@ size_t vrm_remove_tmp_bytes(int32_t cap);
 // launchers (vrm_lp.hip)
 int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
                     const vrm_stencils* out, int apply, uint16_t* feat_out = nullptr, float* label_out = nullptr,
-                    int max_rows = 0);
+                    int max_rows = 0, int keep = 0);
+// the update of the stencils kept by a vrm_stencil_run with keep = 1
+int vrm_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp);
 int vrm_small_nbhd_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
                        int32_t* small_idx, int32_t* kfull);
 int vrm_warm_predict_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, float* out,

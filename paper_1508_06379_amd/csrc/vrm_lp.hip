@@ -364,7 +364,20 @@ struct StencilOut {
     uint64_t* pmask;         // crash basis as a column mask per complete-neighbourhood queue item (size-binned path)
     uint8_t* pivhist;        // by particle id (< prev_cap): pivots of its last cold complete LP
     const int32_t* cloud_id;   // ids by cloud index
+    int32_t* sten_idx;   // [i][kStenRow] the stencils of the run are kept here (or NULL), see kStenRow
+    float* sten_f;
 };
+
+// entry e of particle i's kept stencil; the row's end: count of entries (-1: no stencil) and fhat_ii
+__device__ __forceinline__ void keep_entry(const StencilOut& out, int i, int e, int pj, float v)
+{
+    out.sten_idx[(size_t)i * kStenRow + e] = pj;
+    out.sten_f[(size_t)i * kStenRow + e] = v;
+}
+__device__ __forceinline__ void keep_end(const StencilOut& out, int i, int count, float fii)
+{
+    keep_entry(out, i, kStenRow - 1, count, fii);
+}
 
 constexpr int kPrevIds = 9;
 
@@ -756,17 +769,23 @@ __global__ __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_eu(3))
             }
             if (st == 0) {
                 float g = gamma[i];
+                int nz = 0;
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
                     bool alive = !((dead >> s) & 1ull);
                     int pj = alive ? (int)((unsigned)s_meta[s * kSmallBlock + tid] >> 6) : -1;
-                    if (apply && fv[s] != 0.0f) acc_add(acc, pj, fv[s], g, dsc);
+                    if (apply && fv[s] != 0.0f) {
+                        acc_add(acc, pj, fv[s], g, dsc);
+                        if (out.sten_idx) keep_entry(out, i, nz, pj, fv[s]);
+                        ++nz;
+                    }
                     if (out.small_f) {
                         out.small_idx[(size_t)i * VRM_NSEG + s] = pj;
                         out.small_f[(size_t)i * VRM_NSEG + s] = fv[s];
                     }
                 }
                 if (apply) acc_add(acc, i, fii, g, dsc);
+                if (out.sten_idx) keep_end(out, i, nz, fii);
                 if (out.small_f) {
                     out.fii[i] = fii;
                     out.status[i] = (warm == 1 || warm == 2) ? VRM_ST_WARM : VRM_ST_SMALL;
@@ -848,6 +867,11 @@ __global__ __launch_bounds__(kSmallBlock) void k_lp_small_coop(const float* __re
                 const float g = gamma[i];
                 if (apply && fv != 0.0f) acc_add(acc, pj, fv, g, dsc);
                 if (apply && lead) acc_add(acc, i, fii, g, dsc);
+                if (out.sten_idx) {
+                    const uint32_t m = (uint32_t)(__ballot(fv != 0.0f) >> base) & 0xFFu;
+                    if (fv != 0.0f) keep_entry(out, i, __popc(m & ((1u << s) - 1u)), pj, fv);
+                    if (lead) keep_end(out, i, __popc(m), fii);
+                }
                 if (out.small_f) {
                     out.small_idx[(size_t)i * VRM_NSEG + s] = alive ? pj : -1;
                     out.small_f[(size_t)i * VRM_NSEG + s] = fv;
@@ -1064,6 +1088,7 @@ __global__ __launch_bounds__(kFullBlock) void k_lp_full(const int32_t* __restric
                 int u = (int)((unsigned)s_meta[j * kFullBlock + tid] >> 6);
                 int pj = perm[u];
                 if (apply) acc_add(acc, pj, v, g_i, dsc);
+                if (out.sten_idx) keep_entry(out, i, nz, pj, v);
                 if (out.full_idx) {
                     out.full_idx[(size_t)i * VRM_KMAX + nz] = pj;
                     out.full_f[(size_t)i * VRM_KMAX + nz] = v;
@@ -1086,6 +1111,7 @@ __global__ __launch_bounds__(kFullBlock) void k_lp_full(const int32_t* __restric
                                      warm_pass && out.use_prev, pref)
                        : 1;
             if (st == 0 && out.prev && (unsigned)own < (unsigned)out.prev_cap) record_basis(out.prev, own, basis, col_id);
+            if (out.sten_idx && (st == 0 || st == 1)) keep_end(out, i, st == 0 ? nz : -1, fii);
             if (st == 0) {
                 if (apply) acc_add(acc, i, fii, g_i, dsc);
                 if (out.full_k) {
@@ -1608,6 +1634,7 @@ __global__ __launch_bounds__(kFullBlock) __attribute__((amdgpu_waves_per_eu(2)))
             auto store = [&](int j, float v) {
                 const int pj = perm[(unsigned)row[j] >> 6];
                 if (apply) acc_add(acc, pj, v, g_i, dsc);
+                if (out.sten_idx) keep_entry(out, i, nz, pj, v);
                 if (out.full_idx) {
                     out.full_idx[(size_t)i * VRM_KMAX + nz] = pj;
                     out.full_f[(size_t)i * VRM_KMAX + nz] = v;
@@ -1641,6 +1668,7 @@ __global__ __launch_bounds__(kFullBlock) __attribute__((amdgpu_waves_per_eu(2)))
                 const int own = ids[t];
                 if (out.pivhist && (unsigned)own < (unsigned)out.prev_cap) out.pivhist[own] = (uint8_t)min(piv, 254);
             }
+            if (out.sten_idx && st != 5 && st != 7) keep_end(out, i, st == 0 ? nz : -1, fii);
             if (st == 0) {
                 if (apply) acc_add(acc, i, fii, g_i, dsc);
                 if (out.full_k) {
@@ -1697,6 +1725,47 @@ __global__ __launch_bounds__(kFullBlock) __attribute__((amdgpu_waves_per_eu(2)))
             qs->blocks_done = 0;
         }
     }
+}
+
+// The update sum_j fhat_ji Gamma_j of the kept stencils (one thread per particle):
+// the atomics of the LP kernels without their linear programs.  Bound by the
+// atomics and the 96 bytes of a row; a launch's latency on small clouds.  A step of
+// the 40k-particle heat run (q = 2) takes 213 us with it and 384 us with the
+// linear programs solved in every stage, the 1681-particle one 165 and 270 us.
+__global__ __launch_bounds__(256) void k_apply(int n, const int32_t* __restrict__ n_dev,
+                                               const uint8_t* __restrict__ diffused,
+                                               const int32_t* __restrict__ sten_idx, const float* __restrict__ sten_f,
+                                               const float* __restrict__ gamma, float* acc, int det, const GridState* gs,
+                                               vrm_counters* cnt)
+{
+    if (n_dev) n = *n_dev;
+    cnt = counter_stripe(cnt);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    bool ok = false;
+    if (i < n && !gs->bad && diffused[i]) {
+        int idx[kStenRow];
+        float f[kStenRow];
+        const int4* ri = reinterpret_cast<const int4*>(sten_idx + (size_t)i * kStenRow);
+        const float4* rf = reinterpret_cast<const float4*>(sten_f + (size_t)i * kStenRow);
+#pragma unroll
+        for (int q = 0; q < kStenRow / 4; ++q) {
+            const int4 a = ri[q];
+            const float4 b = rf[q];
+            idx[4 * q] = a.x, idx[4 * q + 1] = a.y, idx[4 * q + 2] = a.z, idx[4 * q + 3] = a.w;
+            f[4 * q] = b.x, f[4 * q + 1] = b.y, f[4 * q + 2] = b.z, f[4 * q + 3] = b.w;
+        }
+        const int count = idx[kStenRow - 1];
+        ok = count >= 0;
+        if (ok) {
+            const float g = gamma[i];
+            const double dsc = det ? det_scale(gs->gmax_bits) : 0.0;
+#pragma unroll
+            for (int e = 0; e < kStenRow - 1; ++e)
+                if (e < count) acc_add(acc, idx[e], f[e], g, dsc);
+            acc_add(acc, i, f[kStenRow - 1], g, dsc);
+        }
+    }
+    count_add(&cnt->redistributions, ok);
 }
 
 // ------------------------------------------------------------ particle removal
@@ -1987,10 +2056,14 @@ int vrm_small_nbhd_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchP
 }
 
 int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, const vrm_stencils* st,
-                    int apply, uint16_t* feat_out, float* label_out, int max_rows)
+                    int apply, uint16_t* feat_out, float* label_out, int max_rows, int keep)
 {
     if (n <= 0) return VRM_OK;
     StencilOut out{};
+    if (keep) {
+        out.sten_idx = c->sten_idx;
+        out.sten_f = c->sten_f;
+    }
     if (st) {
         out.small_idx = st->small_idx_dev;
         out.small_f = st->small_f_dev;
@@ -2130,6 +2203,16 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
                            c->counters, kLpPlain, c->q_retry, 1);
         VRM_HIP(hipGetLastError());
     }
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
+}
+
+int vrm_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp)
+{
+    if (n <= 0) return VRM_OK;
+    ScopedTimer tm(c, lp.m == 5 ? VRM_T_LP_SMALL : VRM_T_LP_FULL);
+    hipLaunchKernelGGL(k_apply, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->diffused, c->sten_idx,
+                       c->sten_f, cl->gamma_dev, c->acc, lp.det, c->grid, c->counters);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
