@@ -21,36 +21,12 @@
 
 #include "vrm_device.h"
 #include "vrm_internal.h"
+#include "vrm_lp_common.h"
 #include "vrm_simplex.h"
 
 using namespace vrm;
 
 namespace {
-
-__device__ __forceinline__ int cell_of_pos(const GridState& g, float x, float y, int& cx, int& cy)
-{
-    float fx = (x - g.x0) * g.inv_cs;
-    float fy = (y - g.y0) * g.inv_cs;
-    fx = fminf(fmaxf(fx, 0.0f), (float)(g.nx - 1));
-    fy = fminf(fmaxf(fy, 0.0f), (float)(g.ny - 1));
-    cx = (int)fx;
-    cy = (int)fy;
-    return cy * g.nx + cx;
-}
-
-// wave-aggregated append of `want` (0/1) items; returns the slot or -1
-__device__ __forceinline__ int wave_append(int* counter, bool want)
-{
-    uint64_t m = __ballot(want);
-    int lane = lane_id();
-    int before = __popcll(m & ((1ull << lane) - 1ull));
-    int total = __popcll(m);
-    int leader = total ? __ffsll((unsigned long long)m) - 1 : 0;
-    int base = 0;
-    if (total && lane == leader) base = atomicAdd(counter, total);
-    base = __shfl(base, leader, VRM_WAVE);
-    return want ? base + before : -1;
-}
 
 // ------------------------------------------------------------- kernels
 // Small neighbourhoods (Sec. 4.3) of the diffused particles, in slot order.
@@ -344,102 +320,6 @@ __global__ __launch_bounds__(256) void k_small_nbhd_coop(int n, const int32_t* _
         const int p2 = block_append_n(&qs->n_full, full && lead ? 1 : 0, s_app);
         if (full && lead) q_full[p2] = t;
     }
-}
-
-struct StencilOut {
-    int32_t* small_idx;
-    float* small_f;
-    float* fii;
-    uint8_t* status;
-    int32_t* full_k;
-    int32_t* full_idx;
-    float* full_f;
-    uint16_t* feat;      // feature rows of solved LPs (collection), or NULL
-    float* lab;          // label rows (basis indicators, fractions) of solved LPs, or NULL
-    int max_rows;
-    const float* pred;   // warm start: small LPs 8 logits, complete ones kMlpOut outputs per queue item; or NULL
-    int32_t* prev;       // basis (column ids) of each particle's last stencil, [id][kPrevIds]: recorded if non-NULL
-    int prev_cap;        // rows of prev: particles with larger ids keep no basis (they start cold)
-    int use_prev;        // warm start from prev instead of pred
-    uint64_t* pmask;         // crash basis as a column mask per complete-neighbourhood queue item (size-binned path)
-    uint8_t* pivhist;        // by particle id (< prev_cap): pivots of its last cold complete LP
-    const int32_t* cloud_id;   // ids by cloud index
-    int32_t* sten_idx;   // [i][kStenRow] the stencils of the run are kept here (or NULL), see kStenRow
-    float* sten_f;
-};
-
-// entry e of particle i's kept stencil; the row's end: count of entries (-1: no stencil) and fhat_ii
-__device__ __forceinline__ void keep_entry(const StencilOut& out, int i, int e, int pj, float v)
-{
-    out.sten_idx[(size_t)i * kStenRow + e] = pj;
-    out.sten_f[(size_t)i * kStenRow + e] = v;
-}
-__device__ __forceinline__ void keep_end(const StencilOut& out, int i, int count, float fii)
-{
-    keep_entry(out, i, kStenRow - 1, count, fii);
-}
-
-constexpr int kPrevIds = 9;
-
-// the previous basis of particle `own` as a mask over columns with ids cid(j), j < k
-template <class ColId>
-__device__ __forceinline__ uint64_t prev_mask(const int32_t* prev, int own, int k, ColId cid)
-{
-    int pv[kPrevIds];
-#pragma unroll
-    for (int r = 0; r < kPrevIds; ++r) pv[r] = prev[(size_t)own * kPrevIds + r];
-    uint64_t m = 0;
-    for (int j = 0; j < k; ++j) {
-        const int id = cid(j);
-        if (id < 0) continue;
-        bool in = false;
-#pragma unroll
-        for (int r = 0; r < kPrevIds; ++r) in = in || pv[r] == id;
-        if (in) m |= 1ull << j;
-    }
-    return m;
-}
-
-// record the basic columns' ids as the particle's basis
-template <class ColId>
-__device__ __forceinline__ void record_basis(int32_t* prev, int own, uint64_t basis, ColId cid)
-{
-    int c = 0;
-    while (basis && c < kPrevIds) {
-        const int j = __ffsll((unsigned long long)basis) - 1;
-        basis &= basis - 1;
-        prev[(size_t)own * kPrevIds + c++] = cid(j);
-    }
-    for (; c < kPrevIds; ++c) prev[(size_t)own * kPrevIds + c] = -1;
-}
-
-__device__ __forceinline__ void count_add(int* p, bool v)
-{
-    uint64_t m = __ballot(v);
-    if (m && lane_id() == __ffsll((unsigned long long)m) - 1) atomicAdd(p, __popcll(m));
-}
-__device__ __forceinline__ void count_add(int64_t* p, bool v)
-{
-    uint64_t m = __ballot(v);
-    if (m && lane_id() == __ffsll((unsigned long long)m) - 1)
-        atomicAdd(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__popcll(m));
-}
-
-// Tie-break of the canonical cost: 2^-10 rank(id); for the removal LP (q = 1)
-// 2^-16 rank^2, convex in the rank because on a lattice the id ranks of
-// opposite neighbours are symmetric and would tie under a linear weight.
-// Exact in FP32 for ranks < 64.
-__device__ __forceinline__ float tie_weight(unsigned rank, int q)
-{
-    return q == 1 ? 0x1p-16f * (float)(rank * rank) : 0.0009765625f * (float)rank;
-}
-
-// add the tie-break to a double-float cost (exact at these magnitudes)
-__device__ __forceinline__ df add_rank(df C, int rank, int q)
-{
-    df w = two_sum(C.hi, tie_weight((unsigned)rank, q));
-    w.lo += C.lo;
-    return fast_two_sum(w.hi, w.lo);
 }
 
 __device__ __forceinline__ uint16_t f2bf(float f)
@@ -897,11 +777,6 @@ __global__ __launch_bounds__(kSmallBlock) void k_lp_small_coop(const float* __re
     }
 }
 
-__device__ __forceinline__ uint64_t member_key(float d2, int id)
-{
-    return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)id;
-}
-
 // Complete neighbourhood of slot t within R_full (its VRM_KMAX nearest by (d2, id)
 // if larger), sorted nearest first.  Slots go to su[j * kFullBlock], keys to
 // sd2 / sid (same layout).  Returns the count.
@@ -1173,7 +1048,6 @@ __global__ __launch_bounds__(kFullBlock) void k_lp_full(const int32_t* __restric
 // as the working set (Sec. 4.3: the closer particles carry the stencil; the
 // canonical cost grows like |r|^4), pricing the others from HBM only once the
 // working set is exhausted -- the optimum is certified over all k columns.
-constexpr int kSiftW = 24;
 constexpr int kDeferMinN = 1 << 20;   // particles from which a cold LP launch defers certifications
 constexpr int kKBins = VRM_KMAX + 1;
 // a record row: (slot << 6) | id rank per column, nearest first
@@ -2021,6 +1895,14 @@ int lp_grid_full(const vrm_ctx* c, int n)
 {
     return n > 0 ? min((n + kFullBlock - 1) / kFullBlock, c->tuning.lp_full_blocks) : 1;
 }
+// workgroups of the sixteen-lane complete-LP kernel: three fit on a CU; one each where
+// it solves what the small LPs left, mostly few
+int lp_group_blocks(const vrm_ctx* c, int m) { return min(c->tuning.lp_full_blocks, m == 9 ? 768 : 256); }
+// Particles up to which complete LPs take sixteen lanes each: below, the one-thread
+// kernels have fewer waves than the chip has SIMDs and last as long as their slowest
+// wave.  Collection and LPs per launch, sixteen lanes against one: 143 and 365 us for
+// 14k LPs, 270 and 510 us for 57k, 610 and 640 us for 143k.
+constexpr int kGroupMaxN = 1 << 17;
 // workgroups of the neighbourhood kernel: 256 particles each, or 256 / kNbL
 // with kNbL lanes per particle up to kNbhdCoopMaxN particles
 int nbhd_blocks(int n) { return n <= kNbhdCoopMaxN ? (n + 256 / kNbL - 1) / (256 / kNbL) : (n + 255) / 256; }
@@ -2132,10 +2014,14 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         o2.lab = nullptr;
         ScopedTimer tm(c, VRM_T_LP_FULL);
         const bool stored = full_stored_costs(c, n);
+        if (lp.phase1 == 0) return vrm_lp_group_run(c, cl, n, lp, o2, apply, stored, lp_group_blocks(c, lp.m));
         hipLaunchKernelGGL((stored ? full_kernel<5, true>(lp.phase1) : full_kernel<5, false>(lp.phase1)),
                            dim3(min(lp_grid_full(c, n), 64)), dim3(kFullBlock), 0, c->stream, c->perm,
                            c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp,
                            o2, apply, c->counters, kLpPlain, c->q_retry, 1);
+    } else if (!feat_out && !warm && lp.phase1 == 0 && n <= kGroupMaxN) {
+        ScopedTimer tm(c, VRM_T_LP_FULL);
+        return vrm_lp_group_run(c, cl, n, lp, out, apply, false, lp_group_blocks(c, lp.m));
     } else if (!feat_out) {
         // size-binned working-set path: column lists (with the previous basis),
         // counting sort, the network's inference from the lists if it predicts, LPs

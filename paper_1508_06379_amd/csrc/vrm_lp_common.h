@@ -1,0 +1,145 @@
+// Pieces shared by the LP kernels of libvrm: the stencil outputs, the tie-break of
+// the canonical cost, queue appends and counters.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "vrm_device.h"
+#include "vrm_internal.h"
+#include "vrm_simplex.h"
+
+namespace vrm {
+
+__device__ __forceinline__ int cell_of_pos(const GridState& g, float x, float y, int& cx, int& cy)
+{
+    float fx = (x - g.x0) * g.inv_cs;
+    float fy = (y - g.y0) * g.inv_cs;
+    fx = fminf(fmaxf(fx, 0.0f), (float)(g.nx - 1));
+    fy = fminf(fmaxf(fy, 0.0f), (float)(g.ny - 1));
+    cx = (int)fx;
+    cy = (int)fy;
+    return cy * g.nx + cx;
+}
+
+// wave-aggregated append of `want` (0/1) items; returns the slot or -1
+__device__ __forceinline__ int wave_append(int* counter, bool want)
+{
+    uint64_t m = __ballot(want);
+    int lane = lane_id();
+    int before = __popcll(m & ((1ull << lane) - 1ull));
+    int total = __popcll(m);
+    int leader = total ? __ffsll((unsigned long long)m) - 1 : 0;
+    int base = 0;
+    if (total && lane == leader) base = atomicAdd(counter, total);
+    base = __shfl(base, leader, VRM_WAVE);
+    return want ? base + before : -1;
+}
+
+struct StencilOut {
+    int32_t* small_idx;
+    float* small_f;
+    float* fii;
+    uint8_t* status;
+    int32_t* full_k;
+    int32_t* full_idx;
+    float* full_f;
+    uint16_t* feat;      // feature rows of solved LPs (collection), or NULL
+    float* lab;          // label rows (basis indicators, fractions) of solved LPs, or NULL
+    int max_rows;
+    const float* pred;   // warm start: small LPs 8 logits, complete ones kMlpOut outputs per queue item; or NULL
+    int32_t* prev;       // basis (column ids) of each particle's last stencil, [id][kPrevIds]: recorded if non-NULL
+    int prev_cap;        // rows of prev: particles with larger ids keep no basis (they start cold)
+    int use_prev;        // warm start from prev instead of pred
+    uint64_t* pmask;         // crash basis as a column mask per complete-neighbourhood queue item (size-binned path)
+    uint8_t* pivhist;        // by particle id (< prev_cap): pivots of its last cold complete LP
+    const int32_t* cloud_id;   // ids by cloud index
+    int32_t* sten_idx;   // [i][kStenRow] the stencils of the run are kept here (or NULL), see kStenRow
+    float* sten_f;
+};
+
+// entry e of particle i's kept stencil; the row's end: count of entries (-1: no stencil) and fhat_ii
+__device__ __forceinline__ void keep_entry(const StencilOut& out, int i, int e, int pj, float v)
+{
+    out.sten_idx[(size_t)i * kStenRow + e] = pj;
+    out.sten_f[(size_t)i * kStenRow + e] = v;
+}
+__device__ __forceinline__ void keep_end(const StencilOut& out, int i, int count, float fii)
+{
+    keep_entry(out, i, kStenRow - 1, count, fii);
+}
+
+constexpr int kPrevIds = 9;
+
+// the previous basis of particle `own` as a mask over columns with ids cid(j), j < k
+template <class ColId>
+__device__ __forceinline__ uint64_t prev_mask(const int32_t* prev, int own, int k, ColId cid)
+{
+    int pv[kPrevIds];
+#pragma unroll
+    for (int r = 0; r < kPrevIds; ++r) pv[r] = prev[(size_t)own * kPrevIds + r];
+    uint64_t m = 0;
+    for (int j = 0; j < k; ++j) {
+        const int id = cid(j);
+        if (id < 0) continue;
+        bool in = false;
+#pragma unroll
+        for (int r = 0; r < kPrevIds; ++r) in = in || pv[r] == id;
+        if (in) m |= 1ull << j;
+    }
+    return m;
+}
+
+// record the basic columns' ids as the particle's basis
+template <class ColId>
+__device__ __forceinline__ void record_basis(int32_t* prev, int own, uint64_t basis, ColId cid)
+{
+    int c = 0;
+    while (basis && c < kPrevIds) {
+        const int j = __ffsll((unsigned long long)basis) - 1;
+        basis &= basis - 1;
+        prev[(size_t)own * kPrevIds + c++] = cid(j);
+    }
+    for (; c < kPrevIds; ++c) prev[(size_t)own * kPrevIds + c] = -1;
+}
+
+__device__ __forceinline__ void count_add(int* p, bool v)
+{
+    uint64_t m = __ballot(v);
+    if (m && lane_id() == __ffsll((unsigned long long)m) - 1) atomicAdd(p, __popcll(m));
+}
+__device__ __forceinline__ void count_add(int64_t* p, bool v)
+{
+    uint64_t m = __ballot(v);
+    if (m && lane_id() == __ffsll((unsigned long long)m) - 1)
+        atomicAdd(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__popcll(m));
+}
+
+// Tie-break of the canonical cost: 2^-10 rank(id); for the removal LP (q = 1)
+// 2^-16 rank^2, convex in the rank because on a lattice the id ranks of
+// opposite neighbours are symmetric and would tie under a linear weight.
+// Exact in FP32 for ranks < 64.
+__device__ __forceinline__ float tie_weight(unsigned rank, int q)
+{
+    return q == 1 ? 0x1p-16f * (float)(rank * rank) : 0.0009765625f * (float)rank;
+}
+
+// add the tie-break to a double-float cost (exact at these magnitudes)
+__device__ __forceinline__ df add_rank(df C, int rank, int q)
+{
+    df w = two_sum(C.hi, tie_weight((unsigned)rank, q));
+    w.lo += C.lo;
+    return fast_two_sum(w.hi, w.lo);
+}
+
+__device__ __forceinline__ uint64_t member_key(float d2, int id)
+{
+    return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)id;
+}
+
+constexpr int kSiftW = 24;
+
+}  // namespace vrm
+
+// launcher (vrm_lp_group.hip): the complete LPs of the queue q_full with sixteen
+// lanes each, as the last LP launch of a stencil run
+int vrm_lp_group_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
+                     const vrm::StencilOut& out, int apply, bool stored, int max_blocks);

@@ -115,6 +115,47 @@ __device__ __forceinline__ df rhs_df(int a, const LaunchParams& P)
     return rhs_row<M>(a) ? df{P.bt_hi, P.bt_lo} : df{0.0f, 0.0f};
 }
 
+// Reduced cost d_j = c_j - y . v_j (phase II; 0 - y . v_j in phase I) and
+// the scale sum |c_j| + sum |y_a v_ja| its tolerance is relative to.
+template <int M>
+__device__ __forceinline__ void reduced(const float (&v)[M], float c, const float (&y)[M], bool p2,
+                                        float& d, float& sc)
+{
+    d = p2 ? c : 0.0f;
+    sc = fabsf(d);
+#pragma unroll
+    for (int a = 0; a < M; ++a) {
+        d = __builtin_fmaf(-y[a], v[a], d);
+        sc = __builtin_fmaf(fabsf(y[a]), fabsf(v[a]), sc);
+    }
+}
+
+// The same for the nine rows of q = 3 by Horner's scheme on the cubic
+// y . v(x, y) = x (y0 + y3 Y + x (y2 + y6 Y + y5 x)) + Y (y1 + Y (y4 + y7 x + y8 Y))
+// (9 operations instead of 7 monomials and 9 products), and its scale from
+// |y| and |x|, |Y| (the |monomials| are the monomials of |x|, |Y|).  p2f is
+// 1 in phase II, 0 in phase I: fma(p2f, c, -p) rounds as (p2 ? c : 0) - p
+// for a finite cost.
+template <int M>
+__device__ __forceinline__ void reduced_horner(float x, float Y, float c, const float (&y)[M],
+                                               const float (&ya)[M], float p2f, float& d, float& sc)
+{
+    static_assert(M == 9, "cubic rows");
+    const float a = __builtin_fmaf(x, y[5], __builtin_fmaf(Y, y[6], y[2]));
+    const float b = __builtin_fmaf(x, a, __builtin_fmaf(Y, y[3], y[0]));
+    const float e = __builtin_fmaf(Y, y[8], __builtin_fmaf(x, y[7], y[4]));
+    const float g = __builtin_fmaf(Y, e, y[1]);
+    const float p = __builtin_fmaf(x, b, Y * g);
+    const float ax = fabsf(x), ay = fabsf(Y);
+    const float aa = __builtin_fmaf(ax, ya[5], __builtin_fmaf(ay, ya[6], ya[2]));
+    const float ab = __builtin_fmaf(ax, aa, __builtin_fmaf(ay, ya[3], ya[0]));
+    const float ae = __builtin_fmaf(ay, ya[8], __builtin_fmaf(ax, ya[7], ya[4]));
+    const float ag = __builtin_fmaf(ay, ae, ya[1]);
+    const float ap = __builtin_fmaf(ax, ab, ay * ag);
+    d = __builtin_fmaf(p2f, c, -p);
+    sc = __builtin_fmaf(p2f, fabsf(c), ap);
+}
+
 // Column store interface (CS):
 //   int k; uint64_t dead;                            number of columns, absent ones
 //   void get(int j, float& rx, float& ry, float& c)  FP32 scaled offset and cost
@@ -381,45 +422,6 @@ struct ThreadSimplex {
             pivot(l, best, alpha, c);
             ++piv;
         }
-    }
-
-    // Reduced cost d_j = c_j - y . v_j (phase II; 0 - y . v_j in phase I) and
-    // the scale sum |c_j| + sum |y_a v_ja| its tolerance is relative to.
-    __device__ __forceinline__ static void reduced(const float (&v)[M], float c, const float (&y)[M], bool p2,
-                                                   float& d, float& sc)
-    {
-        d = p2 ? c : 0.0f;
-        sc = fabsf(d);
-#pragma unroll
-        for (int a = 0; a < M; ++a) {
-            d = __builtin_fmaf(-y[a], v[a], d);
-            sc = __builtin_fmaf(fabsf(y[a]), fabsf(v[a]), sc);
-        }
-    }
-
-    // The same for the nine rows of q = 3 by Horner's scheme on the cubic
-    // y . v(x, y) = x (y0 + y3 Y + x (y2 + y6 Y + y5 x)) + Y (y1 + Y (y4 + y7 x + y8 Y))
-    // (9 operations instead of 7 monomials and 9 products), and its scale from
-    // |y| and |x|, |Y| (the |monomials| are the monomials of |x|, |Y|).  p2f is
-    // 1 in phase II, 0 in phase I: fma(p2f, c, -p) rounds as (p2 ? c : 0) - p
-    // for a finite cost.
-    __device__ __forceinline__ static void reduced_horner(float x, float Y, float c, const float (&y)[M],
-                                                          const float (&ya)[M], float p2f, float& d, float& sc)
-    {
-        static_assert(M == 9, "cubic rows");
-        const float a = __builtin_fmaf(x, y[5], __builtin_fmaf(Y, y[6], y[2]));
-        const float b = __builtin_fmaf(x, a, __builtin_fmaf(Y, y[3], y[0]));
-        const float e = __builtin_fmaf(Y, y[8], __builtin_fmaf(x, y[7], y[4]));
-        const float g = __builtin_fmaf(Y, e, y[1]);
-        const float p = __builtin_fmaf(x, b, Y * g);
-        const float ax = fabsf(x), ay = fabsf(Y);
-        const float aa = __builtin_fmaf(ax, ya[5], __builtin_fmaf(ay, ya[6], ya[2]));
-        const float ab = __builtin_fmaf(ax, aa, __builtin_fmaf(ay, ya[3], ya[0]));
-        const float ae = __builtin_fmaf(ay, ya[8], __builtin_fmaf(ax, ya[7], ya[4]));
-        const float ag = __builtin_fmaf(ay, ae, ya[1]);
-        const float ap = __builtin_fmaf(ax, ab, ay * ag);
-        d = __builtin_fmaf(p2f, c, -p);
-        sc = __builtin_fmaf(p2f, fabsf(c), ap);
     }
 
     // Entering column: the columns are taken in groups of four in their order

@@ -67,3 +67,48 @@ def test_fixed_positions_apply_the_kept_stencils(vrm, q, objective, warm, tuning
     # the same stencils applied, in a third of the LP solves
     assert ca["redistributions"] == cb["redistributions"] > 0
     assert 3 * (ca["n_small"] + ca["n_full"]) == cb["n_small"] + cb["n_full"]
+
+
+def _stencils(vrm, x, y, g, P, mask, n):
+    cloud = vrm.Cloud(x, y, g, capacity=x.size + 64)
+    ctx = vrm.Context(cloud.capacity)
+    m = torch.zeros(cloud.capacity, dtype=torch.uint8, device="cuda")
+    m[:n] = torch.as_tensor(mask, device="cuda")
+    ctx.vrm_set_diffused(cloud, m)
+    st = vrm.Stencils.alloc(cloud.capacity)
+    ctx.vrm_solve_fractions(cloud, P, st)
+    torch.cuda.synchronize()
+    out = [t[:n].cpu().numpy() for t in (st.small_idx, st.small_f, st.fii, st.status, st.full_k, st.full_idx, st.full_f)]
+    c = ctx.vrm_read_counters()
+    return out, {k: c[k] for k in ("n_small", "n_full", "n_infeasible", "n_uncertified", "n_truncated", "pivots",
+                                   "full_cols")}
+
+
+@pytest.mark.parametrize("jitter,r_full,keep", [
+    (0.0, 3.0, 1.0),     # a lattice: degenerate LPs, exact certifications
+    (0.45, 3.0, 1.0),    # up to 48 columns
+    (0.45, 3.0, 0.35),   # holes: few columns, infeasible LPs, none at all
+    (0.3, 3.9, 1.0),     # 48 to 64 members: the 48 nearest
+    (0.3, 4.5, 1.0)])    # more than 64: the 48th nearest by bisection
+def test_sixteen_lane_complete_lps_match_one_thread_ones(vrm, jitter, r_full, keep):
+    """Small clouds solve the nine-row LPs with sixteen lanes each, large ones with one
+    thread: the same particles in a cloud padded past the limit with far, undiffused
+    ones get bit-identical stencils, in the same order, with the same pivots."""
+    print("case sixteen", jitter, r_full, keep, flush=True)
+    wl = workloads.config_jittered(h=0.04, q=3, seed=3, jitter=jitter)
+    sel = np.random.default_rng(7).random(wl.n) < keep
+    x, y, g = wl.x[sel], wl.y[sel], wl.gamma[sel]
+    n = x.size
+    P = vrm.make_params(wl.h, nu=wl.nu, q=3, dt=wl.dt, R_full=r_full)
+    mask = (np.arange(n) % 7 != 3).astype(np.uint8)
+    small = _stencils(vrm, x, y, g, P, mask, n)
+    side = 400
+    px, py = np.meshgrid(5.0 + 0.3 * np.arange(side), 5.0 + 0.3 * np.arange(side))
+    pad = np.zeros(side * side, np.float32)
+    large = _stencils(vrm, np.append(x, px.ravel().astype(np.float32)), np.append(y, py.ravel().astype(np.float32)),
+                      np.append(g, pad), P, mask, n)
+    assert n < (1 << 17) < n + pad.size
+    for a, b in zip(small[0], large[0]):
+        np.testing.assert_array_equal(a, b)
+    assert small[1] == large[1]
+    assert small[1]["n_full"] > 0
