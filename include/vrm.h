@@ -212,7 +212,9 @@ int vrm_solve_fractions(vrm_ctx* ctx, const vrm_cloud* cloud, const vrm_params* 
  * with L = (u, v, nu sum_j f_ji Gamma_j) evaluated at the current state.
  * u_dev, v_dev [N]: caller-supplied velocity at the current positions (NULL
  * for zero velocity).  Stage 0 records y^n.  Uses the diffused set of the
- * step. */
+ * step.  With q = 3 and the canonical objective a stage leaves the bases of its
+ * stencils in the context; the next stage checks them against its own LPs and
+ * solves only those the check does not settle (the same stencils either way). */
 int vrm_rk_stage(vrm_ctx* ctx, vrm_cloud* cloud, const float* u_dev, const float* v_dev,
                  const vrm_params* p, int stage);
 

@@ -232,8 +232,6 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(pivhist, cap);
     A(q_defer, cap);
     A(pmask, cap);
-    A(sten_idx, cap * vrm::kStenRow);
-    A(sten_f, cap * vrm::kStenRow);
 #undef A
     if (r == VRM_OK) {
         c->sort_tmp_bytes = std::max(vrm_sort_tmp_bytes(capacity), vrm_remove_tmp_bytes(capacity));
@@ -279,7 +277,7 @@ int vrm_destroy(vrm_ctx* c)
                     c->perm, c->xs, c->ys, c->ids, c->diffused, c->acc, c->x0, c->y0, c->g0, c->q_small, c->q_full, c->q_retry,
                     c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->ccell, c->crank, c->cstart, c->cperm,
                     c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->verify_buf, c->sort_tmp, c->full_cols,
-                    c->full_k, c->full_order, c->khist, c->lkey, c->pivhist, c->q_defer, c->pmask, c->sten_idx, c->sten_f};
+                    c->full_k, c->full_order, c->khist, c->lkey, c->pivhist, c->q_defer, c->pmask};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (c->q_host) (void)hipHostFree(c->q_host);
@@ -458,7 +456,9 @@ namespace {
 // be captured): the stage kernels read the particle count on the device and
 // size their grids for nb >= N.  fixed: the stages of one call without a velocity.
 // Their positions are the same, so the linear programs of stages 1 and 2 are those
-// of stage 0: stage 0 keeps its stencils, the others apply them.
+// of stage 0: stage 0 keeps its stencils, the others apply them.  Otherwise a stage
+// keeps its bases, from which the next stage of the step starts (each is checked
+// against the stage's own problem, so they are hints only).
 int stage_launch(vrm_ctx* c, vrm_cloud* cl, const float* u_dev, const float* v_dev, const vrm_params* p, int stage,
                  int nb, bool fixed = false)
 {
@@ -475,7 +475,8 @@ int stage_launch(vrm_ctx* c, vrm_cloud* cl, const float* u_dev, const float* v_d
         c->cells_valid = 1;
     }
     r = fixed && stage > 0 ? vrm_apply_run(c, cl, nb, L)
-                           : vrm_stencil_run(c, cl, nb, L, nullptr, 1, nullptr, nullptr, 0, fixed ? 1 : 0);
+                           : vrm_stencil_run(c, cl, nb, L, nullptr, 1, nullptr, nullptr, 0,
+                                             fixed ? vrm::kKeepStencils : vrm::kKeepBases, stage > 0);
     if (!r) {
         vrm::ScopedTimer tm(c, VRM_T_COMBINE);
         r = vrm_combine_run(c, cl, nb, u_dev, v_dev, p->dt, L.lam, stage, L.det);

@@ -159,6 +159,9 @@ constexpr int kMaxCert = 8;              // certification rounds: primal / dual 
 // last index holds their count, or -1 for a particle without a stencil, and the
 // last fraction fhat_ii.
 constexpr int kStenRow = 12;
+// what a stencil run leaves in the kept rows: nothing; the stencils; the columns that
+// carry the fractions (the basis from which a later stage's LPs start)
+constexpr int kKeepNone = 0, kKeepStencils = 1, kKeepBases = 2;
 
 // Fixed-point accumulation (deterministic mode): every contribution f Gamma is
 // rounded to a multiple of 2^(e - 46), where max |Gamma^n| < 2^e, and summed as
@@ -180,6 +183,14 @@ __device__ __forceinline__ void acc_add(float* acc, int j, float f, float g, dou
     else
         atomicAdd(acc + j, f * g);
 }
+
+// The kept rows of a context, by particle index: [cap][kStenRow] columns, then
+// [cap][kStenRow] fractions, in scratch that the runs of their order do not use (the
+// column lists of the nine-row LPs, the column records of the five-row ones).
+struct StenRows {
+    int32_t* idx;
+    float* f;
+};
 
 }  // namespace vrm
 
@@ -264,8 +275,6 @@ struct vrm_ctx {
     hipGraphExec_t graph_exec;
     unsigned char graph_key[256];
     double* t_dev;               // step start time read by the graph's velocity kernels
-    int32_t* sten_idx;           // [cap][kStenRow] stencils kept within one vrm_step call, by particle index:
-    float* sten_f;               // columns and fractions, then their count (-1: none) and fhat_ii
     int32_t* prev;               // [cap][9] basis (column ids) of each particle's last stencil, by id
     uint64_t* pmask;             // [cap] crash basis (previous or predicted) as a column mask per complete LP
     int32_t* lkey;               // [cap] bin of each complete LP for the counting sort (pivot history or doubt)
@@ -287,6 +296,12 @@ struct vrm_ctx {
 };
 
 namespace vrm {
+inline StenRows sten_rows(const vrm_ctx* c, int m)
+{
+    static_assert(2 * kStenRow <= VRM_KMAX && 2 * kStenRow <= 4 * VRM_NSEG, "the rows fit in the scratch");
+    int32_t* p = m == 5 ? c->full_cols : reinterpret_cast<int32_t*>(c->srec.off);
+    return {p, reinterpret_cast<float*>(p + (size_t)c->capacity * kStenRow)};
+}
 constexpr int kMaxTimed = 8192;
 constexpr int kGraphTimed = 64;   // the last kGraphTimed event pairs belong to the step graph
 // Bracket a group of launches with events when timing is on.
@@ -329,8 +344,8 @@ size_t vrm_remove_tmp_bytes(int32_t cap);
 // launchers (vrm_lp.hip)
 int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
                     const vrm_stencils* out, int apply, uint16_t* feat_out = nullptr, float* label_out = nullptr,
-                    int max_rows = 0, int keep = 0);
-// the update of the stencils kept by a vrm_stencil_run with keep = 1
+                    int max_rows = 0, int keep = vrm::kKeepNone, bool from_bases = false);
+// the update of the stencils kept by a vrm_stencil_run with kKeepStencils
 int vrm_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp);
 int vrm_small_nbhd_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
                        int32_t* small_idx, int32_t* kfull);

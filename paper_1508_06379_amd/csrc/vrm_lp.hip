@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/device/device_select.hpp>
 #include <rocprim/iterator/counting_iterator.hpp>
@@ -1089,7 +1090,7 @@ __global__ __launch_bounds__(kCollBlock) __attribute__((amdgpu_waves_per_eu(8)))
                                                              int32_t* khist, int32_t* q_retry, vrm_counters* cnt,
                                                              const int32_t* __restrict__ prev, int prev_cap,
                                                              uint64_t* pmask, const uint8_t* __restrict__ pivhist,
-                                                             int32_t* key)
+                                                             int32_t* key, int min_items)
 {
     static_assert(WM == 0 || WM == 2, "cold or previous-basis column lists");
     __shared__ __attribute__((aligned(16))) uint64_t s_key[kCollGroups][kMemStride];
@@ -1101,7 +1102,7 @@ __global__ __launch_bounds__(kCollBlock) __attribute__((amdgpu_waves_per_eu(8)))
     const int lane = lane_id(), gbase = lane & ~(kCollL - 1);
     for (int b = tid; b < kKBins; b += blockDim.x) s_hist[b] = 0;
     __syncthreads();
-    const int nitems = qs->n_full;
+    const int nitems = qs->n_full > min_items ? qs->n_full : 0;   // fewer: left to the sixteen-lane kernel
     const GridState g = *gs;
     const int ngroups = gridDim.x * kCollGroups;
     const int loops = (nitems + ngroups - 1) / ngroups;
@@ -1288,13 +1289,13 @@ __global__ void k_full_bin_starts(int32_t* khist)
 
 // order[pos] = queue item, grouped by k (decreasing); one atomic per bin and workgroup
 __global__ __launch_bounds__(256) void k_full_bin_scatter(const int32_t* __restrict__ kcol, const Queues* qs,
-                                                          int32_t* khist, int32_t* order)
+                                                          int32_t* khist, int32_t* order, int min_items)
 {
     __shared__ int s_cnt[kKBins], s_base[kKBins];
     const int tid = threadIdx.x;
     for (int b = tid; b < kKBins; b += blockDim.x) s_cnt[b] = 0;
     __syncthreads();
-    const int nitems = qs->n_full;
+    const int nitems = qs->n_full > min_items ? qs->n_full : 0;
     const int r = blockIdx.x * blockDim.x + tid;
     int k = -1, local = 0;
     if (r < nitems) {
@@ -1441,7 +1442,7 @@ __global__ __launch_bounds__(kFullBlock) __attribute__((amdgpu_waves_per_eu(2)))
     const int32_t* __restrict__ ids, const int32_t* __restrict__ order, const int32_t* __restrict__ kcol,
     const int32_t* __restrict__ rec, const int32_t* __restrict__ q_full, Queues* qs, const float* __restrict__ gamma,
     float* acc, LaunchParams P, StencilOut out, int apply, vrm_counters* cnt, int last_launch, const GridState* gs,
-    int32_t* q_defer, int defer_cold)
+    int32_t* q_defer, int defer_cold, int min_items)
 {
     // deferral: always for the warm launches (their cold re-solves run there),
     // for the cold one only when the host asks (large clouds)
@@ -1452,7 +1453,7 @@ __global__ __launch_bounds__(kFullBlock) __attribute__((amdgpu_waves_per_eu(2)))
     cnt = counter_stripe(cnt);
     const int tid = threadIdx.x;
     // the binned items, or the deferred ones
-    const int nitems = WM == 3 ? qs->n_defer : qs->n_full - qs->n_retry;
+    const int nitems = WM == 3 ? qs->n_defer : qs->n_full > min_items ? qs->n_full - qs->n_retry : 0;
     const int stride = gridDim.x * blockDim.x;
     const int loops = (nitems + stride - 1) / stride;
     const double dsc = P.det && apply ? det_scale(gs->gmax_bits) : 0.0;
@@ -1903,6 +1904,9 @@ int lp_group_blocks(const vrm_ctx* c, int m) { return min(c->tuning.lp_full_bloc
 // wave.  Collection and LPs per launch, sixteen lanes against one: 143 and 365 us for
 // 14k LPs, 270 and 510 us for 57k, 610 and 640 us for 143k.
 constexpr int kGroupMaxN = 1 << 17;
+// LPs left by a check of known bases up to which they take sixteen lanes each (4.3 ns an
+// LP; the one-thread launches take 2.0 ns an LP and at least 0.6 ms)
+constexpr int kGroupMaxItems = 1 << 18;
 // workgroups of the neighbourhood kernel: 256 particles each, or 256 / kNbL
 // with kNbL lanes per particle up to kNbhdCoopMaxN particles
 int nbhd_blocks(int n) { return n <= kNbhdCoopMaxN ? (n + 256 / kNbL - 1) / (256 / kNbL) : (n + 255) / 256; }
@@ -1938,14 +1942,20 @@ int vrm_small_nbhd_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchP
 }
 
 int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, const vrm_stencils* st,
-                    int apply, uint16_t* feat_out, float* label_out, int max_rows, int keep)
+                    int apply, uint16_t* feat_out, float* label_out, int max_rows, int keep,
+                    bool from_bases)
 {
     if (n <= 0) return VRM_OK;
     StencilOut out{};
-    if (keep) {
-        out.sten_idx = c->sten_idx;
-        out.sten_f = c->sten_f;
+    if (keep == kKeepStencils || (keep == kKeepBases && lp.m == 9 && lp.phase1 == 0)) {
+        const StenRows rows = sten_rows(c, lp.m);
+        out.sten_idx = rows.idx;
+        out.sten_f = reinterpret_cast<int32_t*>(rows.f) - rows.idx;
     }
+    // nine-row canonical LPs of the update start from a known basis where there is one:
+    // the stage before, or the previous stencil (warm start 2)
+    const bool prev_bases = c->warm == 2 && !from_bases;
+    const bool verify = apply && lp.m == 9 && lp.phase1 == 0 && out.sten_idx && (from_bases || prev_bases);
     if (st) {
         out.small_idx = st->small_idx_dev;
         out.small_f = st->small_f_dev;
@@ -1961,7 +1971,12 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
     out.lab = label_out;
     out.max_rows = max_rows;
     // the LP queues are empty here: the last LP launch of every run empties them
-    {
+    if (verify) {
+        ScopedTimer tm(c, VRM_T_LP_FULL);
+        int r = prev_bases ? vrm_bases_from_prev_run(c, cl, n) : VRM_OK;
+        if (!r) r = vrm_verify_bases_run(c, cl, n, lp, keep == kKeepStencils, c->warm == 2);
+        if (r) return r;
+    } else {
         ScopedTimer tm(c, VRM_T_NBHD);
         const bool coop = n <= kNbhdCoopMaxN;
         hipLaunchKernelGGL(coop ? k_small_nbhd_coop : k_small_nbhd, dim3(nbhd_blocks(n)), dim3(256), 0, c->stream, n,
@@ -2014,18 +2029,20 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         o2.lab = nullptr;
         ScopedTimer tm(c, VRM_T_LP_FULL);
         const bool stored = full_stored_costs(c, n);
-        if (lp.phase1 == 0) return vrm_lp_group_run(c, cl, n, lp, o2, apply, stored, lp_group_blocks(c, lp.m));
+        if (lp.phase1 == 0) return vrm_lp_group_run(c, cl, n, lp, o2, apply, stored, INT_MAX, lp_group_blocks(c, lp.m));
         hipLaunchKernelGGL((stored ? full_kernel<5, true>(lp.phase1) : full_kernel<5, false>(lp.phase1)),
                            dim3(min(lp_grid_full(c, n), 64)), dim3(kFullBlock), 0, c->stream, c->perm,
                            c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp,
                            o2, apply, c->counters, kLpPlain, c->q_retry, 1);
-    } else if (!feat_out && !warm && lp.phase1 == 0 && n <= kGroupMaxN) {
+    } else if (!feat_out && lp.phase1 == 0 && n <= kGroupMaxN && (!warm || verify)) {
         ScopedTimer tm(c, VRM_T_LP_FULL);
-        return vrm_lp_group_run(c, cl, n, lp, out, apply, false, lp_group_blocks(c, lp.m));
+        return vrm_lp_group_run(c, cl, n, lp, out, apply, false, INT_MAX, lp_group_blocks(c, lp.m));
     } else if (!feat_out) {
         // size-binned working-set path: column lists (with the previous basis),
         // counting sort, the network's inference from the lists if it predicts, LPs
-        const int wm = net ? 1 : (warm ? 2 : 0);
+        const int wm = net && !verify ? 1 : (c->warm == 2 ? 2 : 0);
+        // after a check of known bases few LPs are left, and these launches find nothing
+        const int min_items = verify ? kGroupMaxItems : 0;
         {
             ScopedTimer tm(c, VRM_T_FULL_COLS);
             auto collect = wm == 2 ? k_full_collect<2> : k_full_collect<0>;
@@ -2033,10 +2050,10 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
                                c->stream, c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, lp,
                                c->full_cols, c->full_k, c->khist, c->q_retry, c->counters,
                                wm == 2 ? c->prev : nullptr, c->capacity, wm == 2 ? c->pmask : nullptr, c->pivhist,
-                               c->lkey);
+                               c->lkey, min_items);
             hipLaunchKernelGGL(k_full_bin_starts, dim3(1), dim3(64), 0, c->stream, c->khist);
             hipLaunchKernelGGL(k_full_bin_scatter, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->lkey,
-                               c->queues, c->khist, c->full_order);
+                               c->queues, c->khist, c->full_order, min_items);
             VRM_HIP(hipGetLastError());
         }
         if (wm == 1) {
@@ -2065,16 +2082,19 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
                             : (obj == 1 ? k_lp_sift<9, kSiftW, 1, 2> : k_lp_sift<9, kSiftW, 0, 2>);
         hipLaunchKernelGGL(sift, dim3(lp_grid_full(c, n)), dim3(kFullBlock), 0, c->stream, c->perm, c->xs, c->ys,
                            c->ids, c->full_order, c->full_k, c->full_cols, c->q_full, c->queues, cl->gamma_dev, c->acc,
-                           lp, out, apply, c->counters, 0, c->grid, c->q_defer, defer_cold);
+                           lp, out, apply, c->counters, 0, c->grid, c->q_defer, defer_cold, min_items);
         if (obj == 0 && (wm != 0 || defer_cold)) {
             // what the launch deferred, from the bases (count read on the device)
             hipLaunchKernelGGL((k_lp_sift<9, kSiftW, 0, 3>), dim3(lp_grid_full(c, n)), dim3(kFullBlock), 0, c->stream,
                                c->perm, c->xs, c->ys, c->ids, c->full_order, c->full_k, c->full_cols, c->q_full,
                                c->queues, cl->gamma_dev, c->acc, lp, out, apply, c->counters, 0, c->grid, c->q_defer,
-                               0);
+                               0, 0);
         }
-        // lists too long for the collection groups (none in practice): the one-thread
-        // kernel from the retry queue, cold; as the run's last LP launch it empties the queues
+        // lists too long for the collection groups (none in practice), and what a check of
+        // known bases left where that is little, cold; the run's last LP launch empties the queues
+        if (obj == 0)
+            return vrm_lp_group_run(c, cl, n, lp, out, apply, false, verify ? min_items : -1,
+                                    lp_group_blocks(c, verify ? 9 : 5));
         hipLaunchKernelGGL((full_kernel<9, false>(lp.phase1)), dim3(1), dim3(kFullBlock), 0, c->stream, c->perm, c->xs,
                            c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp, out,
                            apply, c->counters, kLpRetry, c->q_retry, 1);
@@ -2097,8 +2117,9 @@ int vrm_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams
 {
     if (n <= 0) return VRM_OK;
     ScopedTimer tm(c, lp.m == 5 ? VRM_T_LP_SMALL : VRM_T_LP_FULL);
-    hipLaunchKernelGGL(k_apply, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->diffused, c->sten_idx,
-                       c->sten_f, cl->gamma_dev, c->acc, lp.det, c->grid, c->counters);
+    const StenRows rows = sten_rows(c, lp.m);
+    hipLaunchKernelGGL(k_apply, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->diffused, rows.idx,
+                       rows.f, cl->gamma_dev, c->acc, lp.det, c->grid, c->counters);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
@@ -2151,7 +2172,7 @@ int vrm_warm_predict_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const Launc
         hipLaunchKernelGGL(k_full_collect<0>, dim3(min((n + kCollGroups - 1) / kCollGroups, 4096)), dim3(kCollBlock),
                            0, c->stream, c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, lp,
                            c->full_cols, c->full_k, c->khist, c->q_retry, c->counters, nullptr, c->capacity, nullptr,
-                           c->pivhist, c->lkey);
+                           c->pivhist, c->lkey, 0);
         hipLaunchKernelGGL(k_full_bin_starts, dim3(1), dim3(64), 0, c->stream, c->khist);
         VRM_HIP(hipGetLastError());
         const FullRec fr{c->full_cols, kRecRow, c->full_k, c->q_full, c->xs, c->ys, lp.scale2e, lp.sc, lp.q};

@@ -53,14 +53,15 @@ struct StencilOut {
     uint8_t* pivhist;        // by particle id (< prev_cap): pivots of its last cold complete LP
     const int32_t* cloud_id;   // ids by cloud index
     int32_t* sten_idx;   // [i][kStenRow] the stencils of the run are kept here (or NULL), see kStenRow
-    float* sten_f;
+    ptrdiff_t sten_f;    // distance from a column's entry to its fraction
 };
 
 // entry e of particle i's kept stencil; the row's end: count of entries (-1: no stencil) and fhat_ii
 __device__ __forceinline__ void keep_entry(const StencilOut& out, int i, int e, int pj, float v)
 {
-    out.sten_idx[(size_t)i * kStenRow + e] = pj;
-    out.sten_f[(size_t)i * kStenRow + e] = v;
+    int32_t* p = out.sten_idx + (size_t)i * kStenRow + e;
+    p[0] = pj;
+    p[out.sten_f] = __float_as_int(v);
 }
 __device__ __forceinline__ void keep_end(const StencilOut& out, int i, int count, float fii)
 {
@@ -139,7 +140,15 @@ constexpr int kSiftW = 24;
 
 }  // namespace vrm
 
-// launcher (vrm_lp_group.hip): the complete LPs of the queue q_full with sixteen
-// lanes each, as the last LP launch of a stencil run
+// launcher (vrm_lp_group.hip): complete LPs with sixteen lanes each, as the last LP
+// launch of a stencil run: those of the queue q_full, or, where it holds more than
+// `limit` (the launches before have then solved them), those left in q_retry
 int vrm_lp_group_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
-                     const vrm::StencilOut& out, int apply, bool stored, int max_blocks);
+                     const vrm::StencilOut& out, int apply, bool stored, int limit, int max_blocks);
+// launchers (vrm_verify.hip): the nine-row LPs of the diffused particles from the bases
+// in the kept rows; what they do not settle is queued in q_full.  keep_f: also keep the
+// fractions.  count_hits: the settled ones are warm-start hits.
+int vrm_verify_bases_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, bool keep_f,
+                         bool count_hits);
+// the kept rows from the bases recorded by particle id (c->prev)
+int vrm_bases_from_prev_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n);

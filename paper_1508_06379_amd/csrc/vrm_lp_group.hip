@@ -609,7 +609,7 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
                                                       const int32_t* __restrict__ q_full, Queues* qs,
                                                       const float* __restrict__ gamma, float* acc, LaunchParams P,
                                                       StencilOut out, int apply, vrm_counters* cnt, int exact_n,
-                                                      int work)
+                                                      int work, const int32_t* __restrict__ q_retry, int limit)
 {
     enum { kPiv, kCols, kFull, kInf, kUnc, kTrunc, kRounds, kExact, kCounts };
     __shared__ GroupLds lds[kGGroups];
@@ -618,11 +618,14 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
     GroupLds& L = lds[tid / kGL];
     if (tid < kCounts) s_cnt[tid] = 0;
     __syncthreads();
-    const int nitems = qs->n_full;
+    // more than `limit` in q_full: the launches before solved them, but for the retry queue
+    const bool left = qs->n_full > limit;
+    const int nitems = left ? qs->n_retry : qs->n_full;
+    const int32_t* __restrict__ queue = left ? q_retry : q_full;
     const GridState g = *gs;
     const double dsc = P.det && apply ? det_scale(g.gmax_bits) : 0.0;
     for (int item = blockIdx.x * kGGroups + tid / kGL; item < nitems; item += gridDim.x * kGGroups) {
-        const int t = q_full[item];
+        const int t = queue[item];
         const int i = perm[t];
         const float xi = xs[t], yi = ys[t];
         lds_fence();   // the previous LP's reads are done
@@ -838,17 +841,16 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
 
 }  // namespace
 
-// Complete LPs of the queue q_full (canonical stencils, cold), as the last LP launch
-// of a stencil run.  stored: the one-thread kernel of the same cloud keeps its costs.
+// Canonical stencils, cold.  stored: the one-thread kernel of the same cloud keeps its costs.
 int vrm_lp_group_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, const StencilOut& out,
-                     int apply, bool stored, int max_blocks)
+                     int apply, bool stored, int limit, int max_blocks)
 {
     const int grid = std::max(1, std::min((n + kGGroups - 1) / kGGroups, max_blocks));
     const int exact_n = lp.m == 9 ? kSiftW : (stored ? VRM_KMAX : 0);
     const int work = lp.m == 9 ? kSiftW : VRM_KMAX;
     hipLaunchKernelGGL((lp.m == 9 ? k_lp_group<9> : k_lp_group<5>), dim3(grid), dim3(kGBlock), 0, c->stream, c->perm,
                        c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp,
-                       out, apply, c->counters, exact_n, work);
+                       out, apply, c->counters, exact_n, work, c->q_retry, limit);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }

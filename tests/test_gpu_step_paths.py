@@ -112,3 +112,88 @@ def test_sixteen_lane_complete_lps_match_one_thread_ones(vrm, jitter, r_full, ke
         np.testing.assert_array_equal(a, b)
     assert small[1] == large[1]
     assert small[1]["n_full"] > 0
+
+
+def _flow_run(vrm, wl, P, vt, warm, hints, steps, u, v):
+    """`steps` steps by single stages; hints: the stages of a step one after the other;
+    else a selection between them, after which a stage starts from no basis."""
+    cloud = vrm.Cloud(wl.x, wl.y, wl.gamma, capacity=4 * wl.n)
+    ctx = vrm.Context(cloud.capacity)
+    ctx.vrm_set_warm_start(warm)
+    t = wl.t0
+    for _ in range(steps):
+        ctx.vrm_insert_particles(cloud, P)
+        for s, c in enumerate((0.0, 1.0, 0.5)):
+            ctx.vrm_vortex_velocity(cloud, vt, wl.nu, t + c * wl.dt, u, v)
+            ctx.vrm_rk_stage(cloud, P, s, u, v)
+        t += wl.dt
+    torch.cuda.synchronize()
+    return _by_id(cloud), ctx.vrm_read_counters()
+
+
+@pytest.mark.parametrize("scale", [1.0, 40.0])
+@pytest.mark.parametrize("warm", [0, 2])
+def test_stages_from_the_bases_of_the_stage_before(vrm, orc, warm, scale):
+    """q = 3 with a prescribed flow: stages 1 and 2 check the bases of the stage before
+    (warm start 2: also the step's first stage, the previous step's) and solve only what
+    the check does not settle.  The same Gamma as the FP64 oracle's step, also with a
+    velocity forty times larger, where many bases change within a step."""
+    wl = workloads._vortex_cloud("flow", -0.5, 0.5, 0.02, 3, 3, 31, 32, 0.1, 3)
+    wl.vortices["gamma"] = wl.vortices["gamma"] * scale
+    P = vrm.params_of(wl)
+    vt = vrm.vortex_table(wl.vortices)
+    u = torch.zeros(4 * wl.n, device="cuda")
+    v = torch.zeros(4 * wl.n, device="cuda")
+    (ids, x, y, g), c = _flow_run(vrm, wl, P, vt, warm, True, 2, u, v)
+    ref = orc.run(wl, steps=2)
+    print("case bases", warm, scale, "N", ids.size, ref.x.size, c, flush=True)
+    np.testing.assert_array_equal(ids, ref.ids)
+    # Gamma within the stated 1e-5 of the oracle
+    assert _rel(g, ref.gamma) <= 1e-5
+    assert c["redistributions"] == c["n_full"] > 0
+    if scale == 1.0:
+        # one LP in three (first step of warm start 2: the same) takes pivots, nine or more each
+        assert c["pivots"] < 0.5 * 12 * c["n_full"]
+    if warm == 2:
+        assert c["warm_hit"] > 0
+
+
+def test_changed_bases_are_solved_again(vrm):
+    """Kept bases are hints: a stage whose particles were moved far from those of stage 0
+    (other neighbourhoods altogether) gives the stencils of its own positions."""
+    wl = workloads.config_jittered(h=0.05, q=3, seed=4)
+    P = vrm.params_of(wl)
+    rng = np.random.default_rng(5)
+    n = wl.n
+    perm = rng.permutation(n)
+    out = []
+    for hints in (True, False):
+        cloud = vrm.Cloud(wl.x, wl.y, wl.gamma, capacity=n + 64)
+        ctx = vrm.Context(cloud.capacity)
+        ctx.vrm_set_diffused(cloud, torch.ones(cloud.capacity, dtype=torch.uint8, device="cuda"))
+        zero = torch.zeros(cloud.capacity, device="cuda")
+        ctx.vrm_rk_stage(cloud, P, 0, zero, zero)
+        g1 = cloud.gamma.clone()
+        # other positions for every particle, from outside (the velocity of stage 0 leaves
+        # the cell list to be rebuilt)
+        cloud.x[:n] = torch.as_tensor(wl.x[perm], device="cuda")
+        cloud.y[:n] = torch.as_tensor(wl.y[perm], device="cuda")
+        ctx.vrm_rk_stage(cloud, P, 1, zero, zero) if hints else None
+        if hints:
+            # stage 1: g = 3/4 g0 + 1/4 (g1 + dt rate); the rate from the stencils
+            torch.cuda.synchronize()
+            got = cloud.gamma[:n].double().cpu().numpy()
+        else:
+            st = vrm.Stencils.alloc(cloud.capacity)
+            ctx.vrm_solve_fractions(cloud, P, st)
+            torch.cuda.synchronize()
+            rate = np.zeros(n)
+            gg = g1[:n].double().cpu().numpy()
+            k, idx, f = (t.cpu().numpy() for t in (st.full_k, st.full_idx, st.full_f))
+            for i in range(n):
+                np.add.at(rate, idx[i, :k[i]], f[i, :k[i]].astype(np.float64) * gg[i])
+            rate += st.fii[:n].double().cpu().numpy() * gg
+            lam = wl.nu / wl.h ** 2
+            out.append(0.75 * wl.gamma.astype(np.float64) + 0.25 * (gg + wl.dt * lam * rate))
+    print("case changed bases", flush=True)
+    assert _rel(got, out[0]) <= 1e-6
