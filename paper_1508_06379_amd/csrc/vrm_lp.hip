@@ -62,54 +62,7 @@ __global__ __launch_bounds__(256) void k_small_nbhd(int n, const int32_t* __rest
         s_best[s * 256 + tid] = -1;
     }
     if (dif && (P.m <= VRM_NSEG || want_kfull)) {
-        GridState g = *gs;
-        float xi = xs[t], yi = ys[t];
-        int cx, cy;
-        cell_of_pos(g, xi, yi, cx, cy);
-        for (int oy = -1; oy <= 1; ++oy) {
-            int yy = cy + oy;
-            if (yy < 0 || yy >= g.ny) continue;
-            {
-                // the three cells of this row are contiguous in slot order
-                int c0 = yy * g.nx + max(cx - 1, 0), c1 = yy * g.nx + min(cx + 1, g.nx - 1);
-                int u0 = cell_start[c0], u1 = cell_start[c1 + 1];
-                // positions read eight at a time: one memory latency per eight candidates
-                for (int ub = u0; ub < u1; ub += 8) {
-                    float bx[8], by[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int v = min(ub + e, u1 - 1);   // past the end: a repeat, not visited
-                        bx[e] = xs[v];
-                        by[e] = ys[v];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int u = ub + e;
-                        if (u >= u1 || u == t) continue;
-                        float dx = bx[e] - xi;
-                        float dy = by[e] - yi;
-                        float d2 = d2_f32(dx, dy);
-                        if (d2 < P.lo2) continue;
-                        if (d2 <= P.hi2f) ++kfull;
-                        if (d2 > P.hi2) continue;
-                        const int at = segment_f32(dx, dy) * 256 + tid;
-                        const float cur = s_bd[at];
-                        if (d2 <= cur) {
-                            bool take = d2 < cur;
-                            if (!take) {
-                                // equal distance: the smaller id wins
-                                const int cb = s_best[at];
-                                take = cb >= 0 && ids[u] < ids[cb];
-                            }
-                            if (take) {
-                                s_bd[at] = d2;
-                                s_best[at] = u;
-                            }
-                        }
-                    }
-                }
-            }
-        }
+        scan_segments(t, xs[t], ys[t], *gs, cell_start, xs, ys, ids, P, s_bd, s_best, tid, kfull);
 #pragma unroll
         for (int s = 0; s < VRM_NSEG; ++s) {
             best[s] = s_best[s * 256 + tid];
@@ -130,33 +83,7 @@ __global__ __launch_bounds__(256) void k_small_nbhd(int n, const int32_t* __rest
         int p1 = block_append_n(&qs->n_small, small_ok ? 1 : 0, s_app);
         if (small_ok) {
             q_small[p1] = t;
-            rec.i[p1] = i;
-            const size_t cap = (size_t)rec.cap;
-            const float xi = xs[t], yi = ys[t];
-            int idb[VRM_NSEG];
-#pragma unroll
-            for (int s = 0; s < VRM_NSEG; ++s) idb[s] = best[s] >= 0 ? ids[best[s]] : 0x7fffffff;
-            int packed = 0;
-#pragma unroll
-            for (int s = 0; s < VRM_NSEG; ++s) {
-                int rank = 0;
-#pragma unroll
-                for (int o = 0; o < VRM_NSEG; ++o) rank += idb[o] < idb[s] ? 1 : 0;
-                packed |= rank << (3 * s);
-                const int u = best[s];
-                df X{0.0f, 0.0f}, Y{0.0f, 0.0f};
-                int pj = -1;
-                if (u >= 0) {
-                    exact_offset(xi, yi, xs[u], ys[u], P.scale2e, X, Y);
-                    pj = perm[u];
-                }
-                rec.pj[s * cap + p1] = pj;
-                rec.off[(4 * s + 0) * cap + p1] = X.hi;
-                rec.off[(4 * s + 1) * cap + p1] = X.lo;
-                rec.off[(4 * s + 2) * cap + p1] = Y.hi;
-                rec.off[(4 * s + 3) * cap + p1] = Y.lo;
-            }
-            rec.rank[p1] = packed;
+            write_small_record(rec, p1, i, xs[t], ys[t], best, perm, xs, ys, ids, P);
         }
         bool full = dif && !small_ok;
         int p2 = block_append_n(&qs->n_full, full ? 1 : 0, s_app);
@@ -651,6 +578,7 @@ __global__ __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_eu(3))
             if (st == 0) {
                 float g = gamma[i];
                 int nz = 0;
+                uint32_t carry = 0;
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
                     bool alive = !((dead >> s) & 1ull);
@@ -659,6 +587,7 @@ __global__ __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_eu(3))
                         acc_add(acc, pj, fv[s], g, dsc);
                         if (out.sten_idx) keep_entry(out, i, nz, pj, fv[s]);
                         ++nz;
+                        carry |= 1u << s;
                     }
                     if (out.small_f) {
                         out.small_idx[(size_t)i * VRM_NSEG + s] = pj;
@@ -667,6 +596,7 @@ __global__ __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_eu(3))
                 }
                 if (apply) acc_add(acc, i, fii, g, dsc);
                 if (out.sten_idx) keep_end(out, i, nz, fii);
+                if (out.seg_mask) out.seg_mask[i] = (uint8_t)carry;
                 if (out.small_f) {
                     out.fii[i] = fii;
                     out.status[i] = (warm == 1 || warm == 2) ? VRM_ST_WARM : VRM_ST_SMALL;
@@ -748,10 +678,22 @@ __global__ __launch_bounds__(kSmallBlock) void k_lp_small_coop(const float* __re
                 const float g = gamma[i];
                 if (apply && fv != 0.0f) acc_add(acc, pj, fv, g, dsc);
                 if (apply && lead) acc_add(acc, i, fii, g, dsc);
-                if (out.sten_idx) {
+                if (out.sten_idx || out.seg_mask) {
                     const uint32_t m = (uint32_t)(__ballot(fv != 0.0f) >> base) & 0xFFu;
-                    if (fv != 0.0f) keep_entry(out, i, __popc(m & ((1u << s) - 1u)), pj, fv);
-                    if (lead) keep_end(out, i, __popc(m), fii);
+                    if (out.seg_mask && lead) out.seg_mask[i] = (uint8_t)m;
+                    if (out.sten_idx && fv != 0.0f) keep_entry(out, i, __popc(m & ((1u << s) - 1u)), pj, fv);
+                    if (out.sten_idx && lead) keep_end(out, i, __popc(m), fii);
+                }
+                if (out.prev) {
+                    // the basic columns' ids, by segment, as the particle's basis
+                    const int o = out.cloud_id[i];
+                    if ((unsigned)o < (unsigned)out.prev_cap) {
+                        const int have = __popcll(basis);
+                        int32_t* row = out.prev + (size_t)o * kPrevIds;
+                        if ((basis >> s) & 1ull) row[__popcll(basis & ((1ull << s) - 1ull))] = out.cloud_id[pj];
+                        if (s >= have) row[s] = -1;
+                        if (lead) row[kPrevIds - 1] = -1;
+                    }
                 }
                 if (out.small_f) {
                     out.small_idx[(size_t)i * VRM_NSEG + s] = alive ? pj : -1;
@@ -1952,10 +1894,13 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         out.sten_idx = rows.idx;
         out.sten_f = reinterpret_cast<int32_t*>(rows.f) - rows.idx;
     }
-    // nine-row canonical LPs of the update start from a known basis where there is one:
-    // the stage before, or the previous stencil (warm start 2)
+    // the five-row LPs keep their basis as a mask of segments (the reorder scratch is free here)
+    if (keep == kKeepBases && lp.m == 5 && lp.phase1 == 0) out.seg_mask = c->tmp_u8;
+    // canonical LPs of the update start from a known basis where there is one: the stage
+    // before, or the previous stencil (warm start 2)
     const bool prev_bases = c->warm == 2 && !from_bases;
-    const bool verify = apply && lp.m == 9 && lp.phase1 == 0 && out.sten_idx && (from_bases || prev_bases);
+    const bool verify = apply && lp.phase1 == 0 && (lp.m == 9 ? out.sten_idx != nullptr : keep == kKeepBases) &&
+                        (from_bases || prev_bases);
     if (st) {
         out.small_idx = st->small_idx_dev;
         out.small_f = st->small_f_dev;
@@ -1971,7 +1916,11 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
     out.lab = label_out;
     out.max_rows = max_rows;
     // the LP queues are empty here: the last LP launch of every run empties them
-    if (verify) {
+    if (verify && lp.m == 5) {
+        ScopedTimer tm(c, VRM_T_NBHD);
+        int r = vrm_verify_small_run(c, cl, n, lp, c->warm == 2 ? c->prev : nullptr, prev_bases);
+        if (r) return r;
+    } else if (verify) {
         ScopedTimer tm(c, VRM_T_LP_FULL);
         int r = prev_bases ? vrm_bases_from_prev_run(c, cl, n) : VRM_OK;
         if (!r) r = vrm_verify_bases_run(c, cl, n, lp, keep == kKeepStencils, c->warm == 2);
@@ -1986,13 +1935,15 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
     VRM_HIP(hipGetLastError());
     const bool net = c->warm == 1 && c->mlp && c->mlp->loaded && !feat_out;
     const bool warm = net || (c->warm == 2 && !feat_out);
+    // the five-row LPs that a check of known bases leaves are solved cold
+    const bool warm_small = warm && !verify;
     out.cloud_id = cl->id_dev;
     if (c->warm == 2 && c->prev && !feat_out) {
         out.prev = c->prev;
         out.prev_cap = c->capacity;
         out.use_prev = 1;
     }
-    if (net && lp.m == 5) {
+    if (net && lp.m == 5 && !verify) {
         // network inputs of the queued small LPs and the forward pass, fused (row count read on the device)
         ScopedTimer tm(c, VRM_T_MLP);
         int r = vrm_mlp_infer_small_run(c, n, &c->queues->n_small, c->srec, lp.sc, lp.q, c->pred);
@@ -2000,11 +1951,12 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         out.pred = c->pred;
     }
     // warm: the pass from the predicted bases, then a cold pass over what it left
-    const int first = warm ? kLpWarm : kLpPlain;
+    const int first = warm_small ? kLpWarm : kLpPlain;
     if (lp.m == 5) {
         {
             ScopedTimer tm(c, VRM_T_LP_SMALL);
-            if (!warm && c->tuning.lp_small_coop && !feat_out && lp.phase1 != 2) {
+            // (always for the few LPs that a check of known bases leaves: a launch's latency)
+            if (!warm_small && (c->tuning.lp_small_coop || verify) && !feat_out && lp.phase1 != 2) {
                 // eight lanes per LP (plain or phase-I pass)
                 const int per_block = kSmallBlock / 8;
                 const int grid = min((n + per_block - 1) / per_block, c->tuning.lp_small_blocks);
@@ -2013,7 +1965,7 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
                                    c->q_full, c->acc, lp, out, apply, c->counters, c->grid);
                 VRM_HIP(hipGetLastError());
             } else {
-                for (int mode = first; mode <= (warm ? kLpRetry : kLpPlain); ++mode) {
+                for (int mode = first; mode <= (warm_small ? kLpRetry : kLpPlain); ++mode) {
                     hipLaunchKernelGGL((by_objective(lp.phase1, k_lp_small<0>, k_lp_small<1>, k_lp_small<2>)), dim3(lp_grid_small(c, n)),
                                        dim3(kSmallBlock), 0, c->stream, c->perm, c->xs, c->ys, c->ids, c->srec,
                                        c->q_small, c->queues, c->q_full, cl->gamma_dev, c->acc, lp, out, apply,

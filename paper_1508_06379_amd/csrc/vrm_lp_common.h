@@ -53,6 +53,7 @@ struct StencilOut {
     uint8_t* pivhist;        // by particle id (< prev_cap): pivots of its last cold complete LP
     const int32_t* cloud_id;   // ids by cloud index
     int32_t* sten_idx;   // [i][kStenRow] the stencils of the run are kept here (or NULL), see kStenRow
+    uint8_t* seg_mask;   // [i] segments that carry a five-row LP's fractions, kept for the next stage, or NULL
     ptrdiff_t sten_f;    // distance from a column's entry to its fraction
 };
 
@@ -138,6 +139,94 @@ __device__ __forceinline__ uint64_t member_key(float d2, int id)
 
 constexpr int kSiftW = 24;
 
+// The closest member of each 45-degree segment around slot t (Sec. 4.3, ties by the
+// smaller id) into s_bd, s_best [segment][256 threads]; adds to kfull the members
+// within R_full h.
+__device__ __forceinline__ void scan_segments(int t, float xi, float yi, const GridState& g,
+                                              const int32_t* __restrict__ cell_start, const float* __restrict__ xs,
+                                              const float* __restrict__ ys, const int32_t* __restrict__ ids,
+                                              const LaunchParams& P, float* s_bd, int* s_best, int tid, int& kfull)
+{
+    int cx, cy;
+    cell_of_pos(g, xi, yi, cx, cy);
+    for (int oy = -1; oy <= 1; ++oy) {
+        int yy = cy + oy;
+        if (yy < 0 || yy >= g.ny) continue;
+        // the three cells of this row are contiguous in slot order
+        int c0 = yy * g.nx + max(cx - 1, 0), c1 = yy * g.nx + min(cx + 1, g.nx - 1);
+        int u0 = cell_start[c0], u1 = cell_start[c1 + 1];
+        // positions read eight at a time: one memory latency per eight candidates
+        for (int ub = u0; ub < u1; ub += 8) {
+            float bx[8], by[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int v = min(ub + e, u1 - 1);   // past the end: a repeat, not visited
+                bx[e] = xs[v];
+                by[e] = ys[v];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int u = ub + e;
+                if (u >= u1 || u == t) continue;
+                float dx = bx[e] - xi;
+                float dy = by[e] - yi;
+                float d2 = d2_f32(dx, dy);
+                if (d2 < P.lo2) continue;
+                if (d2 <= P.hi2f) ++kfull;
+                if (d2 > P.hi2) continue;
+                const int at = segment_f32(dx, dy) * 256 + tid;
+                const float cur = s_bd[at];
+                if (d2 <= cur) {
+                    bool take = d2 < cur;
+                    if (!take) {
+                        // equal distance: the smaller id wins
+                        const int cb = s_best[at];
+                        take = cb >= 0 && ids[u] < ids[cb];
+                    }
+                    if (take) {
+                        s_bd[at] = d2;
+                        s_best[at] = u;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// the column record of a queued small LP (see SmallRec): its members in best (slots, -1: none)
+__device__ __forceinline__ void write_small_record(const SmallRec& rec, int p1, int i, float xi, float yi,
+                                                   const int (&best)[VRM_NSEG], const int32_t* __restrict__ perm,
+                                                   const float* __restrict__ xs, const float* __restrict__ ys,
+                                                   const int32_t* __restrict__ ids, const LaunchParams& P)
+{
+    rec.i[p1] = i;
+    const size_t cap = (size_t)rec.cap;
+    int idb[VRM_NSEG];
+#pragma unroll
+    for (int s = 0; s < VRM_NSEG; ++s) idb[s] = best[s] >= 0 ? ids[best[s]] : 0x7fffffff;
+    int packed = 0;
+#pragma unroll
+    for (int s = 0; s < VRM_NSEG; ++s) {
+        int rank = 0;
+#pragma unroll
+        for (int o = 0; o < VRM_NSEG; ++o) rank += idb[o] < idb[s] ? 1 : 0;
+        packed |= rank << (3 * s);
+        const int u = best[s];
+        df X{0.0f, 0.0f}, Y{0.0f, 0.0f};
+        int pj = -1;
+        if (u >= 0) {
+            exact_offset(xi, yi, xs[u], ys[u], P.scale2e, X, Y);
+            pj = perm[u];
+        }
+        rec.pj[s * cap + p1] = pj;
+        rec.off[(4 * s + 0) * cap + p1] = X.hi;
+        rec.off[(4 * s + 1) * cap + p1] = X.lo;
+        rec.off[(4 * s + 2) * cap + p1] = Y.hi;
+        rec.off[(4 * s + 3) * cap + p1] = Y.lo;
+    }
+    rec.rank[p1] = packed;
+}
+
 }  // namespace vrm
 
 // launcher (vrm_lp_group.hip): complete LPs with sixteen lanes each, as the last LP
@@ -150,5 +239,11 @@ int vrm_lp_group_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::Laun
 // fractions.  count_hits: the settled ones are warm-start hits.
 int vrm_verify_bases_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, bool keep_f,
                          bool count_hits);
+// the small neighbourhoods and five-row LPs of the diffused particles from the segment
+// masks of the stage before, or (from_prev) from the bases recorded by particle id in
+// prev; what they do not settle is queued as by the neighbourhood kernel.  prev: also
+// record the settled bases there, and count them as warm-start hits.
+int vrm_verify_small_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, int32_t* prev,
+                         bool from_prev);
 // the kept rows from the bases recorded by particle id (c->prev)
 int vrm_bases_from_prev_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n);

@@ -419,6 +419,194 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
+// Small neighbourhoods and their five-row LPs, the basis known by its segments: the
+// scan of k_small_nbhd, then the check on the eight columns it found (one per segment,
+// so another particle in a segment does not void the hint).  Nothing is written for an
+// LP that the check settles: no record, no queue entry.  Bound by VALU issue and the
+// scan's loads; four waves per SIMD (128 VGPRs) take 0.60 ms for 3.4M particles, three
+// 0.70 ms; the neighbourhoods and one-thread LPs they stand for 0.39 + 1.40 ms.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_verify_small(
+    int nb, const int32_t* __restrict__ n_dev, const int32_t* __restrict__ perm, const float* __restrict__ xs,
+    const float* __restrict__ ys, const int32_t* __restrict__ ids, const int32_t* __restrict__ cell_start,
+    const GridState* gs, const uint8_t* __restrict__ diffused, const float* __restrict__ gamma, float* acc,
+    LaunchParams P, uint8_t* seg_mask, int32_t* prev, int prev_cap, int from_prev, SmallRec rec,
+    int32_t* q_small, int32_t* q_full, Queues* qs, vrm_counters* cnt)
+{
+    constexpr int M = 5;
+    __shared__ float s_bd[VRM_NSEG * 256];
+    __shared__ int s_best[VRM_NSEG * 256];
+    __shared__ int s_app[17];
+    cnt = counter_stripe(cnt);
+    const int n = min(*n_dev, nb);
+    const int tid = threadIdx.x;
+    const int t = blockIdx.x * 256 + tid;
+    bool dif = t < n && !gs->bad;   // no cell list while a value is not finite
+    int i = 0;
+    if (dif) {
+        i = perm[t];
+        dif = diffused[i];
+    }
+#pragma unroll
+    for (int s = 0; s < VRM_NSEG; ++s) {
+        s_bd[s * 256 + tid] = INFINITY;
+        s_best[s * 256 + tid] = -1;
+    }
+    int best[VRM_NSEG];
+    int ksmall = 0;
+    bool ok = false;
+    if (dif) {
+        const float xi = xs[t], yi = ys[t];
+        int kfull = 0;
+        scan_segments(t, xi, yi, *gs, cell_start, xs, ys, ids, P, s_bd, s_best, tid, kfull);
+        int id[VRM_NSEG];
+        uint32_t present = 0;
+#pragma unroll
+        for (int s = 0; s < VRM_NSEG; ++s) {
+            best[s] = s_best[s * 256 + tid];
+            present |= best[s] >= 0 ? 1u << s : 0u;
+            id[s] = best[s] >= 0 ? ids[best[s]] : 0x7fffffff;
+            // the columns' positions by segment (an absent one: the particle's own)
+            s_bd[s * 256 + tid] = best[s] >= 0 ? xs[best[s]] : xi;
+            s_best[s * 256 + tid] = __float_as_int(best[s] >= 0 ? ys[best[s]] : yi);
+        }
+        ksmall = __popc(present);
+        const int own = prev ? ids[t] : 0;
+        uint32_t mask = 0;
+        if (from_prev) {
+            // segments whose member was in the particle's previous basis
+            int pv[M];
+#pragma unroll
+            for (int r = 0; r < M; ++r)
+                pv[r] = (unsigned)own < (unsigned)prev_cap ? prev[(size_t)own * kPrevIds + r] : -1;
+#pragma unroll
+            for (int s = 0; s < VRM_NSEG; ++s)
+#pragma unroll
+                for (int r = 0; r < M; ++r) mask |= pv[r] == id[s] ? 1u << s : 0u;
+            seg_mask[i] = (uint8_t)mask;   // for the next stage
+        } else {
+            mask = seg_mask[i];
+        }
+        ok = __popc(mask) == M && (mask & ~present) == 0;
+        if (ok) {
+            uint32_t ranks = 0;   // id rank of segment s's column at bit 3 s
+#pragma unroll
+            for (int s = 0; s < VRM_NSEG; ++s) {
+                uint32_t rank = 0;
+#pragma unroll
+                for (int o = 0; o < VRM_NSEG; ++o) rank += id[o] < id[s] ? 1u : 0u;
+                ranks |= (rank & 7u) << (3 * s);
+            }
+            // offset and FP32 cost of segment s's column, from LDS
+            auto column = [&](int s, float& X, float& Y) -> float {
+                X = (s_bd[s * 256 + tid] - xi) * P.scale2e;
+                Y = (__int_as_float(s_best[s * 256 + tid]) - yi) * P.scale2e;
+                const float d2 = X * X + Y * Y;
+                return __builtin_fmaf(d2 * __builtin_sqrtf(d2), P.cs_hi, tie_weight((ranks >> (3 * s)) & 7u, 2));
+            };
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // read them back: registers are short
+            float bpx[M], bpy[M], c[M], y[M], x[M];
+            uint32_t left = mask;
+            Qr<M> qr;
+#pragma unroll
+            for (int r = 0; r < M; ++r) {
+                const int s = __ffs((int)left) - 1;
+                left &= left - 1;
+                bpx[r] = s_bd[s * 256 + tid];
+                bpy[r] = __int_as_float(s_best[s * 256 + tid]);
+                float v[M], X, Y;
+                c[r] = column(s, X, Y);
+                y[r] = c[r];
+                mono<M>(X, Y, v);
+#pragma unroll
+                for (int a = 0; a < M; ++a) qr.a[a][r] = v[a];
+            }
+            qr.factor();
+            const float first = refined_solution<M>(qr, bpx, bpy, xi, yi, P, x);
+            qr.solve_t(y);
+            {
+                float w[M];
+#pragma unroll
+                for (int r = 0; r < M; ++r) {
+                    float v[M];
+                    mono<M>((bpx[r] - xi) * P.scale2e, (bpy[r] - yi) * P.scale2e, v);
+                    float s = c[r];
+#pragma unroll
+                    for (int a = 0; a < M; ++a) s = __builtin_fmaf(-y[a], v[a], s);
+                    w[r] = s;
+                }
+                qr.solve_t(w);
+#pragma unroll
+                for (int a = 0; a < M; ++a) y[a] += w[a];
+            }
+            // every column priced: the basic ones measure the error, the others must clear it
+            float eta = 0.0f, low = __builtin_inff();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int s = 0; s < VRM_NSEG; ++s) {
+                float v[M], X, Y;
+                const float cs = column(s, X, Y);
+                mono<M>(X, Y, v);
+                float d, sc;
+                reduced(v, cs, y, true, d, sc);
+                const float key = d * __builtin_amdgcn_rcpf(sc);
+                const bool basic = (mask >> s) & 1u, other = ((present & ~mask) >> s) & 1u;
+                eta = basic ? fmaxf(eta, fabsf(key)) : eta;
+                low = other ? fminf(low, key) : low;
+            }
+            const float margin = kFastMargin * (first + eta + 1.1920929e-07f);
+            ok = first <= 1e-5f && eta <= 1e-5f && low >= margin * 1.00000095367431640625f;
+#pragma unroll
+            for (int r = 0; r < M; ++r) ok = ok && x[r] >= -kCertX;
+            if (ok) {
+                // the stencil, as finish_lp forms it
+                float sum = 0.0f;
+#pragma unroll
+                for (int r = 0; r < M; ++r) {
+                    x[r] = x[r] > 0.0f ? x[r] : 0.0f;
+                    sum += x[r];
+                }
+                const float tiny = 9.313225746154785e-10f * sum;
+                sum = 0.0f;
+                const float g_i = gamma[i];
+                const double dsc = P.det ? det_scale(gs->gmax_bits) : 0.0;
+                left = mask;
+#pragma unroll
+                for (int r = 0; r < M; ++r) {
+                    const int s = __ffs((int)left) - 1;
+                    left &= left - 1;
+                    x[r] = x[r] < tiny ? 0.0f : x[r];
+                    sum += x[r];
+                    int u = 0;
+#pragma unroll
+                    for (int q = 0; q < VRM_NSEG; ++q) u = q == s ? best[q] : u;
+                    if (x[r] != 0.0f) acc_add(acc, perm[u], x[r], g_i, dsc);
+                    if (prev && (unsigned)own < (unsigned)prev_cap) prev[(size_t)own * kPrevIds + r] = ids[u];
+                }
+                acc_add(acc, i, -sum, g_i, dsc);
+                if (prev && (unsigned)own < (unsigned)prev_cap)
+#pragma unroll
+                    for (int r = M; r < kPrevIds; ++r) prev[(size_t)own * kPrevIds + r] = -1;
+            }
+        }
+    }
+    const bool small_ok = dif && !ok && ksmall >= M;
+    const int p1 = block_append_n(&qs->n_small, small_ok ? 1 : 0, s_app);
+    if (small_ok) {
+        q_small[p1] = t;
+        write_small_record(rec, p1, i, xs[t], ys[t], best, perm, xs, ys, ids, P);
+    }
+    const bool full = dif && !ok && !small_ok;
+    const int p2 = block_append_n(&qs->n_full, full ? 1 : 0, s_app);
+    if (full) q_full[p2] = t;
+    const uint64_t hits = __ballot(ok);
+    if (lane_id() == 0 && hits) {
+        const unsigned long long h = (unsigned long long)__popcll(hits);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&cnt->n_small), h);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&cnt->redistributions), h);
+        if (prev) atomicAdd(reinterpret_cast<unsigned long long*>(&cnt->warm_hit), h);
+    }
+}
+
 // The previous-basis warm start keeps bases by id (they outlive the reordering of the
 // cloud); rows of column indices for k_verify from them.  inv[id]: the particle of an
 // id; an id that left the cloud may find any particle, whose own id then differs.
@@ -466,6 +654,16 @@ int vrm_bases_from_prev_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n)
     hipLaunchKernelGGL(k_index_of_id, dim3(grid), dim3(256), 0, c->stream, n, cl->n_dev, cl->id_dev, c->capacity, inv);
     hipLaunchKernelGGL(k_bases_from_prev, dim3(grid), dim3(256), 0, c->stream, n, cl->n_dev, cl->id_dev, c->capacity,
                        inv, c->prev, sten_rows(c, 9).idx);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
+}
+
+int vrm_verify_small_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, int32_t* prev,
+                         bool from_prev)
+{
+    hipLaunchKernelGGL(k_verify_small, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->perm, c->xs,
+                       c->ys, c->ids, c->cell_start, c->grid, c->diffused, cl->gamma_dev, c->acc, lp, c->tmp_u8, prev,
+                       c->capacity, from_prev ? 1 : 0, c->srec, c->q_small, c->q_full, c->queues, c->counters);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
