@@ -407,7 +407,7 @@ int vrm_read_timing(vrm_ctx* ctx, double* ms_host, int64_t* launches_host);
  * infinite, else 0.  h, q (2 or 3), c_diff as in vrm_params.  Runs on the current
  * device, enqueued on `stream` (a hipStream_t of that device; NULL = the null
  * stream), without synchronising.  Its working state (histogram bins, threshold,
- * flag: about 3 KB) lives in one fixed device array per GPU, kept until the
+ * flag: about 2 KB) lives in one fixed device array per GPU, kept until the
  * process ends; the call allocates nothing and clears that state itself.  Every
  * call on a GPU shares its array: calls that overlap on one GPU (other streams,
  * other threads) race and must be ordered by the caller.  n up to 2^26;

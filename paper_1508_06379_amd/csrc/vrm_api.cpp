@@ -76,12 +76,9 @@ int check_cloud(vrm_ctx* c, const vrm_cloud* cl)
     return VRM_OK;
 }
 
-// Read N from the device (synchronises) and remember it.
-int read_n(vrm_ctx* c, const vrm_cloud* cl)
+// Check the count read from the device and remember it.
+int remember_n(vrm_ctx* c, const vrm_cloud* cl, int32_t n)
 {
-    int32_t n = 0;
-    VRM_HIP(hipMemcpyAsync(&n, cl->n_dev, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-    VRM_HIP(hipStreamSynchronize(c->stream));
     if (n < 0 || n > cl->capacity) return vrm_fail(VRM_E_ARG, "particle count %d outside [0, %d]", n, cl->capacity);
     if (c->n_ptr != cl->n_dev || c->cloud_x != cl->x_dev || c->n != n) {
         // another cloud, or the count changed behind the context: cached cells are stale
@@ -92,6 +89,24 @@ int read_n(vrm_ctx* c, const vrm_cloud* cl)
     c->n_ptr = cl->n_dev;
     c->cloud_x = cl->x_dev;
     return VRM_OK;
+}
+
+// Read N from the device (waits for the stream's work) and remember it.
+int read_n(vrm_ctx* c, const vrm_cloud* cl)
+{
+    vrm::Queues q;
+    if (int r = vrm_read_queues(c, q, cl->n_dev)) return r;
+    return remember_n(c, cl, q.n_now);
+}
+
+// The selection of the cloud's current particles, whose count is read and remembered.
+int select_particles(vrm_ctx* c, const vrm_cloud* cl, const vrm_params* p)
+{
+    const double factor = p->c_diff * std::pow(p->h, p->q + 1);
+    const int32_t guess = c->n_ptr == cl->n_dev ? c->n : cl->capacity;
+    int32_t n = 0;
+    if (int r = vrm_select_run(c, cl, guess, factor, n)) return r;
+    return remember_n(c, cl, n);
 }
 
 int cached_n(vrm_ctx* c, const vrm_cloud* cl)
@@ -188,6 +203,7 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(grid, 1);
     A(queues, 1);
     A(sel, 1);
+    A(sel_bins, vrm::kSelBins);
     A(counters, (vrm::kCounterStripes * vrm::kCounterStride + sizeof(vrm_counters) - 1) / sizeof(vrm_counters));
     A(cell_of, cap);
     A(rank, cap);
@@ -252,6 +268,7 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
         if (e == hipSuccess) e = hipMemsetAsync(c->counters, 0, vrm::kCounterStripes * vrm::kCounterStride, c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->queues, 0, sizeof(vrm::Queues), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->sel, 0, sizeof(vrm::SelectState), c->stream);
+        if (e == hipSuccess) r = vrm_select_init(c);
         if (e == hipSuccess) e = hipMemsetAsync(c->grid, 0, sizeof(vrm::GridState), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->khist, 0, 2 * (VRM_KMAX + 1) * sizeof(int32_t), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->pivhist, 0xff, cap, c->stream);
@@ -273,7 +290,7 @@ int vrm_destroy(vrm_ctx* c)
     if (!c) return VRM_OK;
     (void)hipSetDevice(c->device);
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    void* ptrs[] = {c->grid, c->queues, c->sel, c->counters, c->cell_of, c->rank, c->cell_start, c->scan_part,
+    void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_of, c->rank, c->cell_start, c->scan_part,
                     c->perm, c->xs, c->ys, c->ids, c->diffused, c->acc, c->x0, c->y0, c->g0, c->q_small, c->q_full, c->q_retry,
                     c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->ccell, c->crank, c->cstart, c->cperm,
                     c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->verify_buf, c->sort_tmp, c->full_cols,
@@ -307,18 +324,13 @@ int vrm_select_diffused(vrm_ctx* c, const vrm_cloud* cl, const vrm_params* p, ui
 {
     int r = check_cloud(c, cl);
     if (!r) r = check_params(p);
-    if (!r) r = read_n(c, cl);
     if (r) return r;
-    double factor = p->c_diff * std::pow(p->h, p->q + 1);
     {
         vrm::ScopedTimer tm(c, VRM_T_SELECT);
-        r = vrm_select_run(c, cl->gamma_dev, cl->id_dev, c->n, factor);
+        r = select_particles(c, cl, p);
+        if (!r) r = vrm_select_mask_run(c, cl->gamma_dev, c->n, mask_dev);
     }
     if (r) return r;
-    if (mask_dev && c->n > 0) {
-        hipLaunchKernelGGL(k_copy_mask, dim3((c->n + 255) / 256), dim3(256), 0, c->stream, c->n, c->diffused, mask_dev);
-        VRM_HIP(hipGetLastError());
-    }
     c->n_diffused_valid = 1;
     return VRM_OK;
 }
@@ -356,13 +368,11 @@ int vrm_insert_particles(vrm_ctx* c, vrm_cloud* cl, const vrm_params* p)
 {
     int r = check_cloud(c, cl);
     if (!r) r = check_params(p);
-    if (!r) r = read_n(c, cl);
     if (r) return r;
     vrm::LaunchParams L = launch_params(c, p);
-    double factor = p->c_diff * std::pow(p->h, p->q + 1);
     {
         vrm::ScopedTimer tm(c, VRM_T_SELECT);
-        r = vrm_select_run(c, cl->gamma_dev, cl->id_dev, c->n, factor);
+        r = select_particles(c, cl, p);
     }
     if (r) return r;
     // the cell list of the last reorder is still valid if nothing moved since

@@ -8,6 +8,7 @@
 // the greedy result in (id, segment) order by rounds of the lexicographically
 // first independent set.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -260,124 +261,212 @@ int scan_cells(vrm_ctx* c, int32_t* start)
 // together.  Four 8-bit radix passes resolve the whole key.
 __device__ __forceinline__ uint32_t selection_key(float a) { return __float_as_uint(a); }
 
-// also zeroes the diffused count of every counter copy (k_sel_mask adds to it)
-__global__ void k_sel_init(SelectState* s, vrm_counters* cnt, GridState* gs)
+// The state before a selection: nothing picked, every bin zero.  The last pass leaves
+// it so (the context's selections need no launch for it); a fresh state, and one that
+// overlapping calls may have spoiled, is set by this kernel.
+__global__ __launch_bounds__(256) void k_sel_init(SelectState* s, double* bins, int nbins, GridState* gs)
 {
-    int t = threadIdx.x;
-    if (cnt && t < kCounterStripes)
-        reinterpret_cast<vrm_counters*>(reinterpret_cast<char*>(cnt) + t * kCounterStride)->n_diffused = 0;
+    const int t = threadIdx.x;
+    for (int b = t; b < nbins; b += blockDim.x) bins[b] = 0.0;
+    if (t < 17) s->done_blocks[t] = 0;
     if (t == 0) {
-        s->norm1 = 0.0;
-        s->bound = 0.0;
-        s->prefix = 0.0;
-        s->key_prefix = 0u;
-        s->done = 0u;
-        s->threshold = 0u;
+        s->max_seen = 0u;
+        s->bad_seen = 0;
         s->max_id = -1;
-        gs->bad &= ~kBadGamma;
-    }
-    s->bin_sum[t] = 0.0;
-    s->bin_cnt[t] = 0u;
-}
-
-// One radix pass.  A bin holds FP32 values that share at least the top seven
-// bits of their exponent, i.e. values in [2^E, 2^(E+2)) that are multiples of
-// 2^(E-23); up to 2^26 of them sum to below 2^(E+28), a multiple of 2^(E-23)
-// with at most 51 significant bits, so every FP64 bin sum is exact and does
-// not depend on the order of the atomics.  The first pass also finds non-finite
-// circulations (kBadGamma) and the largest id.
-__global__ __launch_bounds__(256) void k_sel_hist(const float* __restrict__ g, const int32_t* __restrict__ ids, int n,
-                                                  SelectState* s, int shift, GridState* gs)
-{
-    __shared__ double h_sum[256];
-    __shared__ uint32_t h_cnt[256];
-    h_sum[threadIdx.x] = 0.0;
-    h_cnt[threadIdx.x] = 0u;
-    __syncthreads();
-    bool bad = false;
-    int mid = -1;
-    if (!s->done) {
-        uint32_t pre = s->key_prefix;
-        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-            float a = fabsf(g[i]);
-            uint32_t key = selection_key(a);
-            if (shift == 24) {
-                bad = bad || key >= 0x7f800000u;
-                if (ids) mid = max(mid, ids[i]);
-            }
-            if (shift < 24 && (key >> (shift + 8)) != (pre >> (shift + 8))) continue;
-            int b = (key >> shift) & 255u;
-            atomicAdd(&h_sum[b], (double)a);
-            atomicAdd(&h_cnt[b], 1u);
-        }
-    }
-    if (shift == 24) {
-        for (int o = 32; o > 0; o >>= 1) mid = max(mid, __shfl_xor(mid, o, VRM_WAVE));
-        if (lane_id() == 0 && mid >= 0) atomicMax(&s->max_id, mid);
-        if (__any(bad) && lane_id() == 0) atomicOr(&gs->bad, kBadGamma);
-    }
-    __syncthreads();
-    if (h_cnt[threadIdx.x]) {
-        atomicAdd(&s->bin_sum[threadIdx.x], h_sum[threadIdx.x]);
-        atomicAdd(&s->bin_cnt[threadIdx.x], h_cnt[threadIdx.x]);
+        s->done = 2u;   // of no particle at all: none is diffused
+        s->threshold = 0u;
+        if (gs) gs->bad &= ~kBadGamma;
     }
 }
 
-// Pick the bin where the cumulative sum first exceeds the bound (256 threads,
-// one bin each; an FP64 block scan in bin order).
-__global__ __launch_bounds__(256) void k_sel_pick(SelectState* s, int shift, double factor)
+// One thread copies the queue record (and the cloud's count) to the host copy, then
+// writes the sequence number with a system-scope release (after a system fence).
+__device__ __forceinline__ void publish(const Queues* q, const GridState* g, int n_now, HostQueues* h, int32_t seq)
 {
-    __shared__ double wtot[4];
-    __shared__ int first;
-    const int t = threadIdx.x, lane = lane_id(), w = t >> 6;
-    double v = s->bin_sum[t];
-    // inclusive scan of the bin sums (the same association in every run)
+    if (q) {
+        h->q = *q;
+        h->q.nonfinite = g->bad;
+    }
+    h->q.n_now = n_now;
+    __threadfence_system();
+    __hip_atomic_store(&h->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ void k_publish_queues(const Queues* q, const GridState* g, const int32_t* n_dev, HostQueues* h, int32_t seq)
+{
+    if (threadIdx.x == 0 && blockIdx.x == 0) publish(q, g, n_dev ? *n_dev : 0, h, seq);
+}
+
+constexpr int kSelBlock = 1024;
+constexpr int kSelLds = 8192;   // FP64 bins in LDS, all copies
+
+// inclusive FP64 scan over the workgroup in thread order (the same association in every run)
+__device__ __forceinline__ double block_scan_f64(double v, double* wtot)
+{
+    const int lane = lane_id(), w = threadIdx.x >> 6;
     double incl = v;
     for (int o = 1; o < 64; o <<= 1) {
-        double u = __shfl_up(incl, o, VRM_WAVE);
+        const double u = __shfl_up(incl, o, VRM_WAVE);
         if (lane >= o) incl += u;
     }
     if (lane == 63) wtot[w] = incl;
-    if (t == 0) first = 256;
     __syncthreads();
-    double off = 0.0, total = 0.0;
-    for (int k = 0; k < 4; ++k) {
-        if (k < w) off += wtot[k];
-        total += wtot[k];
+    double off = 0.0;
+    for (int k = 0; k < w; ++k) off += wtot[k];
+    return off + incl;
+}
+
+// One radix pass over BITS bits of the key from `shift` up, and the choice of the bin
+// where the cumulative sum first exceeds the bound by the last workgroup to finish.
+// A bin holds FP32 values that share at least the top seven bits of their exponent,
+// i.e. values in [2^E, 2^(E+2)) that are multiples of 2^(E-23); up to 2^26 of them sum
+// to below 2^(E+28), a multiple of 2^(E-23) with at most 51 significant bits, so every
+// FP64 bin sum is exact and does not depend on the order of the atomics.  The first
+// pass also finds non-finite circulations (kBadGamma) and the largest id.
+// Neighbouring particles have circulations of one magnitude, so a wave's first-pass
+// atomics fall on one or two bins: the bins have copies for the lanes (32 of 256 bins,
+// 8 of 1024), next to each other.  With one copy the pass took 99 us for 1.4M particles
+// (10 us for 40k).  The workgroups' sums meet by atomics whose results are waited for,
+// so the last workgroup reads complete bins without a fence (which would write back the
+// caches of every XCD once per workgroup).
+// With n_dev the count is the device's (nothing is done with one outside 0..n), and the
+// first pass hands it to the host: while the passes run, the host reads it and enqueues
+// the launches that need it.
+template <int BITS, bool FIRST>
+__global__ __launch_bounds__(kSelBlock) void k_sel_pass(const float* __restrict__ g, const int32_t* __restrict__ ids,
+                                                        int n, const int32_t* __restrict__ n_dev, SelectState* s,
+                                                        double* bins, int shift, double factor, GridState* gs,
+                                                        vrm_counters* cnt, Queues* qs, HostQueues* host, int32_t seq)
+{
+    if (n_dev) {
+        const int n_now = *n_dev;
+        if (FIRST && blockIdx.x == 0 && threadIdx.x == 0) publish(nullptr, nullptr, n_now, host, seq);
+        if (n_now < 0 || n_now > n) return;
+        n = n_now;
     }
-    incl += off;
-    if (shift == 24) {
-        if (t == 0) {
-            s->norm1 = total;
-            s->bound = factor * total;
-            s->prefix = 0.0;
+    constexpr int NB = 1 << BITS;
+    constexpr int USED = FIRST ? NB / 2 : NB;   // the sign bit is zero
+    constexpr int COPIES = kSelLds / USED < 32 ? kSelLds / USED : 32;
+    __shared__ double h[USED * COPIES];
+    __shared__ double wtot[kSelBlock / 64];
+    __shared__ int s_first, s_last;
+    const int t = threadIdx.x;
+    const bool done = !FIRST && s->done != 0u;
+    const uint32_t pre = FIRST ? 0u : s->key_prefix;
+    if (!done) {
+        for (int b = t; b < USED * COPIES; b += kSelBlock) h[b] = 0.0;
+        __syncthreads();
+        const int copy = lane_id() & (COPIES - 1);
+        bool bad = false;
+        uint32_t mid = 0u;
+        for (int i = blockIdx.x * kSelBlock + t; i < n; i += gridDim.x * kSelBlock) {
+            const float a = fabsf(g[i]);
+            const uint32_t key = selection_key(a);
+            if (FIRST) {
+                bad = bad || key >= 0x7f800000u;
+                if (ids) mid = max(mid, ids[i] >= 0 ? (uint32_t)ids[i] + 1u : 0u);
+            } else if ((key ^ pre) >> (shift + BITS)) {
+                continue;
+            }
+            atomicAdd(&h[((key >> shift) & (NB - 1)) * COPIES + copy], (double)a);
         }
-    }
-    __syncthreads();
-    const bool done = s->done != 0u;
-    const double bound = s->bound, prefix = s->prefix;
-    if (!done && prefix + incl > bound) atomicMin(&first, t);
-    __syncthreads();
-    if (t == 0 && !done) {
-        int b = first;
-        if (b == 256) {
-            // every particle in the current key range is left out
-            uint64_t top = (uint64_t)s->key_prefix + ((uint64_t)256 << shift);
-            s->threshold = top > 0xffffffffull ? 0xffffffffu : (uint32_t)top;
-            s->done = top > 0xffffffffull ? 2u : 1u;
-        } else {
-            s->key_prefix |= (uint32_t)b << shift;
-            if (shift == 0) {
-                s->threshold = s->key_prefix;
-                s->done = 1u;
+        if (FIRST) {
+            for (int o = 32; o > 0; o >>= 1) mid = max(mid, (uint32_t)__shfl_xor((int)mid, o, VRM_WAVE));
+            const bool any = __any(bad);
+            uint32_t old = 0u;
+            if (lane_id() == 0 && mid) old |= atomicMax(&s->max_seen, mid);
+            if (lane_id() == 0 && any) old |= (uint32_t)atomicOr(&s->bad_seen, 1);
+            asm volatile("" ::"v"(old));   // waits for the atomics' results
+        }
+        __syncthreads();
+        for (int b = t; b < USED; b += kSelBlock) {
+            double v = 0.0;
+            for (int c = 0; c < COPIES; ++c) v += h[b * COPIES + c];   // exact: any order
+            if (v != 0.0) {
+                const double old = atomicAdd(&bins[b], v);
+                asm volatile("" ::"v"(old));
             }
         }
     }
-    // cumulative sum below the chosen bin (from its own scan) for the next pass
-    if (!done && t == first && first < 256) s->prefix = prefix + incl - v;
     __syncthreads();
-    s->bin_sum[t] = 0.0;
-    s->bin_cnt[t] = 0u;
+    if (t == 0) {
+        // two levels, so that the workgroups do not queue on one address
+        const int part = blockIdx.x & 15, in_part = ((int)gridDim.x - part + 15) / 16;
+        bool last = atomicAdd(&s->done_blocks[part], 1) == in_part - 1;
+        if (last) last = atomicAdd(&s->done_blocks[16], 1) == min((int)gridDim.x, 16) - 1;
+        s_last = last;
+        s_first = NB;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (t < 17) s->done_blocks[t] = 0;
+    if (FIRST) {
+        // what the step's later kernels start from
+        if (cnt && t < kCounterStripes)
+            reinterpret_cast<vrm_counters*>(reinterpret_cast<char*>(cnt) + t * kCounterStride)->n_diffused = 0;
+        if (t == 0) {
+            const uint32_t m = __hip_atomic_load(&s->max_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int32_t bad = __hip_atomic_load(&s->bad_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s->max_id = (int32_t)m - 1;
+            s->max_seen = 0u;
+            s->bad_seen = 0;
+            gs->bad = (gs->bad & ~kBadGamma) | (bad ? kBadGamma : 0);
+            if (qs) {
+                qs->n_cand = 0;
+                qs->n_undecided = 0;
+                qs->n_accepted = 0;
+                qs->small_state = 0;
+            }
+        }
+    }
+    if (done) return;
+    // PB consecutive bins per thread
+    constexpr int PB = NB > kSelBlock ? NB / kSelBlock : 1;
+    double v[PB], sum = 0.0;
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+        const int b = PB * t + p;
+        v[p] = b < USED ? __hip_atomic_load(&bins[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        if (b < USED) bins[b] = 0.0;
+        sum += v[p];
+    }
+    const double incl = block_scan_f64(sum, wtot);
+    double total = 0.0;
+    for (int k = 0; k < kSelBlock / 64; ++k) total += wtot[k];
+    const double bound = FIRST ? factor * total : s->bound, prefix = FIRST ? 0.0 : s->prefix;
+    double before[PB], at = incl - sum;
+    int mine = NB;
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+        before[p] = at;
+        at = p == PB - 1 ? incl : at + v[p];
+        if (mine == NB && prefix + at > bound) mine = PB * t + p;
+    }
+    if (mine < NB && mine < USED) atomicMin(&s_first, mine);
+    __syncthreads();
+    const int first = s_first;
+    if (t == 0) {
+        if (FIRST) {
+            s->norm1 = total;
+            s->bound = bound;
+        }
+        if (first == NB) {
+            // every particle in the current key range is left out
+            const uint64_t top = (uint64_t)pre + ((uint64_t)NB << shift);
+            s->threshold = top > 0xffffffffull ? 0xffffffffu : (uint32_t)top;
+            s->done = top > 0xffffffffull ? 2u : 1u;
+        } else {
+            const uint32_t p = pre | ((uint32_t)first << shift);
+            s->key_prefix = p;
+            s->threshold = p;
+            s->done = shift == 0 ? 1u : 0u;
+        }
+        if (first == NB) s->prefix = 0.0;
+    }
+    // cumulative sum below the chosen bin, for the next pass
+#pragma unroll
+    for (int p = 0; p < PB; ++p)
+        if (PB * t + p == first) s->prefix = prefix + before[p];
 }
 
 // Diffused: |Gamma| >= fl32(T (1 - 2^-16)), T the first key that does not fit:
@@ -387,15 +476,19 @@ __global__ __launch_bounds__(256) void k_sel_pick(SelectState* s, int shift, dou
 // random-walk round-off of FP32 circulations over 10^2 SSP-RK3 steps).
 constexpr float kTieBand = 0.9999847412109375f;   // 1 - 2^-16
 
+__device__ __forceinline__ bool is_diffused(const SelectState* s, float g)
+{
+    return s->done != 2u && fabsf(g) >= __uint_as_float(s->threshold) * kTieBand;
+}
+
 __global__ __launch_bounds__(256) void k_sel_mask(const float* __restrict__ g, int n, const SelectState* s,
                                                   uint8_t* diffused, uint8_t* mask_out, vrm_counters* cnt)
 {
     if (cnt) cnt = counter_stripe(cnt);
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     bool d = false;
-    const float band = __uint_as_float(s->threshold) * kTieBand;
     if (i < n) {
-        d = s->done == 2u ? false : fabsf(g[i]) >= band;
+        d = is_diffused(s, g[i]);
         diffused[i] = d ? 1 : 0;
         if (mask_out) mask_out[i] = d ? 1 : 0;
     }
@@ -403,9 +496,9 @@ __global__ __launch_bounds__(256) void k_sel_mask(const float* __restrict__ g, i
     if (cnt && lane_id() == 0 && m) atomicAdd(&cnt->n_diffused, __popcll(m));
 }
 
-// one thread per counter copy
 // ------------------------------------------------------------ insertion
-// Candidates: every empty segment of a diffused particle (slot order).
+// Candidates: every empty segment of a diffused particle (slot order); the kernel also
+// writes the diffused set that the selection's threshold defines.
 // L lanes per particle (aligned groups; L = 4 for clouds up to kCandCoopMaxN
 // particles, where one lane per particle leaves the chip mostly idle and the
 // chain of loads of one scan sets the time): the lanes scan interleaved
@@ -417,7 +510,8 @@ __global__ __launch_bounds__(256) void k_candidates(int n, const int32_t* __rest
                                                     const float* __restrict__ xs, const float* __restrict__ ys,
                                                     const int32_t* __restrict__ ids,
                                                     const int32_t* __restrict__ cell_start,
-                                                    const uint8_t* __restrict__ diffused, const GridState* gs,
+                                                    const float* __restrict__ gamma, const SelectState* sel,
+                                                    uint8_t* diffused, vrm_counters* cnt, const GridState* gs,
                                                     LaunchParams P, Queues* qs, int cand_cap, float* cx, float* cy,
                                                     uint64_t* ckey, uint8_t* cstate)
 {
@@ -425,7 +519,15 @@ __global__ __launch_bounds__(256) void k_candidates(int n, const int32_t* __rest
     const int t = blockIdx.x * (256 / L) + threadIdx.x / L;
     int occupied = 0xff;
     float xi = 0.0f, yi = 0.0f;
-    if (t < n && !gs->bad && diffused[perm[t]]) {
+    bool dif = false;
+    if (t < n && !gs->bad) {
+        const int i = perm[t];
+        dif = is_diffused(sel, gamma[i]);
+        if (sub == 0) diffused[i] = dif ? 1 : 0;
+    }
+    const uint64_t members = __ballot(dif && sub == 0);
+    if (lane_id() == 0 && members) atomicAdd(&counter_stripe(cnt)->n_diffused, __popcll(members));
+    if (dif) {
         occupied = 0;
         GridState g = *gs;
         xi = xs[t];
@@ -575,11 +677,11 @@ __global__ __launch_bounds__(256) void k_append(int n0, int na, const int32_t* _
 // accepted ones are appended in key order as after the radix sort.
 constexpr int kInsSmallMax = 1024;
 
-__global__ __launch_bounds__(1024) void k_insert_small(int n0, int capacity, int cand_cap,
-                                                       const float* __restrict__ cx, const float* __restrict__ cy,
-                                                       const uint64_t* __restrict__ ckey, float ex2, float* x, float* y,
-                                                       float* gamma, int32_t* id, uint8_t* diffused, int32_t* n_dev,
-                                                       Queues* qs, vrm_counters* cnt, const SelectState* sel)
+__device__ __forceinline__ void insert_small(int n0, int capacity, int cand_cap,
+                                             const float* __restrict__ cx, const float* __restrict__ cy,
+                                             const uint64_t* __restrict__ ckey, float ex2, float* x, float* y,
+                                             float* gamma, int32_t* id, uint8_t* diffused, int32_t* n_dev, Queues* qs,
+                                             vrm_counters* cnt, const SelectState* sel)
 {
     __shared__ uint64_t key[kInsSmallMax];
     __shared__ int32_t src[kInsSmallMax];
@@ -677,6 +779,19 @@ __global__ __launch_bounds__(1024) void k_insert_small(int n0, int capacity, int
     }
 }
 
+// ... and the record for the host, whatever came out.
+__global__ __launch_bounds__(1024) void k_insert_small(int n0, int capacity, int cand_cap,
+                                                       const float* __restrict__ cx, const float* __restrict__ cy,
+                                                       const uint64_t* __restrict__ ckey, float ex2, float* x, float* y,
+                                                       float* gamma, int32_t* id, uint8_t* diffused, int32_t* n_dev,
+                                                       Queues* qs, vrm_counters* cnt, const SelectState* sel,
+                                                       const GridState* gs, HostQueues* h, int32_t seq)
+{
+    if (n0 > 0)
+        insert_small(n0, capacity, cand_cap, cx, cy, ckey, ex2, x, y, gamma, id, diffused, n_dev, qs, cnt, sel);
+    if (threadIdx.x == 0) publish(qs, gs, 0, h, seq);
+}
+
 // ------------------------------------------------------------- reorder
 __global__ __launch_bounds__(256) void k_gather_cloud(int n, const int32_t* __restrict__ perm,
                                                       const float* __restrict__ g, const uint8_t* __restrict__ dif,
@@ -705,13 +820,6 @@ __global__ __launch_bounds__(256) void k_copy_back(int n, const float* __restric
     perm[t] = t;
 }
 
-__global__ void k_reset_insert(Queues* q)
-{
-    q->n_cand = 0;
-    q->n_undecided = 0;
-    q->n_accepted = 0;
-    q->small_state = 0;
-}
 __global__ void k_reset_undecided(Queues* q) { q->n_undecided = 0; }
 
 __global__ void k_insert_counters(const Queues* q, vrm_counters* cnt, int rounds, int n_after)
@@ -724,28 +832,13 @@ __global__ void k_insert_counters(const Queues* q, vrm_counters* cnt, int rounds
 
 int blocks_for(int n) { return n > 0 ? (n + 255) / 256 : 1; }
 
-// One thread copies the queue record to the host copy, then writes the
-// sequence number with a system-scope release (after a system fence).
-__global__ void k_publish_queues(const Queues* q, const GridState* g, HostQueues* h, int32_t seq)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        h->q = *q;
-        h->q.nonfinite = g->bad;
-        __threadfence_system();
-        __hip_atomic_store(&h->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-}
-
 }  // namespace
 
 // The host spins on the sequence number; every 256 polls it asks the stream:
 // an error ends the wait with that error, and a finished stream without the
 // record is a state error (so a wait cannot outlast the stream's work).
-int vrm_read_queues(vrm_ctx* c, Queues& q)
+static int wait_queues(vrm_ctx* c, int32_t seq, Queues& q)
 {
-    const int32_t seq = ++c->q_seq;
-    hipLaunchKernelGGL(k_publish_queues, dim3(1), dim3(64), 0, c->stream, c->queues, c->grid, c->q_host, seq);
-    VRM_HIP(hipGetLastError());
     for (uint64_t k = 1;; ++k) {
         if (__atomic_load_n(&c->q_host->seq, __ATOMIC_ACQUIRE) == seq) break;
         if ((k & 255) == 0) {
@@ -758,6 +851,14 @@ int vrm_read_queues(vrm_ctx* c, Queues& q)
     }
     std::memcpy(&q, const_cast<const Queues*>(&c->q_host->q), sizeof(Queues));
     return VRM_OK;
+}
+
+int vrm_read_queues(vrm_ctx* c, Queues& q, const int32_t* n_dev)
+{
+    const int32_t seq = ++c->q_seq;
+    hipLaunchKernelGGL(k_publish_queues, dim3(1), dim3(64), 0, c->stream, c->queues, c->grid, n_dev, c->q_host, seq);
+    VRM_HIP(hipGetLastError());
+    return wait_queues(c, seq, q);
 }
 
 // Cell list of (x, y) into ctx->cell_start / perm / xs, ys, ids (slot order).
@@ -788,19 +889,45 @@ int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* i
     return VRM_OK;
 }
 
-int vrm_select_run(vrm_ctx* c, const float* gamma, const int32_t* ids, int32_t n, double factor)
+// The selection's threshold of the cloud's n_dev particles (and, with it, cleared
+// insertion queues and diffused counts).  Returns that count once the first pass has
+// read it; it is out of range (and nothing else done) if below 0 or above the capacity.
+// `guess` only sizes the launches.
+int vrm_select_run(vrm_ctx* c, const vrm_cloud* cl, int32_t guess, double factor, int32_t& n)
 {
     hipStream_t s = c->stream;
-    static_assert(kCounterStripes <= 256, "k_sel_init zeroes one counter copy per thread");
-    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, s, c->sel, c->counters, c->grid);
-    int nb = min(2048, blocks_for(n));
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (n > 0) hipLaunchKernelGGL(k_sel_hist, dim3(nb), dim3(256), 0, s, gamma, ids, n, c->sel, shift, c->grid);
-        hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, s, c->sel, shift, factor);
-    }
+    static_assert(kCounterStripes <= kSelBlock, "the first pass zeroes one counter copy per thread");
+    const int32_t seq = ++c->q_seq;
+    const int nb = std::max(1, min(256, (guess + kSelBlock - 1) / kSelBlock));
+    hipLaunchKernelGGL((k_sel_pass<11, true>), dim3(nb), dim3(kSelBlock), 0, s, cl->gamma_dev, cl->id_dev,
+                       cl->capacity, cl->n_dev, c->sel, c->sel_bins, 21, factor, c->grid, c->counters, c->queues,
+                       c->q_host, seq);
+    hipLaunchKernelGGL((k_sel_pass<11, false>), dim3(nb), dim3(kSelBlock), 0, s, cl->gamma_dev, cl->id_dev,
+                       cl->capacity, cl->n_dev, c->sel, c->sel_bins, 10, factor, c->grid, c->counters, c->queues,
+                       c->q_host, seq);
+    hipLaunchKernelGGL((k_sel_pass<10, false>), dim3(nb), dim3(kSelBlock), 0, s, cl->gamma_dev, cl->id_dev,
+                       cl->capacity, cl->n_dev, c->sel, c->sel_bins, 0, factor, c->grid, c->counters, c->queues,
+                       c->q_host, seq);
+    VRM_HIP(hipGetLastError());
+    Queues q;
+    if (int r = wait_queues(c, seq, q)) return r;
+    n = q.n_now;
+    return VRM_OK;
+}
+
+// The diffused set of the threshold, also to mask_out unless that is NULL.
+int vrm_select_mask_run(vrm_ctx* c, const float* gamma, int32_t n, uint8_t* mask_out)
+{
     if (n > 0)
-        hipLaunchKernelGGL(k_sel_mask, dim3(blocks_for(n)), dim3(256), 0, s, gamma, n, c->sel, c->diffused,
-                           (uint8_t*)nullptr, c->counters);
+        hipLaunchKernelGGL(k_sel_mask, dim3(blocks_for(n)), dim3(256), 0, c->stream, gamma, n, c->sel, c->diffused,
+                           mask_out, c->counters);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
+}
+
+int vrm_select_init(vrm_ctx* c)
+{
+    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, c->stream, c->sel, c->sel_bins, kSelBins, (GridState*)nullptr);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
@@ -811,20 +938,18 @@ int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp)
 {
     hipStream_t s = c->stream;
     const int cand_cap = 2 * c->capacity;
-    hipLaunchKernelGGL(k_reset_insert, dim3(1), dim3(1), 0, s, c->queues);
+    const int32_t seq = ++c->q_seq;
     if (n > 0)
         hipLaunchKernelGGL(n <= kCandCoopMaxN ? k_candidates<4> : k_candidates<1>,
                            dim3(n <= kCandCoopMaxN ? (n + 63) / 64 : blocks_for(n)), dim3(256), 0, s, n, c->perm,
-                           c->xs, c->ys, c->ids,
-                           c->cell_start, c->diffused, c->grid, lp, c->queues, cand_cap, c->cx, c->cy, c->ckey,
-                           c->cstate);
-    if (n > 0)
-        hipLaunchKernelGGL(k_insert_small, dim3(1), dim3(1024), 0, s, n, cl->capacity, cand_cap, c->cx, c->cy, c->ckey,
-                           lp.ex2, cl->x_dev, cl->y_dev, cl->gamma_dev, cl->id_dev, c->diffused, cl->n_dev, c->queues,
-                           c->counters, c->sel);
+                           c->xs, c->ys, c->ids, c->cell_start, cl->gamma_dev, c->sel, c->diffused, c->counters,
+                           c->grid, lp, c->queues, cand_cap, c->cx, c->cy, c->ckey, c->cstate);
+    hipLaunchKernelGGL(k_insert_small, dim3(1), dim3(1024), 0, s, n, cl->capacity, cand_cap, c->cx, c->cy, c->ckey,
+                       lp.ex2, cl->x_dev, cl->y_dev, cl->gamma_dev, cl->id_dev, c->diffused, cl->n_dev, c->queues,
+                       c->counters, c->sel, c->grid, c->q_host, seq);
     VRM_HIP(hipGetLastError());
     Queues q;
-    if (int r = vrm_read_queues(c, q)) return r;
+    if (int r = wait_queues(c, seq, q)) return r;
     if (q.nonfinite) return vrm_nonfinite(c, q.nonfinite);
     if (q.small_state == 2)
         return vrm_fail(VRM_E_CAPACITY, "insertion needs %d particles, capacity is %d", n + q.n_accepted,
@@ -920,10 +1045,11 @@ namespace {
 struct StaticSelect {
     SelectState sel;
     GridState grid;
+    double bins[256];
 };
 constexpr size_t kStaticScratchBytes = 4096;
 static_assert(sizeof(StaticSelect) <= kStaticScratchBytes, "static selection state exceeds its array");
-constexpr int32_t kStaticMaxN = 1 << 26;   // exact FP64 bin sums (k_sel_hist)
+constexpr int32_t kStaticMaxN = 1 << 26;   // exact FP64 bin sums (k_sel_pass)
 constexpr int kStaticMaxDevices = 64;
 
 __global__ void k_static_reset(GridState* g) { g->bad = 0; }
@@ -971,14 +1097,12 @@ extern "C" int vrm_select_diffused_static(const float* gamma_dev, int32_t n, dou
     hipStream_t s = static_cast<hipStream_t>(stream);
     const double factor = c_diff * std::pow(h, q + 1);
     hipLaunchKernelGGL(k_static_reset, dim3(1), dim3(1), 0, s, &st->grid);
-    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, s, &st->sel, (vrm_counters*)nullptr, &st->grid);
-    const int nb = min(2048, blocks_for(n));
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (n > 0)
-            hipLaunchKernelGGL(k_sel_hist, dim3(nb), dim3(256), 0, s, gamma_dev, (const int32_t*)nullptr, n, &st->sel,
-                               shift, &st->grid);
-        hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, s, &st->sel, shift, factor);
-    }
+    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, s, &st->sel, st->bins, 256, &st->grid);
+    const int nb = std::max(1, min(256, (n + kSelBlock - 1) / kSelBlock));
+    for (int shift = 24; shift >= 0; shift -= 8)
+        hipLaunchKernelGGL((shift == 24 ? k_sel_pass<8, true> : k_sel_pass<8, false>), dim3(nb), dim3(kSelBlock), 0, s,
+                           gamma_dev, (const int32_t*)nullptr, n, (const int32_t*)nullptr, &st->sel, st->bins, shift,
+                           factor, &st->grid, (vrm_counters*)nullptr, (Queues*)nullptr, (HostQueues*)nullptr, 0);
     if (n > 0)
         hipLaunchKernelGGL(k_sel_mask, dim3(blocks_for(n)), dim3(256), 0, s, gamma_dev, n, &st->sel, mask_dev,
                            (uint8_t*)nullptr, (vrm_counters*)nullptr);

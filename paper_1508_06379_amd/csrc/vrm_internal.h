@@ -82,6 +82,7 @@ struct Queues {
     int32_t n_rm_uncertified;   // ... of which optimality was not certified
     int32_t nonfinite;     // copy of GridState::bad taken when the record is published
     int32_t n_defer;       // complete LPs whose certification was deferred to a second launch
+    int32_t n_now;         // the cloud's count when the record was published
     int32_t done_part[16]; // blocks_done of every sixteenth block (last_block)
 };
 
@@ -136,9 +137,11 @@ struct SelectState {
     uint32_t done;         // 1 once the threshold is known
     uint32_t threshold;    // particles with key < threshold are left out
     int32_t max_id;        // largest id of the cloud (new particles get max_id + 1, ...)
-    double bin_sum[256];
-    uint32_t bin_cnt[256];
+    uint32_t max_seen;     // of the first pass, zero between selections: largest id + 1,
+    int32_t bad_seen;      // a non-finite circulation,
+    int32_t done_blocks[17];   // finished workgroups of a pass
 };
+constexpr int kSelBins = 2048;   // bins of a context's radix passes (11, 11 and 10 bits)
 
 struct LaunchParams {
     float h, lo2, hi2, lo2f, hi2f;      // annulus bounds (FP32, squared, unnormalised)
@@ -215,6 +218,7 @@ struct vrm_ctx {
     vrm::HostQueues* q_host;    // pinned, coherent host copy of *queues (vrm_read_queues)
     int32_t q_seq;              // last sequence number asked of it
     vrm::SelectState* sel;
+    double* sel_bins;     // [kSelBins] sums of a radix pass, zero between selections
     vrm_counters* counters;
     int32_t* cell_of;     // [cap] cell of particle
     int32_t* rank;        // [cap] rank within its cell
@@ -333,11 +337,13 @@ struct ScopedTimer {
 // launchers (vrm_cells.hip)
 int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* id, int32_t n,
                     const vrm::LaunchParams& lp, const int32_t* n_dev = nullptr);
-int vrm_select_run(vrm_ctx* c, const float* gamma, const int32_t* ids, int32_t n, double bound_factor);
+int vrm_select_run(vrm_ctx* c, const vrm_cloud* cl, int32_t guess, double bound_factor, int32_t& n);
+int vrm_select_mask_run(vrm_ctx* c, const float* gamma, int32_t n, uint8_t* mask_out);
+int vrm_select_init(vrm_ctx* c);
 int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp);
 // the queue record after the work enqueued so far on the context's stream,
-// read from the pinned host copy (no stream synchronisation)
-int vrm_read_queues(vrm_ctx* c, vrm::Queues& q);
+// read from the pinned host copy (no stream synchronisation); n_now of n_dev unless NULL
+int vrm_read_queues(vrm_ctx* c, vrm::Queues& q, const int32_t* n_dev = nullptr);
 int vrm_reorder_cloud(vrm_ctx* c, vrm_cloud* cl, int32_t n);
 int vrm_remove_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, int32_t* n_candidates);
 size_t vrm_remove_tmp_bytes(int32_t cap);
