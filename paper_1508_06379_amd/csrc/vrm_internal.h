@@ -371,7 +371,6 @@ int vrm_velocity_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const float* vo
 int vrm_mlp_alloc(vrm_ctx* c, int max_rows);
 void vrm_mlp_free(vrm_ctx* c);
 int vrm_mlp_set_weights(vrm_ctx* c, const float* w_dev);
-int vrm_mlp_forward(vrm_ctx* c, const uint16_t* X, int rows, float* Y, const int* rows_dev);
 int vrm_mlp_read_weights(vrm_ctx* c, float* w_dev);
 int vrm_mlp_infer_run(vrm_ctx* c, const uint16_t* X, int rows, float* Y, const int* rows_dev);
 // warm-start logits (8 per queued small LP) with the network input built from the positions

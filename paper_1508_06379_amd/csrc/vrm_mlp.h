@@ -20,29 +20,24 @@ constexpr int kOffW3 = kOffB2 + kMlpHid;
 constexpr int kOffB3 = kOffW3 + kMlpHid * kMlpOut;
 constexpr int kMlpParams = kOffB3 + kMlpOut;
 
-constexpr int kEpiAcc = 0, kEpiBias = 1, kEpiBiasGelu = 2, kEpiGeluBwd = 3;
-
 struct MlpState {
     int max_rows;
     int loaded;
     int step;
     float* w;        // FP32 master parameters
-    float* g;        // gradients
     float* am;       // AdamW moments
     float* av;
     uint16_t* wbf;   // BF16 copy of w
     uint16_t* wt;    // BF16 weights transposed to [n][k] (inference)
-    float* z1;       // pre-activations (rows x hid)
-    float* z2;
-    uint16_t* h1;    // activations, BF16
-    uint16_t* h2;
-    float* y;        // outputs (rows x out)
-    uint16_t* dy;
-    float* dyf;
-    float* dz;
-    uint16_t* dzb;
-    uint16_t* dzb2;
-    double* loss;
+    // training: transposed BF16 operands of the weight gradients, [rows / 32][feature][32]
+    uint16_t* xt;    // inputs
+    uint16_t* h1t;   // activations
+    uint16_t* h2t;
+    uint16_t* dyt;   // d loss / d outputs
+    uint16_t* dz2t;  // d loss / d pre-activations
+    uint16_t* dz1t;
+    float* bias_part;    // per workgroup: column sums of the last three in FP32,
+    double* loss_part;   // the loss
 };
 
 }  // namespace vrm

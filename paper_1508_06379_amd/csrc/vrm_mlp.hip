@@ -5,10 +5,10 @@
 //     -> 128 (GELU) -> 128 (GELU) -> 64 (32 basis logits, 32 fractions)
 //
 // Every matrix product runs on the BF16 matrix cores (v_mfma_f32_16x16x32_bf16,
-// FP32 accumulation) in one generic tiled kernel with fused epilogues; the
-// backward pass uses the same kernel with transposed operand strides and
-// split-K atomics for the weight gradients.  Master weights and AdamW state
-// are FP32; the products read BF16 copies.
+// FP32 accumulation).  Inference is one fused kernel; a training step is two: the
+// rows' (forward, loss, backward to the pre-activations) and the parameters' (weight
+// gradients over all rows, AdamW).  Master weights and AdamW state are FP32; the
+// products read BF16 copies.
 #include <hip/hip_runtime.h>
 
 #include "vrm_device.h"
@@ -102,17 +102,13 @@ __device__ __forceinline__ void stage_tile(uint16_t (*T)[TK + KPAD], const uint1
     }
 }
 
-// C(m, n) = epi(sum_k A(m, k) B(k, n));  A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn].
+// C(m, n) = sum_k A(m, k) B(k, n);  A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn].
 // Tile 64 x 64 per block of 4 waves (each 32 x 32 = 2 x 2 MFMA blocks); K in steps of 32.
-// gridDim.z > 1 splits K; the partial sums are added atomically (EPI_ACC only).
-template <int EPI>
+// gridDim.z > 1 splits K; the partial sums are added atomically.
 __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const uint16_t* __restrict__ A, long sam, long sak,
                                               const uint16_t* __restrict__ B, long sbk, long sbn, float* C, long ldc,
-                                              const float* __restrict__ bias, uint16_t* Cbf, const float* Zaux,
-                                              int kchunk, const int* Mdev)
+                                              int kchunk)
 {
-    if (Mdev) M = *Mdev;
-    if ((int)blockIdx.y * TM >= M) return;
     __shared__ __attribute__((aligned(16))) uint16_t As[TM][TK + KPAD];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[TN][TK + KPAD];   // stored [n][k]
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -153,92 +149,17 @@ __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const uint16_
                 if (m >= M || n >= N) continue;
                 float s = acc[i][j][v];
                 long o = (long)m * ldc + n;
-                if constexpr (EPI == kEpiAcc) {
-                    if (gridDim.z > 1)
-                        atomicAdd(&C[o], s);
-                    else
-                        C[o] = s;
-                } else if constexpr (EPI == kEpiBias) {
-                    C[o] = s + bias[n];
-                } else if constexpr (EPI == kEpiBiasGelu) {
-                    float z = s + bias[n];
-                    C[o] = z;                  // pre-activation, kept for the backward pass
-                    Cbf[o] = to_bf16(gelu(z));
-                } else if constexpr (EPI == kEpiGeluBwd) {
-                    float d = s * gelu_grad(Zaux[o]);
-                    C[o] = d;
-                    Cbf[o] = to_bf16(d);
-                }
+                if (gridDim.z > 1)
+                    atomicAdd(&C[o], s);
+                else
+                    C[o] = s;
             }
-}
-
-// Masked loss: BCE-with-logits on the basis indicators and squared error on the
-// fractions, averaged over rows.  dY (BF16) = d loss / d Y.
-__global__ __launch_bounds__(256) void k_loss(int rows, const float* __restrict__ Y, const float* __restrict__ T,
-                                              const uint16_t* __restrict__ X, float wf, uint16_t* dY, float* dYf,
-                                              double* loss)
-{
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    double l = 0.0;
-    if (idx < rows * kMlpSlots) {
-        int r = idx / kMlpSlots, s = idx % kMlpSlots;
-        float mask = from_bf16(X[(long)r * kMlpIn + 2 * kMlpSlots + s]);
-        float z = Y[(long)r * kMlpOut + s], y = T[(long)r * kMlpOut + s];
-        float p = Y[(long)r * kMlpOut + kMlpSlots + s], f = T[(long)r * kMlpOut + kMlpSlots + s];
-        float inv = 1.0f / (float)rows;
-        float sp = fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z)));   // softplus
-        float sig = 1.0f / (1.0f + __expf(-z));
-        l = mask * ((sp - y * z) + wf * (p - f) * (p - f)) * inv;
-        float gz = mask * (sig - y) * inv;
-        float gp = mask * wf * 2.0f * (p - f) * inv;
-        dY[(long)r * kMlpOut + s] = to_bf16(gz);
-        dY[(long)r * kMlpOut + kMlpSlots + s] = to_bf16(gp);
-        if (dYf) {
-            dYf[(long)r * kMlpOut + s] = gz;
-            dYf[(long)r * kMlpOut + kMlpSlots + s] = gp;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, VRM_WAVE);
-    if (lane_id() == 0 && l != 0.0) atomicAdd(loss, l);
-}
-
-// column sums of G[rows][n] (bias gradients), accumulated atomically
-__global__ __launch_bounds__(256) void k_colsum(int rows, int n, const float* __restrict__ G, float* out)
-{
-    int c = threadIdx.x % n;
-    int lanes_per_col = blockDim.x / n;
-    int part = threadIdx.x / n;
-    float s = 0.0f;
-    for (int r = blockIdx.x * lanes_per_col + part; r < rows; r += gridDim.x * lanes_per_col) s += G[(long)r * n + c];
-    atomicAdd(&out[c], s);
-}
-
-__global__ __launch_bounds__(256) void k_adamw(int n, float* w, const float* g, float* m, float* v, float lr, float b1,
-                                               float b2, float eps, float wd, float c1, float c2, uint16_t* wbf)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float gi = g[i];
-    float mi = b1 * m[i] + (1.0f - b1) * gi;
-    float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    float mh = mi / c1, vh = vi / c2;
-    float wi = w[i] - lr * (mh / (sqrtf(vh) + eps) + wd * w[i]);
-    w[i] = wi;
-    wbf[i] = to_bf16(wi);
 }
 
 __global__ __launch_bounds__(256) void k_to_bf16(int n, const float* __restrict__ in, uint16_t* out)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] = to_bf16(in[i]);
-}
-
-__global__ void k_zero_f(int n, float* p)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
 }
 
 int nblk(long n) { return (int)((n + 255) / 256); }
@@ -499,20 +420,318 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
 }
 
-template <int EPI>
-int gemm(hipStream_t s, int M, int N, int K, const uint16_t* A, long sam, long sak, const uint16_t* B, long sbk,
-         long sbn, float* C, long ldc, const float* bias, uint16_t* Cbf, const float* Zaux, int splitk,
-         const int* Mdev = nullptr)
+// ---------------------------------------------------------------- training
+// Transposed BF16 operands of the weight gradients, [rows / 32][feature][32 rows]: a
+// fragment of 16 features is 1 KB in one piece, its 8 rows per lane one 16-byte load.
+constexpr int kRowBlk = 32;
+__device__ __forceinline__ size_t t_index(int features, int f, long row)
 {
-    if (M <= 0) return VRM_OK;
-    int kchunk = K;
-    if (splitk > 1) kchunk = ((K + splitk - 1) / splitk + TK - 1) / TK * TK;
-    int gz = (K + kchunk - 1) / kchunk;
-    dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM, gz);
-    hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(256), 0, s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, Cbf, Zaux,
-                       kchunk, Mdev);
-    VRM_HIP(hipGetLastError());
-    return VRM_OK;
+    return ((size_t)(row / kRowBlk) * features + f) * kRowBlk + (size_t)(row % kRowBlk);
+}
+
+__device__ __forceinline__ bf16x8 frag(const uint16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
+
+// Rows kernel: forward pass, loss and the backward pass to the pre-activations for
+// tiles of 16 rows.  Wave wv holds columns [32 wv, 32 wv + 32) of the hidden layers and
+// [16 wv, 16 wv + 16) of the output.  Masked loss, averaged over rows: BCE-with-logits on
+// the basis indicators (output columns below 32) and squared error on the fractions.
+// At the trainer's 4096 rows this is bound by latency, one tile per CU: five dependent
+// layers.  So a wave keeps its columns of every weight matrix in registers, fetched at
+// once at the start (L2; 128 VGPRs), and the tile's activations go from layer to layer
+// through LDS; pre-activations stay in registers until the backward pass needs them.
+// Before (17 launches: a tiled product per layer and direction, the loss, column sums,
+// clears and copies) a step of 4096 rows took 149 us, of 64 rows 85, of 65536 rows 1263;
+// now 22.7, 12.5 and 130 us (this kernel 16, 10 and 75 us of them).  Two workgroups per CU
+// (256 VGPRs, 19 of them spilled) measured 23.1 us, 13.5 us and 119 us.
+constexpr int kTrainTile = 16;
+constexpr int kTrainBlocks = 256;              // one per CU; more rows: loop
+constexpr int kBiasCols = 2 * kMlpHid + kMlpOut;
+constexpr int DYP = kMlpOut + 8;
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void k_train_rows(
+    int rows, int tiles, const uint16_t* __restrict__ X, const float* __restrict__ T, const uint16_t* __restrict__ wt,
+    const uint16_t* __restrict__ wbf, const float* __restrict__ w, float wf, uint16_t* __restrict__ xt,
+    uint16_t* __restrict__ h1t, uint16_t* __restrict__ h2t, uint16_t* __restrict__ dyt, uint16_t* __restrict__ dz2t,
+    uint16_t* __restrict__ dz1t, float* __restrict__ bias_part, double* __restrict__ loss_part)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t Ta[kTrainTile * FKP];   // x, h2, dz2
+    __shared__ __attribute__((aligned(16))) uint16_t Tb[kTrainTile * FKP];   // h1
+    __shared__ __attribute__((aligned(16))) uint16_t Ty[kTrainTile * DYP];   // dy
+    __shared__ double s_loss[4];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int row = lane & 15, quad = lane >> 4, kq = quad * 8;
+    const bool x_aligned = (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    const float inv = 1.0f / (float)rows;
+    bf16x8 w1[4][2], w2[4][2], w3[4], v3[2][2], v2[4][2];
+    float b1[2], b2[2], b3;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = wv * 32 + j * 16 + row;
+            w1[k][j] = frag(&wt[kOffT1 + n * kMlpIn + 32 * k + kq]);
+            w2[k][j] = frag(&wt[kOffT2 + n * kMlpHid + 32 * k + kq]);
+            v2[k][j] = frag(&wbf[kOffW2 + n * kMlpHid + 32 * k + kq]);
+            if (k < 2) v3[k][j] = frag(&wbf[kOffW3 + n * kMlpOut + 32 * k + kq]);
+            if (k == 0) {
+                b1[j] = w[kOffB1 + n];
+                b2[j] = w[kOffB2 + n];
+            }
+        }
+        w3[k] = frag(&wt[kOffT3 + (wv * 16 + row) * kMlpHid + 32 * k + kq]);
+    }
+    b3 = w[kOffB3 + wv * 16 + row];
+    float s1[2] = {0.0f, 0.0f}, s2[2] = {0.0f, 0.0f}, s3 = 0.0f;   // column sums
+    double loss = 0.0;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const long r0 = (long)tile * kTrainTile;
+        // the targets of this lane's outputs: rows 4 quad + v, column 16 wv + row
+        float y[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const long r = r0 + 4 * quad + v;
+            y[v] = r < rows ? T[r * kMlpOut + wv * 16 + row] : 0.0f;
+        }
+        {
+            const int r = tid >> 4, c8 = (tid & 15) * 8;
+            uint4 v = {0u, 0u, 0u, 0u};
+            if (r0 + r < rows) {
+                const uint16_t* src = &X[(r0 + r) * kMlpIn + c8];
+                if (x_aligned) {
+                    v = *reinterpret_cast<const uint4*>(src);
+                } else {
+                    uint32_t e[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) e[k] = (uint32_t)src[2 * k] | ((uint32_t)src[2 * k + 1] << 16);
+                    v = uint4{e[0], e[1], e[2], e[3]};
+                }
+            }
+            *reinterpret_cast<uint4*>(&Ta[r * FKP + c8]) = v;
+        }
+        __syncthreads();
+        float mask[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            mask[v] = from_bf16(Ta[(4 * quad + v) * FKP + 2 * kMlpSlots + (wv & 1) * 16 + row]);
+        {
+            // the tile transposed: eight rows of one input per thread
+            const int c = tid & (kMlpIn - 1), o = (tid >> 7) * 8;
+            uint32_t e[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                e[k] = (uint32_t)Ta[(o + 2 * k) * FKP + c] | ((uint32_t)Ta[(o + 2 * k + 1) * FKP + c] << 16);
+            *reinterpret_cast<uint4*>(&xt[t_index(kMlpIn, c, r0 + o)]) = uint4{e[0], e[1], e[2], e[3]};
+        }
+        f32x4 z1[2], z2[2];
+        // one hidden layer: A -> z (kept), GELU -> O and the transposed copy
+        auto hidden = [&](const uint16_t* A, const bf16x8 (&wk)[4][2], const float (&b)[2], f32x4 (&z)[2], uint16_t* O,
+                          uint16_t* ot) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) z[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bf16x8 a = frag(&A[row * FKP + 32 * k + kq]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) z[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wk[k][j], z[j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int n = wv * 32 + j * 16 + row;
+                uint16_t e[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    z[j][v] += b[j];
+                    e[v] = to_bf16(gelu(z[j][v]));
+                    O[(4 * quad + v) * FKP + n] = e[v];
+                    if (r0 + 4 * quad + v >= rows) e[v] = 0;
+                }
+                *reinterpret_cast<uint2*>(&ot[t_index(kMlpHid, n, r0 + 4 * quad)]) =
+                    uint2{(uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16)};
+            }
+            __syncthreads();
+        };
+        hidden(Ta, w1, b1, z1, Tb, h1t);
+        hidden(Tb, w2, b2, z2, Ta, h2t);
+        {
+            f32x4 p = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(&Ta[row * FKP + 32 * k + kq]), w3[k], p, 0, 0, 0);
+            uint16_t e[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float z = p[v] + b3;
+                float g;
+                if (wv < 2) {
+                    const float sp = fmaxf(z, 0.0f) + log1pf(__expf(-fabsf(z)));   // softplus
+                    const float sig = 1.0f / (1.0f + __expf(-z));
+                    loss += (double)(mask[v] * (sp - y[v] * z) * inv);
+                    g = mask[v] * (sig - y[v]) * inv;
+                } else {
+                    loss += (double)(mask[v] * (wf * (z - y[v]) * (z - y[v])) * inv);
+                    g = mask[v] * wf * 2.0f * (z - y[v]) * inv;
+                }
+                // (no loss from rows past the last: their mask is zero, but the outputs may not be finite)
+                if (r0 + 4 * quad + v >= rows) g = 0.0f;
+                s3 += g;
+                e[v] = to_bf16(g);
+                Ty[(4 * quad + v) * DYP + wv * 16 + row] = e[v];
+            }
+            *reinterpret_cast<uint2*>(&dyt[t_index(kMlpOut, wv * 16 + row, r0 + 4 * quad)]) =
+                uint2{(uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16)};
+        }
+        __syncthreads();
+        // d loss / d pre-activation of a hidden layer: (A W^T) gelu'(z)
+        auto backward = [&](f32x4 (&d)[2], const f32x4 (&z)[2], float (&sum)[2], uint16_t* O, uint16_t* ot) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int n = wv * 32 + j * 16 + row;
+                uint16_t e[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float g = d[j][v] * gelu_grad(z[j][v]);
+                    if (r0 + 4 * quad + v >= rows) g = 0.0f;
+                    sum[j] += g;
+                    e[v] = to_bf16(g);
+                    if (O) O[(4 * quad + v) * FKP + n] = e[v];
+                }
+                *reinterpret_cast<uint2*>(&ot[t_index(kMlpHid, n, r0 + 4 * quad)]) =
+                    uint2{(uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16)};
+            }
+        };
+        f32x4 d[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const bf16x8 a = frag(&Ty[row * DYP + 32 * k + kq]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) d[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, v3[k][j], d[j], 0, 0, 0);
+        }
+        backward(d, z2, s2, Ta, dz2t);
+        __syncthreads();
+        d[0] = d[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bf16x8 a = frag(&Ta[row * FKP + 32 * k + kq]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) d[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, v2[k][j], d[j], 0, 0, 0);
+        }
+        backward(d, z1, s1, nullptr, dz1t);
+        __syncthreads();   // the next tile overwrites Ta
+    }
+    // column sums of this workgroup's rows: the four lanes of a column
+    auto column = [&](float s) {
+        s += __shfl_xor(s, 16, VRM_WAVE);
+        return s + __shfl_xor(s, 32, VRM_WAVE);
+    };
+    float* part = bias_part + (size_t)blockIdx.x * kBiasCols;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float a = column(s1[j]), b = column(s2[j]);
+        if (quad == 0) {
+            part[wv * 32 + j * 16 + row] = a;
+            part[kMlpHid + wv * 32 + j * 16 + row] = b;
+        }
+    }
+    const float b = column(s3);
+    if (quad == 0) part[2 * kMlpHid + wv * 16 + row] = b;
+    for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, VRM_WAVE);
+    if (lane == 0) s_loss[wv] = loss;
+    __syncthreads();
+    if (tid == 0) loss_part[blockIdx.x] = s_loss[0] + s_loss[1] + s_loss[2] + s_loss[3];
+}
+
+struct AdamW {
+    float lr, wd, c1, c2;   // lr 0: no step
+    float *w, *m, *v, *grad;
+    uint16_t *wbf, *wt;
+};
+
+// the gradient of parameter i out, and its step; returns the BF16 weight
+__device__ __forceinline__ uint16_t adamw(const AdamW& a, int i, float g)
+{
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    if (a.grad) a.grad[i] = g;
+    if (!(a.lr > 0.0f)) return 0;
+    const float mi = b1 * a.m[i] + (1.0f - b1) * g;
+    const float vi = b2 * a.v[i] + (1.0f - b2) * g * g;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    const float mh = mi / a.c1, vh = vi / a.c2;
+    const float wi = a.w[i] - a.lr * (mh / (sqrtf(vh) + eps) + a.wd * a.w[i]);
+    a.w[i] = wi;
+    const uint16_t h = to_bf16(wi);
+    a.wbf[i] = h;
+    return h;
+}
+
+// Parameters kernel.  A workgroup of 16 waves owns a 16 x 16 block of one weight
+// matrix: the waves take the row blocks in turn, their sums meet in LDS, and the same
+// workgroup makes the parameters' AdamW step: no atomics, no cleared sums, one order of
+// additions in every run.  160 workgroups read 32 features each (42 MB of L2 reads at
+// 4096 rows, in 6 to 8 us; 61 us at 65536 rows); larger blocks read less but leave more of
+// the chip idle.  Five more workgroups sum the bias gradients, the last of them the loss.
+constexpr int kTilesW = (kMlpHid / 16) * (kMlpHid / 16), kTilesW3 = (kMlpHid / 16) * (kMlpOut / 16);
+__global__ __launch_bounds__(1024) void k_train_params(int nblk32, int parts, const uint16_t* __restrict__ xt,
+                                                       const uint16_t* __restrict__ h1t,
+                                                       const uint16_t* __restrict__ h2t,
+                                                       const uint16_t* __restrict__ dyt,
+                                                       const uint16_t* __restrict__ dz2t,
+                                                       const uint16_t* __restrict__ dz1t,
+                                                       const float* __restrict__ bias_part,
+                                                       const double* __restrict__ loss_part, double* loss_out, AdamW a)
+{
+    static_assert(kMlpIn == kMlpHid, "one tile count for the first two layers");
+    __shared__ float red[16][256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int b = blockIdx.x;
+    if (b < 2 * kTilesW + kTilesW3) {
+        const int layer = b / kTilesW;   // the third holds fewer tiles
+        b -= layer * kTilesW;
+        const int nout = layer == 2 ? kMlpOut : kMlpHid;
+        const int m0 = b / (nout / 16) * 16, n0 = b % (nout / 16) * 16;
+        const uint16_t* A = layer == 0 ? xt : layer == 1 ? h1t : h2t;
+        const uint16_t* B = layer == 0 ? dz1t : layer == 1 ? dz2t : dyt;
+        const int row = lane & 15, quad = lane >> 4;
+        const uint16_t* pa = A + (size_t)(m0 + row) * kRowBlk + quad * 8;
+        const uint16_t* pb = B + (size_t)(n0 + row) * kRowBlk + quad * 8;
+        const size_t sa = (size_t)kMlpHid * kRowBlk, sb = (size_t)nout * kRowBlk;
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 8
+        for (int k = wv; k < nblk32; k += 16)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(pa + k * sa), frag(pb + k * sb), acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wv][(4 * quad + v) * 16 + row] = acc[v];
+        __syncthreads();
+        if (tid < 256) {
+            float g = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) g += red[k][tid];
+            const int m = m0 + tid / 16, n = n0 + tid % 16;
+            const int off = layer == 0 ? kOffW1 : layer == 1 ? kOffW2 : kOffW3;
+            const int toff = layer == 0 ? kOffT1 : layer == 1 ? kOffT2 : kOffT3;
+            const uint16_t h = adamw(a, off + m * nout + n, g);
+            if (a.lr > 0.0f) a.wt[toff + n * kMlpHid + m] = h;
+        }
+        return;
+    }
+    b -= 2 * kTilesW + kTilesW3;   // bias columns [64 b, 64 b + 64)
+    const int col = 64 * b + lane;
+    float s = 0.0f;
+#pragma unroll 8
+    for (int p = wv; p < parts; p += 16) s += bias_part[(size_t)p * kBiasCols + col];
+    red[wv][lane] = s;
+    __syncthreads();
+    if (tid < 64) {
+        float g = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) g += red[k][lane];
+        (void)adamw(a, col < kMlpHid ? kOffB1 + col : col < 2 * kMlpHid ? kOffB2 + col - kMlpHid : kOffB3 + col - 2 * kMlpHid, g);
+    } else if (tid < 128 && b == kBiasCols / 64 - 1 && loss_out) {
+        double l = 0.0;
+        for (int p = lane; p < parts; p += 64) l += loss_part[p];
+        for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, VRM_WAVE);
+        if (lane == 0) *loss_out = l;
+    }
 }
 
 }  // namespace
@@ -536,12 +755,12 @@ int vrm_mlp_alloc(vrm_ctx* c, int max_rows)
         m = new MlpState();
         std::memset(m, 0, sizeof(*m));
         AL(w, sizeof(float) * kMlpParams);
-        AL(g, sizeof(float) * kMlpParams);
         AL(am, sizeof(float) * kMlpParams);
         AL(av, sizeof(float) * kMlpParams);
         AL(wbf, sizeof(uint16_t) * kMlpParams);
         AL(wt, sizeof(uint16_t) * kWtSize);
-        AL(loss, sizeof(double) * 2);
+        AL(loss_part, sizeof(double) * kTrainBlocks);
+        AL(bias_part, sizeof(float) * kTrainBlocks * kBiasCols);
         VRM_HIP(hipMemsetAsync(m->w, 0, sizeof(float) * kMlpParams, c->stream));
         VRM_HIP(hipMemsetAsync(m->wbf, 0, sizeof(uint16_t) * kMlpParams, c->stream));
         VRM_HIP(hipMemsetAsync(m->am, 0, sizeof(float) * kMlpParams, c->stream));
@@ -549,21 +768,21 @@ int vrm_mlp_alloc(vrm_ctx* c, int max_rows)
         c->mlp = m;
     }
     if (max_rows > m->max_rows) {
-        void* old[] = {m->z1, m->z2, m->h1, m->h2, m->y, m->dy, m->dyf, m->dz, m->dzb, m->dzb2};
+        uint16_t** bufs[] = {&m->xt, &m->h1t, &m->h2t, &m->dyt, &m->dz2t, &m->dz1t};
         VRM_HIP(hipStreamSynchronize(c->stream));
-        for (void* q : old)
-            if (q) (void)hipFree(q);
-        size_t R = (size_t)max_rows;
-        AL(z1, sizeof(float) * R * kMlpHid);
-        AL(z2, sizeof(float) * R * kMlpHid);
-        AL(h1, sizeof(uint16_t) * R * kMlpHid);
-        AL(h2, sizeof(uint16_t) * R * kMlpHid);
-        AL(y, sizeof(float) * R * kMlpOut);
-        AL(dy, sizeof(uint16_t) * R * kMlpOut);
-        AL(dyf, sizeof(float) * R * kMlpOut);
-        AL(dz, sizeof(float) * R * kMlpHid);
-        AL(dzb, sizeof(uint16_t) * R * kMlpHid);
-        AL(dzb2, sizeof(uint16_t) * R * kMlpHid);
+        m->max_rows = 0;
+        for (uint16_t** q : bufs) {
+            if (*q) (void)hipFree(*q);
+            *q = nullptr;
+        }
+        // whole blocks of 32 rows
+        const size_t R = ((size_t)max_rows + kRowBlk - 1) / kRowBlk * kRowBlk;
+        AL(xt, sizeof(uint16_t) * R * kMlpIn);
+        AL(h1t, sizeof(uint16_t) * R * kMlpHid);
+        AL(h2t, sizeof(uint16_t) * R * kMlpHid);
+        AL(dyt, sizeof(uint16_t) * R * kMlpOut);
+        AL(dz2t, sizeof(uint16_t) * R * kMlpHid);
+        AL(dz1t, sizeof(uint16_t) * R * kMlpHid);
         m->max_rows = max_rows;
     }
 #undef AL
@@ -574,8 +793,8 @@ void vrm_mlp_free(vrm_ctx* c)
 {
     if (!c->mlp) return;
     MlpState* m = c->mlp;
-    void* ptrs[] = {m->w, m->g, m->am, m->av, m->wbf, m->wt, m->z1, m->z2, m->h1, m->h2, m->y, m->dy, m->dyf, m->dz, m->dzb,
-                    m->dzb2, m->loss};
+    void* ptrs[] = {m->w, m->am, m->av, m->wbf, m->wt, m->xt, m->h1t, m->h2t, m->dyt, m->dz2t, m->dz1t,
+                    m->bias_part, m->loss_part};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     delete m;
@@ -594,26 +813,6 @@ int vrm_mlp_set_weights(vrm_ctx* c, const float* w_dev)
     m->step = 0;
     m->loaded = 1;
     return VRM_OK;
-}
-
-// forward pass over `rows` feature rows X (BF16); Y (FP32, rows x 64).  With
-// rows_dev the row count is read on the device (rows is then an upper bound).
-int vrm_mlp_forward(vrm_ctx* c, const uint16_t* X, int rows, float* Y, const int* rows_dev)
-{
-    MlpState* m = c->mlp;
-    hipStream_t s = c->stream;
-    const uint16_t* W1 = m->wbf + kOffW1;
-    const uint16_t* W2 = m->wbf + kOffW2;
-    const uint16_t* W3 = m->wbf + kOffW3;
-    int r = gemm<kEpiBiasGelu>(s, rows, kMlpHid, kMlpIn, X, kMlpIn, 1, W1, kMlpHid, 1, m->z1, kMlpHid, m->w + kOffB1,
-                               m->h1, nullptr, 1, rows_dev);
-    if (!r)
-        r = gemm<kEpiBiasGelu>(s, rows, kMlpHid, kMlpHid, m->h1, kMlpHid, 1, W2, kMlpHid, 1, m->z2, kMlpHid,
-                               m->w + kOffB2, m->h2, nullptr, 1, rows_dev);
-    if (!r)
-        r = gemm<kEpiBias>(s, rows, kMlpOut, kMlpHid, m->h2, kMlpHid, 1, W3, kMlpOut, 1, Y, kMlpOut, m->w + kOffB3,
-                           nullptr, nullptr, 1, rows_dev);
-    return r;
 }
 
 // fused forward for inference (no intermediate buffers); rows may be an upper bound with rows_dev
@@ -656,49 +855,21 @@ int vrm_mlp_train(vrm_ctx* c, const uint16_t* X, const float* T, int rows, float
 {
     MlpState* m = c->mlp;
     hipStream_t s = c->stream;
-    int r = vrm_mlp_forward(c, X, rows, m->y, nullptr);
-    if (r) return r;
-    VRM_HIP(hipMemsetAsync(m->loss, 0, sizeof(double), s));
-    VRM_HIP(hipMemsetAsync(m->g, 0, sizeof(float) * kMlpParams, s));
-    hipLaunchKernelGGL(k_loss, dim3(nblk((long)rows * kMlpSlots)), dim3(256), 0, s, rows, m->y, T, X, wf, m->dy, m->dyf,
-                       m->loss);
-    VRM_HIP(hipGetLastError());
-    const uint16_t* W2 = m->wbf + kOffW2;
-    const uint16_t* W3 = m->wbf + kOffW3;
-    int split = rows >= 4096 ? 16 : 1;
-    // layer 3: dW3 = H2^T dY, db3 = colsum dY, dZ2 = (dY W3^T) * gelu'(Z2)
-    r = gemm<kEpiAcc>(s, kMlpHid, kMlpOut, rows, m->h2, 1, kMlpHid, m->dy, kMlpOut, 1, m->g + kOffW3, kMlpOut, nullptr,
-                      nullptr, nullptr, split);
-    if (r) return r;
-    hipLaunchKernelGGL(k_colsum, dim3(64), dim3(256), 0, s, rows, kMlpOut, m->dyf, m->g + kOffB3);
-    r = gemm<kEpiGeluBwd>(s, rows, kMlpHid, kMlpOut, m->dy, kMlpOut, 1, W3, 1, kMlpOut, m->dz, kMlpHid, nullptr, m->dzb,
-                          m->z2, 1);
-    if (r) return r;
-    // layer 2
-    r = gemm<kEpiAcc>(s, kMlpHid, kMlpHid, rows, m->h1, 1, kMlpHid, m->dzb, kMlpHid, 1, m->g + kOffW2, kMlpHid, nullptr,
-                      nullptr, nullptr, split);
-    if (r) return r;
-    hipLaunchKernelGGL(k_colsum, dim3(64), dim3(256), 0, s, rows, kMlpHid, m->dz, m->g + kOffB2);
-    r = gemm<kEpiGeluBwd>(s, rows, kMlpHid, kMlpHid, m->dzb, kMlpHid, 1, W2, 1, kMlpHid, m->dz, kMlpHid, nullptr,
-                          m->dzb2, m->z1, 1);
-    if (r) return r;
-    // layer 1
-    r = gemm<kEpiAcc>(s, kMlpIn, kMlpHid, rows, X, 1, kMlpIn, m->dzb2, kMlpHid, 1, m->g + kOffW1, kMlpHid, nullptr,
-                      nullptr, nullptr, split);
-    if (r) return r;
-    hipLaunchKernelGGL(k_colsum, dim3(64), dim3(256), 0, s, rows, kMlpHid, m->dz, m->g + kOffB1);
-    VRM_HIP(hipGetLastError());
-    if (grad_out) VRM_HIP(hipMemcpyAsync(grad_out, m->g, sizeof(float) * kMlpParams, hipMemcpyDeviceToDevice, s));
-    if (loss_out) VRM_HIP(hipMemcpyAsync(loss_out, m->loss, sizeof(double), hipMemcpyDeviceToDevice, s));
+    // tiles of 16 rows, an even number of them (the row blocks of 32 are written whole)
+    const int nblk32 = (int)(((long)rows + kRowBlk - 1) / kRowBlk);
+    const int tiles = nblk32 * (kRowBlk / kTrainTile);
+    const int parts = tiles < kTrainBlocks ? tiles : kTrainBlocks;
+    hipLaunchKernelGGL(k_train_rows, dim3(parts), dim3(256), 0, s, rows, tiles, X, T, m->wt, m->wbf, m->w, wf, m->xt,
+                       m->h1t, m->h2t, m->dyt, m->dz2t, m->dz1t, m->bias_part, m->loss_part);
+    AdamW a{lr, wd, 1.0f, 1.0f, m->w, m->am, m->av, grad_out, m->wbf, m->wt};
     if (lr > 0.0f) {
         m->step += 1;
-        const float b1 = 0.9f, b2 = 0.999f;
-        float c1 = 1.0f - powf(b1, (float)m->step), c2 = 1.0f - powf(b2, (float)m->step);
-        hipLaunchKernelGGL(k_adamw, dim3(nblk(kMlpParams)), dim3(256), 0, s, kMlpParams, m->w, m->g, m->am, m->av, lr, b1,
-                           b2, 1e-8f, wd, c1, c2, m->wbf);
-        hipLaunchKernelGGL(k_transpose_w, dim3(nblk(kMlpIn * kMlpHid)), dim3(256), 0, s, m->wbf, m->wt);
-        VRM_HIP(hipGetLastError());
+        a.c1 = 1.0f - powf(0.9f, (float)m->step);
+        a.c2 = 1.0f - powf(0.999f, (float)m->step);
     }
+    hipLaunchKernelGGL(k_train_params, dim3(2 * kTilesW + kTilesW3 + kBiasCols / 64), dim3(1024), 0, s, nblk32, parts,
+                       m->xt, m->h1t, m->h2t, m->dyt, m->dz2t, m->dz1t, m->bias_part, m->loss_part, loss_out, a);
+    VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
 
@@ -708,6 +879,10 @@ int vrm_gemm_test(vrm_ctx* c, const uint16_t* A, const uint16_t* B, float* C, in
 {
     long sam = transA ? 1 : K, sak = transA ? M : 1;
     long sbk = transB ? 1 : N, sbn = transB ? K : 1;
-    return gemm<kEpiAcc>(c->stream, M, N, K, A, sam, sak, B, sbk, sbn, C, N, nullptr, nullptr, nullptr,
-                         K >= 1024 ? 8 : 1);
+    const int splitk = K >= 1024 ? 8 : 1;
+    const int kchunk = splitk > 1 ? ((K + splitk - 1) / splitk + TK - 1) / TK * TK : K;
+    hipLaunchKernelGGL(k_gemm, dim3((N + TN - 1) / TN, (M + TM - 1) / TM, (K + kchunk - 1) / kchunk), dim3(256), 0,
+                       c->stream, M, N, K, A, sam, sak, B, sbk, sbn, C, (long)N, kchunk);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
 }
