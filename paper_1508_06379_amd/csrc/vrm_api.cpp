@@ -205,10 +205,10 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(sel, 1);
     A(sel_bins, vrm::kSelBins);
     A(counters, (vrm::kCounterStripes * vrm::kCounterStride + sizeof(vrm_counters) - 1) / sizeof(vrm_counters));
-    A(cell_of, cap);
+    A(cell_count, nc + 7);
     A(rank, cap);
     A(cell_start, nc);
-    A(scan_part, 1024);
+    A(cell_scratch, 1);
     A(perm, cap);
     A(xs, cap);
     A(ys, cap);
@@ -268,6 +268,8 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
         if (e == hipSuccess) e = hipMemsetAsync(c->counters, 0, vrm::kCounterStripes * vrm::kCounterStride, c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->queues, 0, sizeof(vrm::Queues), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->sel, 0, sizeof(vrm::SelectState), c->stream);
+        if (e == hipSuccess) e = hipMemsetAsync(c->cell_count, 0, (nc + 7) * sizeof(int32_t), c->stream);
+        if (e == hipSuccess) e = hipMemsetAsync(c->cell_scratch, 0, sizeof(vrm::CellScratch), c->stream);
         if (e == hipSuccess) r = vrm_select_init(c);
         if (e == hipSuccess) e = hipMemsetAsync(c->grid, 0, sizeof(vrm::GridState), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->khist, 0, 2 * (VRM_KMAX + 1) * sizeof(int32_t), c->stream);
@@ -290,7 +292,7 @@ int vrm_destroy(vrm_ctx* c)
     if (!c) return VRM_OK;
     (void)hipSetDevice(c->device);
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_of, c->rank, c->cell_start, c->scan_part,
+    void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_count, c->rank, c->cell_start, c->cell_scratch,
                     c->perm, c->xs, c->ys, c->ids, c->diffused, c->acc, c->x0, c->y0, c->g0, c->q_small, c->q_full, c->q_retry,
                     c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->ccell, c->crank, c->cstart, c->cperm,
                     c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->verify_buf, c->sort_tmp, c->full_cols,

@@ -21,89 +21,126 @@ using namespace vrm;
 
 namespace {
 
-constexpr int kScanBlocks = 512;
-
-__global__ void k_grid_reset(GridState* g)
+// True in every thread of the last workgroup to get here; what the others wrote with
+// atomics whose results they waited for is complete then.  Two levels, so that the
+// workgroups do not queue on one address (18 ns each); done[17] is left zero.
+__device__ __forceinline__ bool last_here(int32_t* done)
 {
-    g->bad &= ~kBadPos;
-    g->bbox[0] = 0xffffffffu;
-    g->bbox[1] = 0xffffffffu;
-    g->bbox[2] = 0u;
-    g->bbox[3] = 0u;
+    __shared__ int s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int part = blockIdx.x & 15, in_part = ((int)gridDim.x - part + 15) / 16;
+        bool last = atomicAdd(&done[part], 1) == in_part - 1;
+        if (last) last = atomicAdd(&done[16], 1) == min((int)gridDim.x, 16) - 1;
+        s_last = last;
+    }
+    __syncthreads();
+    if (s_last && threadIdx.x < 17) done[threadIdx.x] = 0;
+    return s_last != 0;
 }
 
-__global__ __launch_bounds__(256) void k_bbox(const float* __restrict__ x, const float* __restrict__ y, int n,
-                                              const int32_t* __restrict__ n_dev, GridState* g)
+// The grid of a cloud: its bounding box, and by the last workgroup the cells.  Bound by
+// latency for small clouds and by HBM for large ones: eight particles of a thread are in
+// flight at once, and every workgroup leaves its box in a slot of its own (four atomics
+// of every workgroup on one address each were 18 of 35 us at 2.7M particles).
+constexpr int kBoxPer = 8;
+__global__ __launch_bounds__(256) void k_grid(const float* __restrict__ x, const float* __restrict__ y, int n,
+                                              const int32_t* __restrict__ n_dev, GridState* g, CellScratch* sc, float cs,
+                                              int ncell_cap, vrm_counters* cnt)
 {
     if (n_dev) n = *n_dev;
     uint32_t mnx = 0xffffffffu, mny = 0xffffffffu, mxx = 0u, mxy = 0u;
     bool bad = false;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        float xv = x[i], yv = y[i];
+    const int stride = gridDim.x * 256;
+    auto take = [&](float xv, float yv) {
         if (!(fabsf(xv) <= 3.4028235e38f) || !(fabsf(yv) <= 3.4028235e38f)) {
             bad = true;   // NaN or infinite: reported, never given a cell
-            continue;
+            return;
         }
-        uint32_t kx = ordered_key(xv), ky = ordered_key(yv);
+        const uint32_t kx = ordered_key(xv), ky = ordered_key(yv);
         mnx = min(mnx, kx);
         mny = min(mny, ky);
         mxx = max(mxx, kx);
         mxy = max(mxy, ky);
+    };
+    for (long i = blockIdx.x * 256 + threadIdx.x; i < n; i += (long)kBoxPer * stride) {
+        float xv[kBoxPer], yv[kBoxPer];
+#pragma unroll
+        for (int e = 0; e < kBoxPer; ++e) {
+            const long k = min(i + (long)e * stride, (long)n - 1);   // past the end: a repeat
+            xv[e] = x[k];
+            yv[e] = y[k];
+        }
+#pragma unroll
+        for (int e = 0; e < kBoxPer; ++e) take(xv[e], yv[e]);
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        mnx = min(mnx, (uint32_t)__shfl_xor((int)mnx, o, VRM_WAVE));
-        mny = min(mny, (uint32_t)__shfl_xor((int)mny, o, VRM_WAVE));
-        mxx = max(mxx, (uint32_t)__shfl_xor((int)mxx, o, VRM_WAVE));
-        mxy = max(mxy, (uint32_t)__shfl_xor((int)mxy, o, VRM_WAVE));
-    }
-    __shared__ uint32_t red[4][8];
-    int w = threadIdx.x >> 6;
-    if (lane_id() == 0) {
-        red[0][w] = mnx;
-        red[1][w] = mny;
-        red[2][w] = mxx;
-        red[3][w] = mxy;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int nw = blockDim.x >> 6;
-        for (int k = 1; k < nw; ++k) {
+    __shared__ uint32_t red[4][4];
+    // over the wave, then over the four waves
+    auto reduce = [&] {
+        for (int o = 32; o > 0; o >>= 1) {
+            mnx = min(mnx, (uint32_t)__shfl_xor((int)mnx, o, VRM_WAVE));
+            mny = min(mny, (uint32_t)__shfl_xor((int)mny, o, VRM_WAVE));
+            mxx = max(mxx, (uint32_t)__shfl_xor((int)mxx, o, VRM_WAVE));
+            mxy = max(mxy, (uint32_t)__shfl_xor((int)mxy, o, VRM_WAVE));
+        }
+        const int w = threadIdx.x >> 6;
+        __syncthreads();
+        if (lane_id() == 0) {
+            red[0][w] = mnx;
+            red[1][w] = mny;
+            red[2][w] = mxx;
+            red[3][w] = mxy;
+        }
+        __syncthreads();
+        for (int k = 0; k < 4; ++k) {
             mnx = min(mnx, red[0][k]);
             mny = min(mny, red[1][k]);
             mxx = max(mxx, red[2][k]);
             mxy = max(mxy, red[3][k]);
         }
-        atomicMin(&g->bbox[0], mnx);
-        atomicMin(&g->bbox[1], mny);
-        atomicMax(&g->bbox[2], mxx);
-        atomicMax(&g->bbox[3], mxy);
+    };
+    reduce();
+    uint32_t old = 0u;
+    if (threadIdx.x < 4)
+        old = atomicExch(&sc->box[threadIdx.x][blockIdx.x],
+                         threadIdx.x == 0 ? mnx : threadIdx.x == 1 ? mny : threadIdx.x == 2 ? mxx : mxy);
+    if (__any(bad) && lane_id() == 0) old |= (uint32_t)atomicOr(&sc->bad_seen, kBadPos);
+    asm volatile("" ::"v"(old));   // waits for the atomics' results
+    if (!last_here(sc->done)) return;
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += 256) {
+        mnx = min(mnx, __hip_atomic_load(&sc->box[0][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        mny = min(mny, __hip_atomic_load(&sc->box[1][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        mxx = max(mxx, __hip_atomic_load(&sc->box[2][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        mxy = max(mxy, __hip_atomic_load(&sc->box[3][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
-    if (__any(bad) && lane_id() == 0) atomicOr(&g->bad, kBadPos);
-}
-
-__global__ void k_grid_params(GridState* g, float cs, int ncell_cap, vrm_counters* cnt)
-{
+    reduce();
+    if (threadIdx.x != 0) return;
+    const int32_t bad_seen = __hip_atomic_load(&sc->bad_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sc->bad_seen = 0;
+    g->bad = (g->bad & ~kBadPos) | bad_seen;
     float xmin = 0.0f, ymin = 0.0f, xmax = 0.0f, ymax = 0.0f;
-    if (g->bbox[0] != 0xffffffffu) {
-        xmin = ordered_key_inv(g->bbox[0]);
-        ymin = ordered_key_inv(g->bbox[1]);
-        xmax = ordered_key_inv(g->bbox[2]);
-        ymax = ordered_key_inv(g->bbox[3]);
+    if (mnx != 0xffffffffu) {
+        xmin = ordered_key_inv(mnx);
+        ymin = ordered_key_inv(mny);
+        xmax = ordered_key_inv(mxx);
+        ymax = ordered_key_inv(mxy);
     }
     g->cs = cs;
-    g->inv_cs = 1.0f / cs;
-    g->x0 = xmin - cs;
-    g->y0 = ymin - cs;
-    double fx = ((double)xmax - (double)g->x0) * (double)g->inv_cs;
-    double fy = ((double)ymax - (double)g->y0) * (double)g->inv_cs;
+    const float inv_cs = 1.0f / cs, x0 = xmin - cs, y0 = ymin - cs;
+    g->inv_cs = inv_cs;
+    g->x0 = x0;
+    g->y0 = y0;
+    double fx = ((double)xmax - (double)x0) * (double)inv_cs;
+    double fy = ((double)ymax - (double)y0) * (double)inv_cs;
     long long nx = (long long)fmin(fx, 1.0e9) + 2;
     long long ny = (long long)fmin(fy, 1.0e9) + 2;
     int clamped = 0;
     if (nx * ny > ncell_cap) {
         // keep the aspect ratio; far particles share the edge cells (still exact, slower)
         double f = sqrt((double)ncell_cap / (double)(nx * ny));
-        nx = nx * f > 1 ? (long long)(nx * f) : 1;
-        ny = ncell_cap / nx;
+        // (a side alone may exceed the capacity: a few particles in a long, thin box)
+        nx = min(max((long long)(nx * f), 1ll), (long long)ncell_cap);
+        ny = min(ny, ncell_cap / nx);
         clamped = 1;
     }
     g->nx = (int)nx;
@@ -122,65 +159,50 @@ __device__ __forceinline__ int cell_index(const GridState& g, float x, float y)
     return (int)fy * g.nx + (int)fx;
 }
 
-__global__ __launch_bounds__(256) void k_clear_cells(int32_t* start, const GridState* g)
-{
-    int nc = g->ncells + 1;
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += gridDim.x * blockDim.x) start[c] = 0;
-}
-
+// count: particles per cell, zero before and after a build (k_cell_starts clears it)
 __global__ __launch_bounds__(256) void k_count(const float* __restrict__ x, const float* __restrict__ y, int n,
-                                               const int32_t* __restrict__ n_dev, const GridState* gs, int32_t* start,
-                                               int32_t* cell_of, int32_t* rank)
+                                               const int32_t* __restrict__ n_dev, const GridState* gs, int32_t* count,
+                                               int32_t* rank)
 {
     if (n_dev) n = *n_dev;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = i < n;
-    GridState g = *gs;
+    const GridState g = *gs;
     if (g.bad & kBadPos) return;   // a non-finite position: no cell indices (the same for every thread)
     const int c = live ? cell_index(g, x[i], y[i]) : -1;
-    if (live) cell_of[i] = c;
-    // The rank only has to be unique within the cell.  The cloud is kept in cell
-    // order, so the lanes of a wave share few cells: in up to eight rounds, the
-    // lanes in the cell of the first lane still waiting take consecutive ranks
-    // from one atomic; lanes left after that (an unsorted cloud) add alone.
+    // The rank only has to be unique within the cell.  The cloud is kept in cell order,
+    // so the lanes of a wave form runs of one cell: the first lane of a run adds for all,
+    // one atomic in flight per lane.  (Grouping the lanes of equal cells wherever they
+    // are, in rounds, each round's atomic waiting for the one before, took 73 us for 2.7M
+    // particles, with the atomics issued together 55, now 15.)
     const int lane = lane_id();
-    bool todo = live;
-    int r = 0;
-    for (int round = 0; round < 8; ++round) {
-        const uint64_t act = __ballot(todo);
-        if (!act) break;
-        const int leader = __ffsll((unsigned long long)act) - 1;
-        const int lc = __shfl(c, leader, 64);
-        const bool mine = todo && c == lc;
-        const uint64_t same = __ballot(mine);
-        int base = 0;
-        if (lane == leader) base = atomicAdd(&start[lc], __popcll(same));
-        base = __shfl(base, leader, 64);
-        if (mine) {
-            r = base + __popcll(same & ((1ull << lane) - 1ull));
-            todo = false;
-        }
-    }
-    if (todo) r = atomicAdd(&start[c], 1);
-    if (live) rank[i] = r;
+    const int left = __shfl_up(c, 1, VRM_WAVE);
+    const uint64_t heads = __ballot(lane == 0 || c != left);
+    const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+    const uint64_t after = lane == 63 ? 0ull : heads & (~0ull << (lane + 1));
+    const int at = lane - head, size = (after ? __ffsll((unsigned long long)after) - 1 : 64) - lane;   // of a head
+    int base = 0;
+    if (live && head == lane) base = atomicAdd(&count[c], size);
+    base = __shfl(base, head, VRM_WAVE);
+    if (live) rank[i] = base + at;
 }
 
-// ----- three-kernel exclusive scan over start[0..ncells), total in start[ncells]
+// exclusive scan over the workgroup
 __device__ __forceinline__ int block_exclusive_scan(int v, int& total)
 {
-    __shared__ int wsum[8];
-    int lane = lane_id(), w = threadIdx.x >> 6;
+    __shared__ int wsum[16];
+    const int lane = lane_id(), w = threadIdx.x >> 6;
     int incl = v;
     for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(incl, o, VRM_WAVE);
+        const int t = __shfl_up(incl, o, VRM_WAVE);
         if (lane >= o) incl += t;
     }
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
-    int nw = blockDim.x >> 6;
+    const int nw = blockDim.x >> 6;
     int off = 0, tot = 0;
     for (int k = 0; k < nw; ++k) {
-        int s = wsum[k];
+        const int s = wsum[k];
         if (k < w) off += s;
         tot += s;
     }
@@ -189,68 +211,100 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int& total)
     return off + incl - v;
 }
 
-__global__ __launch_bounds__(256) void k_scan_partial(const int32_t* start, const GridState* g, int32_t* part)
+// First slots of the cells: the exclusive scan of the counts, which are cleared, in one
+// launch.  A workgroup takes its chunk by a ticket, publishes the chunk's sum with the
+// launch's number in one 64-bit word, and adds the sums of the chunks before it: it waits
+// only for workgroups with lower tickets, which run already and publish before they
+// wait, so every wait ends whatever else runs on the GPU.  (Three launches before; each
+// is 4.6 us of a small cloud's stage.)  The launch's number is the ticket's upper part:
+// kCellParts divides 2^32, so it stays in step when the counter wraps.
+__global__ __launch_bounds__(1024) void k_cell_starts(int32_t* __restrict__ count, int32_t* __restrict__ start,
+                                                      const GridState* g, CellScratch* sc)
 {
-    int nc = g->ncells;
-    int chunk = (nc + kScanBlocks - 1) / kScanBlocks;
-    int lo = blockIdx.x * chunk, hi = min(nc, lo + chunk);
-    int s = 0;
-    for (int c = lo + threadIdx.x; c < hi; c += blockDim.x) s += start[c];
-    int tot;
-    block_exclusive_scan(s, tot);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(kScanBlocks) void k_scan_top(int32_t* part)
-{
-    int v = part[threadIdx.x];
-    int tot;
-    int ex = block_exclusive_scan(v, tot);
-    part[threadIdx.x] = ex;
-    if (threadIdx.x == 0) part[kScanBlocks] = tot;
-}
-
-__global__ __launch_bounds__(256) void k_scan_final(int32_t* start, const GridState* g, const int32_t* part)
-{
-    int nc = g->ncells;
-    int chunk = (nc + kScanBlocks - 1) / kScanBlocks;
-    int lo = blockIdx.x * chunk, hi = min(nc, lo + chunk);
-    int carry = part[blockIdx.x];
-    for (int base = lo; base < hi; base += blockDim.x) {
-        int c = base + threadIdx.x;
-        int v = c < hi ? start[c] : 0;
-        int tot;
-        int ex = block_exclusive_scan(v, tot);
-        if (c < hi) start[c] = carry + ex;
-        carry += tot;
+    __shared__ uint32_t s_ticket;
+    const int t = threadIdx.x;
+    if (t == 0) s_ticket = atomicAdd(&sc->ticket, 1u);
+    const int nc = g->ncells;
+    __syncthreads();
+    const int b = (int)(s_ticket % kCellParts);
+    const uint32_t launch = s_ticket / kCellParts + 1u;
+    // whole groups of four cells (the counts past the last cell are zero)
+    const int chunk = ((nc + kCellParts - 1) / kCellParts + 3) & ~3;
+    const int lo = min(nc, b * chunk), hi = min(nc, lo + chunk);
+    int sum = 0;
+    for (int c = lo + 4 * t; c < hi; c += 4 * 1024) {
+        const int4 v = *reinterpret_cast<const int4*>(&count[c]);
+        sum += v.x + v.y + v.z + v.w;
     }
-    if (blockIdx.x == kScanBlocks - 1 && threadIdx.x == 0) start[nc] = part[kScanBlocks];
+    int total;
+    (void)block_exclusive_scan(sum, total);
+    if (t == 0)
+        __hip_atomic_store(&sc->part[b], ((uint64_t)launch << 32) | (uint32_t)total, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    int before = 0;
+    if (t < b) {
+        uint64_t v;
+        while ((uint32_t)((v = __hip_atomic_load(&sc->part[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) !=
+               launch)
+            __builtin_amdgcn_s_sleep(1);
+        before = (int)(uint32_t)v;
+    }
+    int carry;
+    (void)block_exclusive_scan(before, carry);
+    for (int c0 = lo; c0 < hi; c0 += 4 * 1024) {
+        const int c = c0 + 4 * t;
+        int4 v = {0, 0, 0, 0};
+        if (c < hi) {
+            v = *reinterpret_cast<const int4*>(&count[c]);
+            *reinterpret_cast<int4*>(&count[c]) = int4{0, 0, 0, 0};
+        }
+        int tot;
+        const int ex = carry + block_exclusive_scan(v.x + v.y + v.z + v.w, tot);
+        carry += tot;
+        const int o[4] = {ex, ex + v.x, ex + v.x + v.y, ex + v.x + v.y + v.z};
+        if (c + 3 < hi) {
+            *reinterpret_cast<int4*>(&start[c]) = int4{o[0], o[1], o[2], o[3]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c + e < hi) start[c + e] = o[e];
+        }
+    }
+    if (b == kCellParts - 1 && t == 0) start[nc] = carry;
 }
 
 __global__ __launch_bounds__(256) void k_scatter(const float* __restrict__ x, const float* __restrict__ y,
                                                  const int32_t* __restrict__ id, int n,
                                                  const int32_t* __restrict__ n_dev,
-                                                 const int32_t* __restrict__ start, const int32_t* __restrict__ cell_of,
-                                                 const int32_t* __restrict__ rank, int32_t* perm, float* xs, float* ys,
-                                                 int32_t* ids, const GridState* gs)
+                                                 const int32_t* __restrict__ start, const int32_t* __restrict__ rank,
+                                                 int32_t* perm, float* xs, float* ys, int32_t* ids, const GridState* gs)
 {
     if (n_dev) n = *n_dev;
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || (gs->bad & kBadPos)) return;
-    int t = start[cell_of[i]] + rank[i];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const GridState g = *gs;
+    if (i >= n || (g.bad & kBadPos)) return;
+    const float xi = x[i], yi = y[i];
+    const int t = start[cell_index(g, xi, yi)] + rank[i];
     perm[t] = i;
     if (xs) {
-        xs[t] = x[i];
-        ys[t] = y[i];
+        xs[t] = xi;
+        ys[t] = yi;
         ids[t] = id[i];
     }
 }
 
-int scan_cells(vrm_ctx* c, int32_t* start)
+// The cell list of (x, y) on the grid in ctx: first slots, and the points in slot order
+// (xs, ys, ids may be NULL).
+int cell_list(vrm_ctx* c, const float* x, const float* y, const int32_t* id, int32_t n, const int32_t* n_dev,
+              int32_t* start, int32_t* rank, int32_t* perm, float* xs, float* ys, int32_t* ids)
 {
-    hipLaunchKernelGGL(k_scan_partial, dim3(kScanBlocks), dim3(256), 0, c->stream, start, c->grid, c->scan_part);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanBlocks), 0, c->stream, c->scan_part);
-    hipLaunchKernelGGL(k_scan_final, dim3(kScanBlocks), dim3(256), 0, c->stream, start, c->grid, c->scan_part);
+    hipStream_t s = c->stream;
+    const int nb = (n + 255) / 256;
+    if (n > 0) hipLaunchKernelGGL(k_count, dim3(nb), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_count, rank);
+    hipLaunchKernelGGL(k_cell_starts, dim3(kCellParts), dim3(1024), 0, s, c->cell_count, start, c->grid, c->cell_scratch);
+    if (n > 0)
+        hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(256), 0, s, x, y, id, n, n_dev, start, rank, perm, xs, ys, ids,
+                           c->grid);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
@@ -349,7 +403,7 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_pass(const float* __restrict_
     constexpr int COPIES = kSelLds / USED < 32 ? kSelLds / USED : 32;
     __shared__ double h[USED * COPIES];
     __shared__ double wtot[kSelBlock / 64];
-    __shared__ int s_first, s_last;
+    __shared__ int s_first;
     const int t = threadIdx.x;
     const bool done = !FIRST && s->done != 0u;
     const uint32_t pre = FIRST ? 0u : s->key_prefix;
@@ -388,18 +442,8 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_pass(const float* __restrict_
             }
         }
     }
-    __syncthreads();
-    if (t == 0) {
-        // two levels, so that the workgroups do not queue on one address
-        const int part = blockIdx.x & 15, in_part = ((int)gridDim.x - part + 15) / 16;
-        bool last = atomicAdd(&s->done_blocks[part], 1) == in_part - 1;
-        if (last) last = atomicAdd(&s->done_blocks[16], 1) == min((int)gridDim.x, 16) - 1;
-        s_last = last;
-        s_first = NB;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    if (t < 17) s->done_blocks[t] = 0;
+    if (t == 0) s_first = NB;
+    if (!last_here(s->done_blocks)) return;
     if (FIRST) {
         // what the step's later kernels start from
         if (cnt && t < kCounterStripes)
@@ -867,26 +911,13 @@ int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* i
 {
     ScopedTimer tm(c, VRM_T_CELLS);
     hipStream_t s = c->stream;
-    hipLaunchKernelGGL(k_grid_reset, dim3(1), dim3(1), 0, s, c->grid);
-    int nbb = min(256, blocks_for(n));
-    hipLaunchKernelGGL(k_bbox, dim3(nbb), dim3(256), 0, s, x, y, n, n_dev, c->grid);
-    float Rmax = (float)fmax((double)lp.hi2, (double)lp.hi2f);
-    float cs = sqrtf(Rmax) * (1.0f + 1.0f / 1024.0f);
-    hipLaunchKernelGGL(k_grid_params, dim3(1), dim3(1), 0, s, c->grid, cs, c->ncell_cap, c->counters);
-    hipLaunchKernelGGL(k_clear_cells, dim3(1024), dim3(256), 0, s, c->cell_start, c->grid);
-    if (n > 0) {
-        hipLaunchKernelGGL(k_count, dim3(blocks_for(n)), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_start,
-                           c->cell_of, c->rank);
-    }
-    VRM_HIP(hipGetLastError());
-    int r = scan_cells(c, c->cell_start);
-    if (r) return r;
-    if (n > 0) {
-        hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n)), dim3(256), 0, s, x, y, id, n, n_dev, c->cell_start,
-                           c->cell_of, c->rank, c->perm, c->xs, c->ys, c->ids, c->grid);
-    }
-    VRM_HIP(hipGetLastError());
-    return VRM_OK;
+    const float Rmax = (float)fmax((double)lp.hi2, (double)lp.hi2f);
+    const float cs = sqrtf(Rmax) * (1.0f + 1.0f / 1024.0f);
+    // (at least one workgroup, which sets the grid of an empty cloud)
+    const int nbb = std::max(1, min(kBoxBlocks, (n + 256 * kBoxPer - 1) / (256 * kBoxPer)));
+    hipLaunchKernelGGL(k_grid, dim3(nbb), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_scratch, cs, c->ncell_cap,
+                       c->counters);
+    return cell_list(c, x, y, id, n, n_dev, c->cell_start, c->rank, c->perm, c->xs, c->ys, c->ids);
 }
 
 // The selection's threshold of the cloud's n_dev particles (and, with it, cleared
@@ -961,16 +992,9 @@ int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp)
     int na = 0;
     if (nc > 0) {
         // cell list of the candidates on the particles' grid
-        hipLaunchKernelGGL(k_clear_cells, dim3(1024), dim3(256), 0, s, c->cstart, c->grid);
-        hipLaunchKernelGGL(k_count, dim3(blocks_for(nc)), dim3(256), 0, s, c->cx, c->cy, nc, (const int32_t*)nullptr,
-                           c->grid, c->cstart, c->ccell, c->crank);
-        VRM_HIP(hipGetLastError());
-        int r = scan_cells(c, c->cstart);
-        if (r) return r;
-        hipLaunchKernelGGL(k_scatter, dim3(blocks_for(nc)), dim3(256), 0, s, c->cx, c->cy, (const int32_t*)nullptr,
-                           nc, (const int32_t*)nullptr, c->cstart, c->ccell, c->crank, c->cperm, (float*)nullptr,
-                           (float*)nullptr, (int32_t*)nullptr, c->grid);
-        VRM_HIP(hipGetLastError());
+        if (int r = cell_list(c, c->cx, c->cy, nullptr, nc, nullptr, c->cstart, c->crank, c->cperm, nullptr, nullptr,
+                              nullptr))
+            return r;
         for (;;) {
             const int batch = 4;
             for (int k = 0; k < batch; ++k) {

@@ -53,7 +53,6 @@ __device__ __forceinline__ vrm_counters* counter_stripe(vrm_counters* base)
 
 // Grid of square cells over the bounding box of the cloud (device side).
 struct GridState {
-    uint32_t bbox[4];      // ordered keys: min x, min y, max x, max y
     float x0, y0, cs, inv_cs;
     int32_t nx, ny, ncells, clamped;
     // kBadPos: a position the last cell build read was not finite; kBadGamma: a
@@ -62,6 +61,16 @@ struct GridState {
     int32_t bad;
     // bits of max |Gamma^n| (stage 0): scale of the fixed-point accumulation
     uint32_t gmax_bits;
+};
+// Scratch of a cell build; `done` and `bad_seen` are zero between builds.
+constexpr int kBoxBlocks = 1024;
+constexpr int kCellParts = 128;   // a power of two
+struct CellScratch {
+    uint32_t box[4][kBoxBlocks];   // the workgroups' boxes: ordered keys of min x, min y, max x, max y
+    uint64_t part[kCellParts];     // launch number over the sum of a chunk's counts
+    uint32_t ticket;
+    int32_t bad_seen;
+    int32_t done[17];
 };
 constexpr int32_t kBadPos = 1;
 constexpr int32_t kBadGamma = 2;
@@ -220,10 +229,10 @@ struct vrm_ctx {
     vrm::SelectState* sel;
     double* sel_bins;     // [kSelBins] sums of a radix pass, zero between selections
     vrm_counters* counters;
-    int32_t* cell_of;     // [cap] cell of particle
+    int32_t* cell_count;  // [ncell_cap + 8] particles per cell, zero between builds
     int32_t* rank;        // [cap] rank within its cell
     int32_t* cell_start;  // [ncell_cap + 1]
-    int32_t* scan_part;   // [1024]
+    vrm::CellScratch* cell_scratch;
     int32_t* perm;        // [cap] slot -> particle
     float* xs;            // [cap] positions in slot order
     float* ys;
