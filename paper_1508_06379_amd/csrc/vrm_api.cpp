@@ -230,7 +230,6 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(cy, cap2);
     A(ckey, cap2);
     A(cstate, cap2);
-    A(ccell, cap2);
     A(crank, cap2);
     A(cstart, nc);
     A(cperm, cap2);
@@ -250,7 +249,7 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(pmask, cap);
 #undef A
     if (r == VRM_OK) {
-        c->sort_tmp_bytes = std::max(vrm_sort_tmp_bytes(capacity), vrm_remove_tmp_bytes(capacity));
+        c->sort_tmp_bytes = vrm_sort_tmp_bytes(capacity);
         void* p = nullptr;
         hipError_t e = hipMalloc(&p, c->sort_tmp_bytes + 256);
         if (e != hipSuccess) r = vrm_hip_check(e, "hipMalloc(sort)");
@@ -294,7 +293,7 @@ int vrm_destroy(vrm_ctx* c)
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_count, c->rank, c->cell_start, c->cell_scratch,
                     c->perm, c->xs, c->ys, c->ids, c->diffused, c->acc, c->x0, c->y0, c->g0, c->q_small, c->q_full, c->q_retry,
-                    c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->ccell, c->crank, c->cstart, c->cperm,
+                    c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->crank, c->cstart, c->cperm,
                     c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->verify_buf, c->sort_tmp, c->full_cols,
                     c->full_k, c->full_order, c->khist, c->lkey, c->pivhist, c->q_defer, c->pmask};
     for (void* p : ptrs)
@@ -428,7 +427,7 @@ int vrm_remove_particles(vrm_ctx* c, vrm_cloud* cl, const vrm_params* p, int32_t
     R.cs_lo = (float)((double)L.sc * (double)L.sc - (double)R.cs_hi);
     R.phase1 = 0;
     int32_t nc = 0;
-    const int m = vrm_remove_run(c, cl, c->n, R, &nc);
+    const int m = vrm_remove_run(c, cl, c->n, R, c->n <= c->tuning.full_stored_cost_n, &nc);
     if (m < 0) return m;
     if (n_candidates) *n_candidates = nc;
     if (n_removed) *n_removed = c->n - m;

@@ -333,19 +333,6 @@ __global__ __launch_bounds__(256) void k_sel_init(SelectState* s, double* bins, 
     }
 }
 
-// One thread copies the queue record (and the cloud's count) to the host copy, then
-// writes the sequence number with a system-scope release (after a system fence).
-__device__ __forceinline__ void publish(const Queues* q, const GridState* g, int n_now, HostQueues* h, int32_t seq)
-{
-    if (q) {
-        h->q = *q;
-        h->q.nonfinite = g->bad;
-    }
-    h->q.n_now = n_now;
-    __threadfence_system();
-    __hip_atomic_store(&h->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 __global__ void k_publish_queues(const Queues* q, const GridState* g, const int32_t* n_dev, HostQueues* h, int32_t seq)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) publish(q, g, n_dev ? *n_dev : 0, h, seq);
@@ -881,7 +868,7 @@ int blocks_for(int n) { return n > 0 ? (n + 255) / 256 : 1; }
 // The host spins on the sequence number; every 256 polls it asks the stream:
 // an error ends the wait with that error, and a finished stream without the
 // record is a state error (so a wait cannot outlast the stream's work).
-static int wait_queues(vrm_ctx* c, int32_t seq, Queues& q)
+int vrm_wait_queues(vrm_ctx* c, int32_t seq, Queues& q)
 {
     for (uint64_t k = 1;; ++k) {
         if (__atomic_load_n(&c->q_host->seq, __ATOMIC_ACQUIRE) == seq) break;
@@ -902,7 +889,7 @@ int vrm_read_queues(vrm_ctx* c, Queues& q, const int32_t* n_dev)
     const int32_t seq = ++c->q_seq;
     hipLaunchKernelGGL(k_publish_queues, dim3(1), dim3(64), 0, c->stream, c->queues, c->grid, n_dev, c->q_host, seq);
     VRM_HIP(hipGetLastError());
-    return wait_queues(c, seq, q);
+    return vrm_wait_queues(c, seq, q);
 }
 
 // Cell list of (x, y) into ctx->cell_start / perm / xs, ys, ids (slot order).
@@ -941,7 +928,7 @@ int vrm_select_run(vrm_ctx* c, const vrm_cloud* cl, int32_t guess, double factor
                        c->q_host, seq);
     VRM_HIP(hipGetLastError());
     Queues q;
-    if (int r = wait_queues(c, seq, q)) return r;
+    if (int r = vrm_wait_queues(c, seq, q)) return r;
     n = q.n_now;
     return VRM_OK;
 }
@@ -980,7 +967,7 @@ int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp)
                        c->counters, c->sel, c->grid, c->q_host, seq);
     VRM_HIP(hipGetLastError());
     Queues q;
-    if (int r = wait_queues(c, seq, q)) return r;
+    if (int r = vrm_wait_queues(c, seq, q)) return r;
     if (q.nonfinite) return vrm_nonfinite(c, q.nonfinite);
     if (q.small_state == 2)
         return vrm_fail(VRM_E_CAPACITY, "insertion needs %d particles, capacity is %d", n + q.n_accepted,

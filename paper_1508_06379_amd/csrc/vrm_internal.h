@@ -65,15 +65,20 @@ struct GridState {
 // Scratch of a cell build; `done` and `bad_seen` are zero between builds.
 constexpr int kBoxBlocks = 1024;
 constexpr int kCellParts = 128;   // a power of two
+constexpr int kPackTiles = 16384; // of 4096 particles
 struct CellScratch {
     uint32_t box[4][kBoxBlocks];   // the workgroups' boxes: ordered keys of min x, min y, max x, max y
     uint64_t part[kCellParts];     // launch number over the sum of a chunk's counts
+    uint64_t pack[kPackTiles];     // removal: call number, kind and count of a tile
     uint32_t ticket;
+    int32_t pack_ticket;           // zero between calls
     int32_t bad_seen;
     int32_t done[17];
 };
 constexpr int32_t kBadPos = 1;
 constexpr int32_t kBadGamma = 2;
+
+constexpr int kRmRounds = 8;   // rounds of the removal's selection per wait
 
 // Queue counters of a stage (device side).
 struct Queues {
@@ -87,8 +92,8 @@ struct Queues {
     int32_t blocks_done;   // blocks of the last LP launch that have finished
     int32_t last_small;    // n_small and n_full of the last stencil run (the queues
     int32_t last_full;     // themselves are zero between runs)
-    int32_t n_removed;     // particle removal: particles removed by the last call
-    int32_t n_rm_uncertified;   // ... of which optimality was not certified
+    int32_t n_rm_uncertified;   // particle removal: particles whose optimality was not certified
+    int32_t rm_open[8];    // round k of a batch left candidates undecided
     int32_t nonfinite;     // copy of GridState::bad taken when the record is published
     int32_t n_defer;       // complete LPs whose certification was deferred to a second launch
     int32_t n_now;         // the cloud's count when the record was published
@@ -115,6 +120,20 @@ struct HostQueues {
     Queues q;
     int32_t seq;
 };
+
+// One thread copies the queue record (and the cloud's count) to the host copy, then
+// writes the sequence number with a system-scope release (after a system fence).
+__device__ __forceinline__ void publish(const Queues* q, const GridState* g, int n_now, HostQueues* h, int32_t seq)
+{
+    if (q) {
+        h->q = *q;
+        h->q.nonfinite = g->bad;
+    }
+    h->q.n_now = n_now;
+    __threadfence_system();
+    __hip_atomic_store(&h->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 
 // Column records of the queued small-neighbourhood LPs, in queue order and
 // plane-major (plane p of item r at p * cap + r) so that the LP and network
@@ -251,7 +270,6 @@ struct vrm_ctx {
     float* cy;
     uint64_t* ckey;       // [2 cap] (id << 3) | segment
     uint8_t* cstate;      // [2 cap] 0 undecided, 1 in, 2 out
-    int32_t* ccell;       // [2 cap]
     int32_t* crank;
     int32_t* cstart;      // [ncell_cap + 1]
     int32_t* cperm;       // [2 cap]
@@ -353,9 +371,11 @@ int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const vrm::LaunchParams
 // the queue record after the work enqueued so far on the context's stream,
 // read from the pinned host copy (no stream synchronisation); n_now of n_dev unless NULL
 int vrm_read_queues(vrm_ctx* c, vrm::Queues& q, const int32_t* n_dev = nullptr);
+// the record a kernel publishes with the number seq
+int vrm_wait_queues(vrm_ctx* c, int32_t seq, vrm::Queues& q);
 int vrm_reorder_cloud(vrm_ctx* c, vrm_cloud* cl, int32_t n);
-int vrm_remove_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, int32_t* n_candidates);
-size_t vrm_remove_tmp_bytes(int32_t cap);
+int vrm_remove_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, bool stored,
+                   int32_t* n_candidates);
 // launchers (vrm_lp.hip)
 int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
                     const vrm_stencils* out, int apply, uint16_t* feat_out = nullptr, float* label_out = nullptr,

@@ -603,7 +603,7 @@ __device__ int scan_members(int t, float xi, float yi, const GridState& g, const
 // FP32 ones; the simplex starts on the nearest `work` columns (the choices of the
 // one-thread kernels, so that the pivots are theirs)
 template <int M>
-__global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_lp_group(const int32_t* __restrict__ perm, const float* __restrict__ xs,
+__global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(M == 3 ? 5 : 3))) void k_lp_group(const int32_t* __restrict__ perm, const float* __restrict__ xs,
                                                       const float* __restrict__ ys, const int32_t* __restrict__ ids,
                                                       const int32_t* __restrict__ cell_start, const GridState* gs,
                                                       const int32_t* __restrict__ q_full, Queues* qs,
@@ -619,11 +619,14 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
     if (tid < kCounts) s_cnt[tid] = 0;
     __syncthreads();
     // more than `limit` in q_full: the launches before solved them, but for the retry queue
-    const bool left = qs->n_full > limit;
-    const int nitems = left ? qs->n_retry : qs->n_full;
-    const int32_t* __restrict__ queue = left ? q_retry : q_full;
+    const bool left = M != 3 && qs->n_full > limit;
     const GridState g = *gs;
-    const double dsc = P.det && apply ? det_scale(g.gmax_bits) : 0.0;
+    // (M = 3, the removal: nothing if a circulation is not finite or the choice of the
+    // particles is not complete)
+    const int nitems = M == 3 ? (g.bad || qs->rm_open[kRmRounds - 1] ? 0 : qs->n_accepted)
+                       : left ? qs->n_retry : qs->n_full;
+    const int32_t* __restrict__ queue = left ? q_retry : q_full;
+    const double dsc = M != 3 && P.det && apply ? det_scale(g.gmax_bits) : 0.0;
     for (int item = blockIdx.x * kGGroups + tid / kGL; item < nitems; item += gridDim.x * kGGroups) {
         const int t = queue[item];
         const int i = perm[t];
@@ -774,7 +777,9 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
                     out.full_f[(size_t)i * VRM_KMAX + at] = v;
                 }
             }
-            if (s == 0) {
+            if (M == 3) {
+                if (s == 0) out.status[i] = 1;   // removed
+            } else if (s == 0) {
                 if (apply) acc_add(acc, i, fii, g_i, dsc);
                 if (out.full_k) {
                     out.full_k[i] = nz;
@@ -795,7 +800,7 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
                     if (s >= have && s < kPrevIds) out.prev[(size_t)own * kPrevIds + s] = -1;
                 }
             }
-        } else if (s == 0 && out.status) {
+        } else if (M != 3 && s == 0 && out.status) {
             out.status[i] = VRM_ST_INFEASIBLE;
         }
         if (s == 0) {
@@ -816,6 +821,10 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
         }
     }
     __syncthreads();
+    if constexpr (M == 3) {
+        if (tid == 0 && s_cnt[kUnc]) atomicAdd(&qs->n_rm_uncertified, s_cnt[kUnc]);
+        return;
+    }
     if (tid < kCounts && s_cnt[tid]) {
         vrm_counters* c = counter_stripe(cnt);
         int64_t* to[kCounts] = {&c->pivots, &c->full_cols, &c->n_full, &c->n_infeasible, &c->n_uncertified,
@@ -840,6 +849,23 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(3))) vo
 }
 
 }  // namespace
+
+// The removal's identity LPs: of the slots in `taken` (n_accepted of the queues), with
+// removed[particle] set where the circulation was given away.  One thread per LP with
+// its columns in LDS (three waves per CU) took 154 us for a removal from 2.7M particles
+// (one particle in twenty close to another), now 95; three waves per SIMD 115.
+int vrm_rm_lp_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, const int32_t* taken,
+                  uint8_t* removed, bool stored)
+{
+    StencilOut out{};
+    out.status = removed;
+    const int grid = std::max(1, std::min((n + kGGroups - 1) / kGGroups, 5 * 256));
+    hipLaunchKernelGGL(k_lp_group<3>, dim3(grid), dim3(kGBlock), 0, c->stream, c->perm, c->xs, c->ys, c->ids,
+                       c->cell_start, c->grid, taken, c->queues, cl->gamma_dev, c->acc, lp, out, 1, c->counters,
+                       stored ? VRM_KMAX : 0, VRM_KMAX, (const int32_t*)nullptr, 0);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
+}
 
 // Canonical stencils, cold.  stored: the one-thread kernel of the same cloud keeps its costs.
 int vrm_lp_group_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, const StencilOut& out,
