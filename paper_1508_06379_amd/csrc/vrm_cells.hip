@@ -150,13 +150,20 @@ __global__ __launch_bounds__(256) void k_grid(const float* __restrict__ x, const
     if (clamped) atomicAdd(&cnt->n_grid_clamped, 1);
 }
 
-__device__ __forceinline__ int cell_index(const GridState& g, float x, float y)
+__device__ __forceinline__ void cell_xy(const GridState& g, float x, float y, int& cx, int& cy)
 {
     float fx = (x - g.x0) * g.inv_cs;
     float fy = (y - g.y0) * g.inv_cs;
     fx = fminf(fmaxf(fx, 0.0f), (float)(g.nx - 1));
     fy = fminf(fmaxf(fy, 0.0f), (float)(g.ny - 1));
-    return (int)fy * g.nx + (int)fx;
+    cx = (int)fx;
+    cy = (int)fy;
+}
+__device__ __forceinline__ int cell_index(const GridState& g, float x, float y)
+{
+    int cx, cy;
+    cell_xy(g, x, y, cx, cy);
+    return cy * g.nx + cx;
 }
 
 // count: particles per cell, zero before and after a build (k_cell_starts clears it)
@@ -286,25 +293,18 @@ __global__ __launch_bounds__(256) void k_scatter(const float* __restrict__ x, co
     const float xi = x[i], yi = y[i];
     const int t = start[cell_index(g, xi, yi)] + rank[i];
     perm[t] = i;
-    if (xs) {
-        xs[t] = xi;
-        ys[t] = yi;
-        ids[t] = id[i];
-    }
+    xs[t] = xi;
+    ys[t] = yi;
+    ids[t] = id[i];
 }
 
-// The cell list of (x, y) on the grid in ctx: first slots, and the points in slot order
-// (xs, ys, ids may be NULL).
-int cell_list(vrm_ctx* c, const float* x, const float* y, const int32_t* id, int32_t n, const int32_t* n_dev,
-              int32_t* start, int32_t* rank, int32_t* perm, float* xs, float* ys, int32_t* ids)
+// Slots of (x, y) on the grid in ctx: the cells' first slots, each point's rank in its cell.
+int cell_slots(vrm_ctx* c, const float* x, const float* y, int32_t n, const int32_t* n_dev, int32_t* start, int32_t* rank)
 {
     hipStream_t s = c->stream;
-    const int nb = (n + 255) / 256;
-    if (n > 0) hipLaunchKernelGGL(k_count, dim3(nb), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_count, rank);
-    hipLaunchKernelGGL(k_cell_starts, dim3(kCellParts), dim3(1024), 0, s, c->cell_count, start, c->grid, c->cell_scratch);
     if (n > 0)
-        hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(256), 0, s, x, y, id, n, n_dev, start, rank, perm, xs, ys, ids,
-                           c->grid);
+        hipLaunchKernelGGL(k_count, dim3((n + 255) / 256), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_count, rank);
+    hipLaunchKernelGGL(k_cell_starts, dim3(kCellParts), dim3(1024), 0, s, c->cell_count, start, c->grid, c->cell_scratch);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }
@@ -450,7 +450,6 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_pass(const float* __restrict_
             gs->bad = (gs->bad & ~kBadGamma) | (bad ? kBadGamma : 0);
             if (qs) {
                 qs->n_cand = 0;
-                qs->n_undecided = 0;
                 qs->n_accepted = 0;
                 qs->small_state = 0;
             }
@@ -624,84 +623,242 @@ __global__ __launch_bounds__(256) void k_candidates(int n, const int32_t* __rest
     }
 }
 
+// The candidates in cell order, as the rounds read them: position and key by slot.
+struct CandSlots {
+    float* x;
+    float* y;
+    uint64_t* key;
+    uint8_t* state;     // 0 undecided, 1 accepted, 2 rejected
+    int32_t* taken;     // accepted slots, in no order
+    uint32_t* mask;     // by particle id, a byte each: segments with an accepted candidate
+};
+
+// Cleared marks of the ids in the cloud (up to the capacity) and of the rounds.
+__global__ __launch_bounds__(256) void k_ins_begin(int capacity, const SelectState* sel, CandSlots C, Queues* qs)
+{
+    const int words = ((int)min((long)sel->max_id + 1, (long)capacity) + 3) / 4;
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < words; k += gridDim.x * 256) C.mask[k] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < kRmRounds) qs->rm_open[threadIdx.x] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_ins_scatter(const float* __restrict__ cx, const float* __restrict__ cy,
+                                                     const uint64_t* __restrict__ ckey, int nc,
+                                                     const int32_t* __restrict__ start,
+                                                     const int32_t* __restrict__ rank, CandSlots C, const GridState* gs)
+{
+    const int a = blockIdx.x * 256 + threadIdx.x;
+    if (a >= nc) return;
+    const float x = cx[a], y = cy[a];
+    const int u = start[cell_index(*gs, x, y)] + rank[a];
+    C.x[u] = x;
+    C.y[u] = y;
+    C.key[u] = ckey[a];
+}
+
 // One round of the lexicographically first independent set: a candidate is
 // accepted once every conflicting candidate of smaller key is rejected, and
-// rejected as soon as one of them is accepted.
-__global__ __launch_bounds__(256) void k_mis_round(int nc, const float* __restrict__ cx, const float* __restrict__ cy,
-                                                   const uint64_t* __restrict__ ckey, uint8_t* cstate,
-                                                   const int32_t* __restrict__ cstart, const int32_t* __restrict__ cperm,
-                                                   const GridState* gs, float ex2, Queues* qs)
+// rejected as soon as one of them is accepted.  (States only go from undecided to
+// accepted or rejected, and either value of one that changes leads to the same set, so
+// caches may hold older ones.)  Bound by latency: eight candidates of the cells within
+// reach are read at once.  Accepted ones are queued and marked by id.  A round that leaves
+// one undecided sets rm_open[round]; the rounds after one that left none do nothing.
+// 640k particles, a tenth of the lattice gone: with an index per candidate, all nine cells and one
+// candidate at a time, 148 us for the first round and 500 for all, now 54 and 115.
+constexpr int kInsBlock = 512;
+__global__ __launch_bounds__(kInsBlock) void k_mis_round(int round, int nc, CandSlots C,
+                                                         const int32_t* __restrict__ cstart, const GridState* gs,
+                                                         float ex2, int capacity, Queues* qs)
 {
-    int a = blockIdx.x * blockDim.x + threadIdx.x;
-    bool undecided = false;
-    if (a < nc && cstate[a] == 0) {
-        GridState g = *gs;
-        float xa = cx[a], ya = cy[a];
-        uint64_t ka = ckey[a];
-        int c0 = cell_index(g, xa, ya);
-        int cxa = c0 % g.nx, cya = c0 / g.nx;
+    __shared__ int s_n, s_at;
+    if (round > 0 && !qs->rm_open[round - 1]) return;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const int u = blockIdx.x * kInsBlock + threadIdx.x;
+    auto state_of = [&](int v) {
+        return __hip_atomic_load(&C.state[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    };
+    bool take = false, open = false;
+    if (u < nc && state_of(u) == 0) {
+        const GridState g = *gs;
+        const float px = C.x[u], py = C.y[u];
+        const uint64_t ka = C.key[u];
+        // the cells that the square around the candidate touches (an upper bound of the
+        // offsets whose FP32 squared length is below ex2; cell indices are monotone)
+        const float rad = sqrtf(ex2) * (1.0f + 9.5367431640625e-7f);
+        const float xa = px - rad, xb = px + rad, ya = py - rad, yb = py + rad;
+        int cx0, cy0, cx1, cy1;
+        cell_xy(g, xa - fabsf(xa) * 2.384185791015625e-7f, ya - fabsf(ya) * 2.384185791015625e-7f, cx0, cy0);
+        cell_xy(g, xb + fabsf(xb) * 2.384185791015625e-7f, yb + fabsf(yb) * 2.384185791015625e-7f, cx1, cy1);
         bool any_in = false, any_open = false;
-        for (int oy = -1; oy <= 1 && !any_in; ++oy) {
-            int yy = cya + oy;
-            if (yy < 0 || yy >= g.ny) continue;
-            for (int ox = -1; ox <= 1 && !any_in; ++ox) {
-                int xx = cxa + ox;
-                if (xx < 0 || xx >= g.nx) continue;
-                int c = yy * g.nx + xx;
-                for (int u = cstart[c]; u < cstart[c + 1]; ++u) {
-                    int b = cperm[u];
-                    if (b == a || ckey[b] >= ka) continue;
-                    float dx = cx[b] - xa;
-                    float dy = cy[b] - ya;
-                    if (!(d2_f32(dx, dy) < ex2)) continue;
-                    uint8_t sb = ((volatile const uint8_t*)cstate)[b];
-                    if (sb == 1) {
-                        any_in = true;
-                        break;
-                    }
-                    if (sb == 0) any_open = true;
+        for (int yy = cy0; yy <= cy1 && !any_in; ++yy) {
+            const int u0 = cstart[yy * g.nx + cx0], u1 = cstart[yy * g.nx + cx1 + 1];
+            for (int v0 = u0; v0 < u1 && !any_in; v0 += 8) {
+                float bx[8], by[8];
+                uint64_t kb[8];
+                uint8_t sb[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int v = min(v0 + e, u1 - 1);   // past the end: a repeat
+                    bx[e] = C.x[v];
+                    by[e] = C.y[v];
+                    kb[e] = C.key[v];
+                    sb[e] = state_of(v);
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    // (not itself: its key is not smaller)
+                    const bool near = kb[e] < ka && d2_f32(bx[e] - px, by[e] - py) < ex2;
+                    any_in = any_in || (near && sb[e] == 1);
+                    any_open = any_open || (near && sb[e] == 0);
                 }
             }
         }
-        if (any_in)
-            cstate[a] = 2;
-        else if (!any_open)
-            cstate[a] = 1;
-        else
-            undecided = true;
+        take = !any_in && !any_open;
+        open = !any_in && any_open;
+        if (!open)
+            __hip_atomic_store(&C.state[u], (uint8_t)(take ? 1 : 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        if (take) {
+            const uint64_t id = ka >> 3;
+            if (id < (uint64_t)capacity) atomicOr(&C.mask[id >> 2], 1u << (8 * (uint32_t)(id & 3) + (uint32_t)(ka & 7)));
+        }
     }
-    // a flag (the host only asks whether any candidate is left)
-    if (undecided) qs->n_undecided = 1;
+    const uint64_t m = __ballot(take);
+    int at = 0;
+    if (m && lane_id() == 0) at = atomicAdd(&s_n, __popcll(m));
+    at = __shfl(at, 0, VRM_WAVE) + __popcll(m & ((1ull << lane_id()) - 1ull));
+    const int left = __syncthreads_or(open);
+    if (threadIdx.x == 0) {
+        if (s_n) s_at = atomicAdd(&qs->n_accepted, s_n);
+        if (left) qs->rm_open[round] = 1;
+    }
+    __syncthreads();
+    if (take) C.taken[s_at + at] = u;
 }
 
-__global__ __launch_bounds__(256) void k_accepted(int nc, const uint64_t* __restrict__ ckey,
-                                                  const uint8_t* __restrict__ cstate, Queues* qs, uint64_t* akey,
-                                                  int32_t* aidx)
+// The accepted candidates' order: keys are (id, segment), so the number of marks before a
+// group of sixteen ids is its first position (a scan as in k_cell_starts).  Only where the
+// marks can tell: ids below the capacity, no id twice (the marks' total is the number of
+// accepted ones); otherwise the host sorts the keys.  (Sorting 35-bit keys took 17
+// launches, 200 us.)
+__global__ __launch_bounds__(1024) void k_ins_order(int capacity, const SelectState* sel, CandSlots C,
+                                                    int32_t* __restrict__ first, CellScratch* sc, Queues* qs)
 {
-    __shared__ int s_app[17];
-    int a = blockIdx.x * blockDim.x + threadIdx.x;
-    bool acc = a < nc && cstate[a] == 1;
-    int p = block_append_n(&qs->n_accepted, acc ? 1 : 0, s_app);
-    if (acc) {
-        akey[p] = ckey[a];
-        aidx[p] = a;
+    __shared__ uint32_t s_ticket;
+    const int t = threadIdx.x;
+    if (qs->rm_open[kRmRounds - 1]) return;   // not chosen yet
+    if (t == 0) s_ticket = atomicAdd(&sc->ticket, 1u);
+    __syncthreads();
+    const int b = (int)(s_ticket % kCellParts);
+    const uint32_t launch = s_ticket / kCellParts + 1u;
+    const int words = ((int)min((long)sel->max_id + 1, (long)capacity) + 3) / 4;
+    const int groups = (words + 3) / 4;
+    const int chunk = (groups + kCellParts - 1) / kCellParts;
+    const int lo = min(groups, b * chunk), hi = min(groups, lo + chunk);
+    auto marks = [&](int g) {
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) n += 4 * g + k < words ? __popc(C.mask[4 * g + k]) : 0;
+        return n;
+    };
+    int sum = 0;
+    for (int g = lo + t; g < hi; g += 1024) sum += marks(g);
+    int total;
+    (void)block_exclusive_scan(sum, total);
+    if (t == 0)
+        __hip_atomic_store(&sc->part[b], ((uint64_t)launch << 32) | (uint32_t)total, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    int before = 0;
+    if (t < b) {
+        uint64_t v;
+        while ((uint32_t)((v = __hip_atomic_load(&sc->part[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) !=
+               launch)
+            __builtin_amdgcn_s_sleep(1);
+        before = (int)(uint32_t)v;
     }
+    int carry;
+    (void)block_exclusive_scan(before, carry);
+    for (int g0 = lo; g0 < hi; g0 += 1024) {
+        const int g = g0 + t;
+        int tot;
+        const int ex = block_exclusive_scan(g < hi ? marks(g) : 0, tot);
+        if (g < hi) first[g] = carry + ex;
+        carry += tot;
+    }
+    // 2: more than the capacity holds, 3: in order, 4: to be sorted
+    if (b == kCellParts - 1 && t == 0) qs->small_state = carry == qs->n_accepted && sel->max_id < capacity ? 3 : 4;
+}
+
+// The accepted candidates appended in key order, and the record for the host.
+__global__ __launch_bounds__(256) void k_ins_append(int n0, int capacity, int nc, int rounds, CandSlots C,
+                                                    const int32_t* __restrict__ first, float* x, float* y, float* gamma,
+                                                    int32_t* id, uint8_t* diffused, int32_t* n_dev,
+                                                    const SelectState* sel, Queues* qs, vrm_counters* cnt,
+                                                    const GridState* gs, HostQueues* h, int32_t seq)
+{
+    const bool open = qs->rm_open[kRmRounds - 1] != 0;
+    const int na = qs->n_accepted, state = qs->small_state;
+    const bool fits = n0 + na <= capacity, mine = !open && fits && state == 3;
+    if (mine) {
+        for (int k = blockIdx.x * 256 + threadIdx.x; k < na; k += gridDim.x * 256) {
+            const int u = C.taken[k];
+            const uint64_t key = C.key[u];
+            const uint32_t i = (uint32_t)(key >> 3), word = i >> 2, below = 8 * (i & 3) + (uint32_t)(key & 7);
+            int r = first[i >> 4] + __popc(C.mask[word] & ((1u << below) - 1u));
+            for (uint32_t w = word & ~3u; w < word; ++w) r += __popc(C.mask[w]);
+            x[n0 + r] = C.x[u];
+            y[n0 + r] = C.y[u];
+            gamma[n0 + r] = 0.0f;
+            id[n0 + r] = sel->max_id + 1 + r;
+            diffused[n0 + r] = 0;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (mine) *n_dev = n0 + na;
+        if (!open && !fits) cnt->capacity_needed = n0 + na;
+        if (!open && fits) {
+            // rounds run, in the batches of four that the counter is kept in
+            int r = 0;
+            while (r < kRmRounds && qs->rm_open[r]) ++r;
+            cnt->n_candidates = nc;
+            cnt->mis_rounds = rounds + (r / 4 + 1) * 4;
+            if (mine) {
+                cnt->n_inserted = na;
+                cnt->n = n0 + na;
+            }
+        }
+        publish(qs, gs, 0, h, seq);
+    }
+}
+
+__global__ void k_ins_next_rounds(Queues* q)
+{
+    for (int k = 0; k < kRmRounds; ++k) q->rm_open[k] = 0;
+}
+
+// the accepted candidates' keys, to be sorted
+__global__ __launch_bounds__(256) void k_accepted(int na, CandSlots C, uint64_t* key)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < na) key[k] = C.key[C.taken[k]];
 }
 
 // New particles get ids max_id + 1, max_id + 2, ... in key order (the largest
 // id of the cloud is found by the selection's first pass), so ids stay unique
 // after particles were removed.
-__global__ __launch_bounds__(256) void k_append(int n0, int na, const int32_t* __restrict__ aidx_sorted,
-                                                const float* __restrict__ cx, const float* __restrict__ cy, float* x,
-                                                float* y, float* gamma, int32_t* id, uint8_t* diffused, int32_t* n_dev,
-                                                const SelectState* sel)
+__global__ __launch_bounds__(256) void k_append(int n0, int na, const int32_t* __restrict__ sorted, CandSlots C,
+                                                float* x, float* y, float* gamma, int32_t* id, uint8_t* diffused,
+                                                int32_t* n_dev, const SelectState* sel, vrm_counters* cnt)
 {
     int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0) *n_dev = n0 + na;
+    if (r == 0) {
+        *n_dev = n0 + na;
+        cnt->n_inserted = na;
+        cnt->n = n0 + na;
+    }
     if (r >= na) return;
-    int a = aidx_sorted[r];
-    x[n0 + r] = cx[a];
-    y[n0 + r] = cy[a];
+    const int u = sorted[r];
+    x[n0 + r] = C.x[u];
+    y[n0 + r] = C.y[u];
     gamma[n0 + r] = 0.0f;
     id[n0 + r] = sel->max_id + 1 + r;
     diffused[n0 + r] = 0;
@@ -824,8 +981,7 @@ __global__ __launch_bounds__(1024) void k_insert_small(int n0, int capacity, int
                                                        Queues* qs, vrm_counters* cnt, const SelectState* sel,
                                                        const GridState* gs, HostQueues* h, int32_t seq)
 {
-    if (n0 > 0)
-        insert_small(n0, capacity, cand_cap, cx, cy, ckey, ex2, x, y, gamma, id, diffused, n_dev, qs, cnt, sel);
+    insert_small(n0, capacity, cand_cap, cx, cy, ckey, ex2, x, y, gamma, id, diffused, n_dev, qs, cnt, sel);
     if (threadIdx.x == 0) publish(qs, gs, 0, h, seq);
 }
 
@@ -855,16 +1011,6 @@ __global__ __launch_bounds__(256) void k_copy_back(int n, const float* __restric
     g[t] = tg[t];
     dif[t] = tdif[t];
     perm[t] = t;
-}
-
-__global__ void k_reset_undecided(Queues* q) { q->n_undecided = 0; }
-
-__global__ void k_insert_counters(const Queues* q, vrm_counters* cnt, int rounds, int n_after)
-{
-    cnt->n_candidates = q->n_cand;
-    cnt->n_inserted = q->n_accepted;
-    cnt->mis_rounds = rounds;
-    cnt->n = n_after;
 }
 
 int blocks_for(int n) { return n > 0 ? (n + 255) / 256 : 1; }
@@ -910,7 +1056,12 @@ int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* i
     const int nbb = std::max(1, min(kBoxBlocks, (n + 256 * kBoxPer - 1) / (256 * kBoxPer)));
     hipLaunchKernelGGL(k_grid, dim3(nbb), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_scratch, cs, c->ncell_cap,
                        c->counters);
-    return cell_list(c, x, y, id, n, n_dev, c->cell_start, c->rank, c->perm, c->xs, c->ys, c->ids);
+    if (int r = cell_slots(c, x, y, n, n_dev, c->cell_start, c->rank)) return r;
+    if (n > 0)
+        hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n)), dim3(256), 0, s, x, y, id, n, n_dev, c->cell_start, c->rank,
+                           c->perm, c->xs, c->ys, c->ids, c->grid);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
 }
 
 // The selection's threshold of the cloud's n_dev particles (and, with it, cleared
@@ -981,53 +1132,47 @@ int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp)
     if (q.small_state == 1) return n + q.n_accepted;
     int nc = q.n_cand;
     if (nc > cand_cap) return vrm_fail(VRM_E_CAPACITY, "insertion: %d candidates exceed the buffer of %d", nc, cand_cap);
-    int rounds = 0;
-    int na = 0;
-    if (nc > 0) {
-        // cell list of the candidates on the particles' grid
-        if (int r = cell_list(c, c->cx, c->cy, nullptr, nc, nullptr, c->cstart, c->crank, c->cperm, nullptr, nullptr,
-                              nullptr))
-            return r;
-        for (;;) {
-            const int batch = 4;
-            for (int k = 0; k < batch; ++k) {
-                hipLaunchKernelGGL(k_reset_undecided, dim3(1), dim3(1), 0, s, c->queues);
-                hipLaunchKernelGGL(k_mis_round, dim3(blocks_for(nc)), dim3(256), 0, s, nc, c->cx, c->cy, c->ckey,
-                                   c->cstate, c->cstart, c->cperm, c->grid, lp.ex2, c->queues);
-            }
-            rounds += batch;
-            VRM_HIP(hipGetLastError());
-            if (int e = vrm_read_queues(c, q)) return e;
-            if (q.n_undecided == 0) break;
-            if (rounds > 4 * nc + 64)
-                return vrm_fail(VRM_E_STATE, "insertion: conflict resolution did not converge");
-        }
-        hipLaunchKernelGGL(k_accepted, dim3(blocks_for(nc)), dim3(256), 0, s, nc, c->ckey, c->cstate, c->queues,
-                           c->akey, c->aidx);
+    // The candidates in cell order, in scratch that is free here; cx, cy and ckey are free
+    // once they are in place.
+    CandSlots C{c->tmp_f, reinterpret_cast<float*>(c->aidx), c->akey, c->cstate, c->cperm,
+                reinterpret_cast<uint32_t*>(c->tmp_i)};
+    hipLaunchKernelGGL(k_ins_begin, dim3(256), dim3(256), 0, s, cl->capacity, c->sel, C, c->queues);
+    if (int r = cell_slots(c, c->cx, c->cy, nc, nullptr, c->cstart, c->crank)) return r;
+    hipLaunchKernelGGL(k_ins_scatter, dim3(blocks_for(nc)), dim3(256), 0, s, c->cx, c->cy, c->ckey, nc, c->cstart,
+                       c->crank, C, c->grid);
+    int32_t* first = c->crank;
+    for (int rounds = 0;; rounds += kRmRounds) {
+        for (int k = 0; k < kRmRounds; ++k)
+            hipLaunchKernelGGL(k_mis_round, dim3((nc + kInsBlock - 1) / kInsBlock), dim3(kInsBlock), 0, s, k, nc, C,
+                               c->cstart, c->grid, lp.ex2, cl->capacity, c->queues);
+        hipLaunchKernelGGL(k_ins_order, dim3(kCellParts), dim3(1024), 0, s, cl->capacity, c->sel, C, first,
+                           c->cell_scratch, c->queues);
+        const int32_t done = ++c->q_seq;
+        hipLaunchKernelGGL(k_ins_append, dim3(min(blocks_for(nc), 512)), dim3(256), 0, s, n, cl->capacity, nc, rounds, C,
+                           first, cl->x_dev, cl->y_dev, cl->gamma_dev, cl->id_dev, c->diffused, cl->n_dev, c->sel,
+                           c->queues, c->counters, c->grid, c->q_host, done);
         VRM_HIP(hipGetLastError());
-        if (int e = vrm_read_queues(c, q)) return e;
-        na = q.n_accepted;
-        if (n + na > cl->capacity) {
-            int need = n + na;
-            hipMemcpyAsync(&c->counters->capacity_needed, &need, sizeof(int), hipMemcpyHostToDevice, s);
-            hipStreamSynchronize(s);
-            return vrm_fail(VRM_E_CAPACITY, "insertion needs %d particles, capacity is %d", n + na, cl->capacity);
-        }
-        if (na > 0) {
-            // ids and append order follow the (id, segment) keys; sorted pairs go to the reorder scratch
-            size_t bytes = c->sort_tmp_bytes;
-            uint64_t* kin = c->akey;
-            int32_t* vin = c->aidx;
-            uint64_t* ksorted = reinterpret_cast<uint64_t*>(c->tmp_f);
-            int32_t* vsorted = c->tmp_i;
-            VRM_HIP(rocprim::radix_sort_pairs(c->sort_tmp, bytes, kin, ksorted, vin, vsorted, (size_t)na, 0, 35, s));
-            hipLaunchKernelGGL(k_append, dim3(blocks_for(na)), dim3(256), 0, s, n, na, vsorted, c->cx, c->cy, cl->x_dev,
-                               cl->y_dev, cl->gamma_dev, cl->id_dev, c->diffused, cl->n_dev, c->sel);
-            VRM_HIP(hipGetLastError());
-        }
+        if (int r = vrm_wait_queues(c, done, q)) return r;
+        if (!q.rm_open[kRmRounds - 1]) break;
+        if (rounds > 4 * (long)nc + 64) return vrm_fail(VRM_E_STATE, "insertion: conflict resolution did not converge");
+        hipLaunchKernelGGL(k_ins_next_rounds, dim3(1), dim3(1), 0, s, c->queues);
     }
-    hipLaunchKernelGGL(k_insert_counters, dim3(1), dim3(1), 0, s, c->queues, c->counters, rounds, n + na);
-    VRM_HIP(hipGetLastError());
+    const int na = q.n_accepted;
+    if (n + na > cl->capacity)
+        return vrm_fail(VRM_E_CAPACITY, "insertion needs %d particles, capacity is %d", n + na, cl->capacity);
+    if (q.small_state == 4) {
+        // ids and append order follow the (id, segment) keys
+        size_t bytes = c->sort_tmp_bytes;
+        uint64_t* kin = c->ckey;
+        uint64_t* ksorted = reinterpret_cast<uint64_t*>(c->cx);
+        int32_t* vsorted = c->tmp_i;
+        hipLaunchKernelGGL(k_accepted, dim3(blocks_for(na)), dim3(256), 0, s, na, C, kin);
+        VRM_HIP(hipGetLastError());
+        VRM_HIP(rocprim::radix_sort_pairs(c->sort_tmp, bytes, kin, ksorted, C.taken, vsorted, (size_t)na, 0, 35, s));
+        hipLaunchKernelGGL(k_append, dim3(blocks_for(na)), dim3(256), 0, s, n, na, vsorted, C, cl->x_dev, cl->y_dev,
+                           cl->gamma_dev, cl->id_dev, c->diffused, cl->n_dev, c->sel, c->counters);
+        VRM_HIP(hipGetLastError());
+    }
     return n + na;
 }
 

@@ -78,22 +78,22 @@ struct CellScratch {
 constexpr int32_t kBadPos = 1;
 constexpr int32_t kBadGamma = 2;
 
-constexpr int kRmRounds = 8;   // rounds of the removal's selection per wait
+constexpr int kRmRounds = 8;   // rounds of an insertion's or removal's choice per wait
 
 // Queue counters of a stage (device side).
 struct Queues {
     int32_t n_small;       // items in the small-LP queue
     int32_t n_full;        // items in the complete-LP queue
     int32_t n_cand;        // insertion candidates
-    int32_t n_undecided;   // non-zero while insertion candidates are undecided
     int32_t n_accepted;    // accepted insertion candidates
-    int32_t small_state;   // single-workgroup insertion: 0 not taken, 1 done, 2 capacity exceeded
+    int32_t small_state;   // insertion: 0 many candidates, 1 done by one workgroup, 2 capacity exceeded,
+                           // 3 done in rounds, 4 chosen in rounds, keys to be sorted
     int32_t n_retry;       // LPs left by the warm pass for a cold solve
     int32_t blocks_done;   // blocks of the last LP launch that have finished
     int32_t last_small;    // n_small and n_full of the last stencil run (the queues
     int32_t last_full;     // themselves are zero between runs)
     int32_t n_rm_uncertified;   // particle removal: particles whose optimality was not certified
-    int32_t rm_open[8];    // round k of a batch left candidates undecided
+    int32_t rm_open[8];    // round k of a batch (insertion, removal) left candidates undecided
     int32_t nonfinite;     // copy of GridState::bad taken when the record is published
     int32_t n_defer;       // complete LPs whose certification was deferred to a second launch
     int32_t n_now;         // the cloud's count when the record was published
