@@ -300,8 +300,10 @@ int vrm_read_counters(vrm_ctx* ctx, vrm_counters* out_host);
  * the particles induce on themselves,
  *   u_i = sum_j Gamma_j K_eps(x_i - x_j),
  *   K_eps(d) = (-d_y, d_x) (1 - exp(-|d|^2 / eps^2)) / (2 pi |d|^2),  K_eps(0) = 0,
- * by a direct sum over all N^2 pairs in FP32 (the paper evaluates it with a
- * fast multipole method; the direct sum suits clouds up to ~10^5 particles).
+ * in FP32: by a direct sum over all N^2 pairs up to 14000 particles, above by
+ * boxes (near ones pair by pair, the others by multipole expansions truncated
+ * below the rounding of the sums; the paper evaluates it with a fast multipole
+ * method), or directly where a cloud's boxes would save little.
  * u_dev, v_dev: device floats [capacity], caller-owned; the first N entries
  * are overwritten.  eps > 0 (the paper: eps = 3h).  Enqueued on the context's
  * stream; no synchronisation. */

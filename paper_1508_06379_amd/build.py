@@ -8,7 +8,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libvrm.so")
 SOURCES = ["vrm_api.cpp", "vrm_cells.hip", "vrm_lp.hip", "vrm_lp_group.hip", "vrm_verify.hip", "vrm_remove.hip",
-           "vrm_stage.hip", "vrm_mlp.hip"]
+           "vrm_stage.hip", "vrm_biot_savart.hip", "vrm_mlp.hip"]
 ARCH = os.environ.get("VRM_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

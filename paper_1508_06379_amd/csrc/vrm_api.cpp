@@ -209,6 +209,7 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(rank, cap);
     A(cell_start, nc);
     A(cell_scratch, 1);
+    A(bs_state, 1);
     A(perm, cap);
     A(xs, cap);
     A(ys, cap);
@@ -269,6 +270,7 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
         if (e == hipSuccess) e = hipMemsetAsync(c->sel, 0, sizeof(vrm::SelectState), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->cell_count, 0, (nc + 7) * sizeof(int32_t), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->cell_scratch, 0, sizeof(vrm::CellScratch), c->stream);
+        if (e == hipSuccess) e = hipMemsetAsync(c->bs_state, 0, sizeof(vrm::BoxState), c->stream);
         if (e == hipSuccess) r = vrm_select_init(c);
         if (e == hipSuccess) e = hipMemsetAsync(c->grid, 0, sizeof(vrm::GridState), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->khist, 0, 2 * (VRM_KMAX + 1) * sizeof(int32_t), c->stream);
@@ -291,7 +293,7 @@ int vrm_destroy(vrm_ctx* c)
     if (!c) return VRM_OK;
     (void)hipSetDevice(c->device);
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_count, c->rank, c->cell_start, c->cell_scratch,
+    void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_count, c->rank, c->cell_start, c->cell_scratch, c->bs_state,
                     c->perm, c->xs, c->ys, c->ids, c->diffused, c->acc, c->x0, c->y0, c->g0, c->q_small, c->q_full, c->q_retry,
                     c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->crank, c->cstart, c->cperm,
                     c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->verify_buf, c->sort_tmp, c->full_cols,

@@ -21,24 +21,6 @@ using namespace vrm;
 
 namespace {
 
-// True in every thread of the last workgroup to get here; what the others wrote with
-// atomics whose results they waited for is complete then.  Two levels, so that the
-// workgroups do not queue on one address (18 ns each); done[17] is left zero.
-__device__ __forceinline__ bool last_here(int32_t* done)
-{
-    __shared__ int s_last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int part = blockIdx.x & 15, in_part = ((int)gridDim.x - part + 15) / 16;
-        bool last = atomicAdd(&done[part], 1) == in_part - 1;
-        if (last) last = atomicAdd(&done[16], 1) == min((int)gridDim.x, 16) - 1;
-        s_last = last;
-    }
-    __syncthreads();
-    if (s_last && threadIdx.x < 17) done[threadIdx.x] = 0;
-    return s_last != 0;
-}
-
 // The grid of a cloud: its bounding box, and by the last workgroup the cells.  Bound by
 // latency for small clouds and by HBM for large ones: eight particles of a thread are in
 // flight at once, and every workgroup leaves its box in a slot of its own (four atomics
@@ -171,7 +153,7 @@ __global__ __launch_bounds__(256) void k_count(const float* __restrict__ x, cons
                                                const int32_t* __restrict__ n_dev, const GridState* gs, int32_t* count,
                                                int32_t* rank)
 {
-    if (n_dev) n = *n_dev;
+    if (n_dev) n = min(n, *n_dev);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = i < n;
     const GridState g = *gs;
@@ -286,7 +268,7 @@ __global__ __launch_bounds__(256) void k_scatter(const float* __restrict__ x, co
                                                  const int32_t* __restrict__ start, const int32_t* __restrict__ rank,
                                                  int32_t* perm, float* xs, float* ys, int32_t* ids, const GridState* gs)
 {
-    if (n_dev) n = *n_dev;
+    if (n_dev) n = min(n, *n_dev);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const GridState g = *gs;
     if (i >= n || (g.bad & kBadPos)) return;
@@ -296,17 +278,6 @@ __global__ __launch_bounds__(256) void k_scatter(const float* __restrict__ x, co
     xs[t] = xi;
     ys[t] = yi;
     ids[t] = id[i];
-}
-
-// Slots of (x, y) on the grid in ctx: the cells' first slots, each point's rank in its cell.
-int cell_slots(vrm_ctx* c, const float* x, const float* y, int32_t n, const int32_t* n_dev, int32_t* start, int32_t* rank)
-{
-    hipStream_t s = c->stream;
-    if (n > 0)
-        hipLaunchKernelGGL(k_count, dim3((n + 255) / 256), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_count, rank);
-    hipLaunchKernelGGL(k_cell_starts, dim3(kCellParts), dim3(1024), 0, s, c->cell_count, start, c->grid, c->cell_scratch);
-    VRM_HIP(hipGetLastError());
-    return VRM_OK;
 }
 
 // ------------------------------------------------------ reduced operator
@@ -1044,6 +1015,18 @@ int vrm_read_queues(vrm_ctx* c, Queues& q, const int32_t* n_dev)
     return vrm_wait_queues(c, seq, q);
 }
 
+// Slots of (x, y) on a grid: the cells' first slots, each point's rank in its cell.
+int vrm_cell_slots(vrm_ctx* c, const GridState* g, const float* x, const float* y, int32_t n, const int32_t* n_dev,
+                   int32_t* start, int32_t* rank)
+{
+    hipStream_t s = c->stream;
+    if (n > 0)
+        hipLaunchKernelGGL(k_count, dim3(blocks_for(n)), dim3(256), 0, s, x, y, n, n_dev, g, c->cell_count, rank);
+    hipLaunchKernelGGL(k_cell_starts, dim3(kCellParts), dim3(1024), 0, s, c->cell_count, start, g, c->cell_scratch);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
+}
+
 // Cell list of (x, y) into ctx->cell_start / perm / xs, ys, ids (slot order).
 int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* id, int32_t n, const LaunchParams& lp,
                     const int32_t* n_dev)
@@ -1056,7 +1039,7 @@ int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* i
     const int nbb = std::max(1, min(kBoxBlocks, (n + 256 * kBoxPer - 1) / (256 * kBoxPer)));
     hipLaunchKernelGGL(k_grid, dim3(nbb), dim3(256), 0, s, x, y, n, n_dev, c->grid, c->cell_scratch, cs, c->ncell_cap,
                        c->counters);
-    if (int r = cell_slots(c, x, y, n, n_dev, c->cell_start, c->rank)) return r;
+    if (int r = vrm_cell_slots(c, c->grid, x, y, n, n_dev, c->cell_start, c->rank)) return r;
     if (n > 0)
         hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n)), dim3(256), 0, s, x, y, id, n, n_dev, c->cell_start, c->rank,
                            c->perm, c->xs, c->ys, c->ids, c->grid);
@@ -1137,7 +1120,7 @@ int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp)
     CandSlots C{c->tmp_f, reinterpret_cast<float*>(c->aidx), c->akey, c->cstate, c->cperm,
                 reinterpret_cast<uint32_t*>(c->tmp_i)};
     hipLaunchKernelGGL(k_ins_begin, dim3(256), dim3(256), 0, s, cl->capacity, c->sel, C, c->queues);
-    if (int r = cell_slots(c, c->cx, c->cy, nc, nullptr, c->cstart, c->crank)) return r;
+    if (int r = vrm_cell_slots(c, c->grid, c->cx, c->cy, nc, nullptr, c->cstart, c->crank)) return r;
     hipLaunchKernelGGL(k_ins_scatter, dim3(blocks_for(nc)), dim3(256), 0, s, c->cx, c->cy, c->ckey, nc, c->cstart,
                        c->crank, C, c->grid);
     int32_t* first = c->crank;

@@ -75,6 +75,18 @@ struct CellScratch {
     int32_t bad_seen;
     int32_t done[17];
 };
+
+// State of a velocity sum by boxes (box, done and bad_seen as in CellScratch).
+struct BoxState {
+    GridState g;            // boxes as cells: x0, y0, side cs, nx x ny
+    unsigned long long all_pairs;
+    alignas(128) unsigned long long work;   // of the boxes, in pairs (lines of their own: atomics)
+    alignas(128) unsigned long long fullest;   // particles of the fullest box over its index
+    alignas(128) int32_t items;             // work items
+    int32_t bad_seen;
+    int32_t done[17];
+    uint32_t box[4][kBoxBlocks];
+};
 constexpr int32_t kBadPos = 1;
 constexpr int32_t kBadGamma = 2;
 
@@ -111,6 +123,24 @@ __device__ __forceinline__ bool last_block(Queues* qs)
     if (atomicAdd(&qs->blocks_done, 1) != min((int)gridDim.x, 16) - 1) return false;
     qs->blocks_done = 0;
     return true;
+}
+
+// True in every thread of the last workgroup to get here; what the others wrote with
+// atomics whose results they waited for is complete then.  Two levels, so that the
+// workgroups do not queue on one address (18 ns each); done[17] is left zero.
+__device__ __forceinline__ bool last_here(int32_t* done)
+{
+    __shared__ int s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int part = blockIdx.x & 15, in_part = ((int)gridDim.x - part + 15) / 16;
+        bool last = atomicAdd(&done[part], 1) == in_part - 1;
+        if (last) last = atomicAdd(&done[16], 1) == min((int)gridDim.x, 16) - 1;
+        s_last = last;
+    }
+    __syncthreads();
+    if (s_last && threadIdx.x < 17) done[threadIdx.x] = 0;
+    return s_last != 0;
 }
 
 // Queue record published to pinned, coherent host memory: the kernel writes q,
@@ -252,6 +282,7 @@ struct vrm_ctx {
     int32_t* rank;        // [cap] rank within its cell
     int32_t* cell_start;  // [ncell_cap + 1]
     vrm::CellScratch* cell_scratch;
+    vrm::BoxState* bs_state;
     int32_t* perm;        // [cap] slot -> particle
     float* xs;            // [cap] positions in slot order
     float* ys;
@@ -365,6 +396,8 @@ struct ScopedTimer {
 int vrm_build_cells(vrm_ctx* c, const float* x, const float* y, const int32_t* id, int32_t n,
                     const vrm::LaunchParams& lp, const int32_t* n_dev = nullptr);
 int vrm_select_run(vrm_ctx* c, const vrm_cloud* cl, int32_t guess, double bound_factor, int32_t& n);
+int vrm_cell_slots(vrm_ctx* c, const vrm::GridState* g, const float* x, const float* y, int32_t n,
+                   const int32_t* n_dev, int32_t* start, int32_t* rank);
 int vrm_select_mask_run(vrm_ctx* c, const float* gamma, int32_t n, uint8_t* mask_out);
 int vrm_select_init(vrm_ctx* c);
 int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp);
