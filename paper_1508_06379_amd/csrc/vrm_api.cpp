@@ -477,6 +477,15 @@ int stage_launch(vrm_ctx* c, vrm_cloud* cl, const float* u_dev, const float* v_d
 {
     int r;
     vrm::LaunchParams L = launch_params(c, p);
+    // (FP32 sums: a stage of fixed positions is combined by the launch that applies the
+    // stencils of the next one, unless the two are timed)
+    const bool fused = fixed && !L.det && !c->timing;
+    if (fused && stage > 0) {
+        r = vrm_combine_apply_run(c, cl, nb, L, stage - 1, p->dt, stage - 1);
+        if (r || stage == 1) return r;
+        c->base_valid = 0;
+        return vrm_combine_run(c, cl, nb, nullptr, nullptr, p->dt, L.lam, 2, 0);
+    }
     if (stage == 0) {
         r = vrm_save_base_run(c, cl, nb, L.det);
         if (r) return r;
@@ -490,7 +499,7 @@ int stage_launch(vrm_ctx* c, vrm_cloud* cl, const float* u_dev, const float* v_d
     r = fixed && stage > 0 ? vrm_apply_run(c, cl, nb, L)
                            : vrm_stencil_run(c, cl, nb, L, nullptr, 1, nullptr, nullptr, 0,
                                              fixed ? vrm::kKeepStencils : vrm::kKeepBases, stage > 0);
-    if (!r) {
+    if (!r && !fused) {
         vrm::ScopedTimer tm(c, VRM_T_COMBINE);
         r = vrm_combine_run(c, cl, nb, u_dev, v_dev, p->dt, L.lam, stage, L.det);
     }
@@ -709,8 +718,10 @@ int vrm_step(vrm_ctx* c, vrm_cloud* cl, const vrm_params* p, const float* vort_d
         std::memcpy(c->graph_key, key, sizeof(key));
         std::memcpy(c->graph_flags, f1, sizeof(f1));
     }
-    hipLaunchKernelGGL(k_set_time, dim3(1), dim3(1), 0, c->stream, c->t_dev, t);
-    VRM_HIP(hipGetLastError());
+    if (n_vort > 0) {   // only the velocity reads the time
+        hipLaunchKernelGGL(k_set_time, dim3(1), dim3(1), 0, c->stream, c->t_dev, t);
+        VRM_HIP(hipGetLastError());
+    }
     VRM_HIP(hipGraphLaunch(c->graph_exec, c->stream));
     c->graph_replays += 1;
     c->graph_pending = c->timing && c->graph_slots > 0;

@@ -92,6 +92,15 @@ constexpr int32_t kBadGamma = 2;
 
 constexpr int kRmRounds = 8;   // rounds of an insertion's or removal's choice per wait
 
+// Shu-Osher SSP-RK3: y_s = a y^n + b (y_(s-1) + dt f(y_(s-1))).
+constexpr float kStageA[3] = {0.0f, 0.75f, 1.0f / 3.0f};
+constexpr float kStageB[3] = {1.0f, 0.25f, 2.0f / 3.0f};
+__device__ __forceinline__ float combined_gamma(float a, float b, float dt, float dg, float g, float g0)
+{
+    const float s = b * __builtin_fmaf(dt, dg, g);
+    return a != 0.0f ? __builtin_fmaf(a, g0, s) : s;
+}
+
 // Queue counters of a stage (device side).
 struct Queues {
     int32_t n_small;       // items in the small-LP queue
@@ -414,6 +423,8 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::Launc
                     const vrm_stencils* out, int apply, uint16_t* feat_out = nullptr, float* label_out = nullptr,
                     int max_rows = 0, int keep = vrm::kKeepNone, bool from_bases = false);
 // the update of the stencils kept by a vrm_stencil_run with kKeepStencils
+int vrm_combine_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, int stage, double dt,
+                          int half);
 int vrm_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp);
 int vrm_small_nbhd_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp,
                        int32_t* small_idx, int32_t* kfull);

@@ -1546,16 +1546,34 @@ __global__ __launch_bounds__(kFullBlock) __attribute__((amdgpu_waves_per_eu(2)))
 // atomics and the 96 bytes of a row; a launch's latency on small clouds.  A step of
 // the 40k-particle heat run (q = 2) takes 213 us with it and 384 us with the
 // linear programs solved in every stage, the 1681-particle one 165 and 270 us.
+// COMBINE: the stage before is combined first (as k_combine without a velocity), its
+// update read from `sum` and cleared there: one launch instead of two, where the FP32
+// sums leave room for a second accumulator (a step of 1681 particles 113 -> 110 us).
+template <bool COMBINE>
 __global__ __launch_bounds__(256) void k_apply(int n, const int32_t* __restrict__ n_dev,
                                                const uint8_t* __restrict__ diffused,
                                                const int32_t* __restrict__ sten_idx, const float* __restrict__ sten_f,
-                                               const float* __restrict__ gamma, float* acc, int det, const GridState* gs,
-                                               vrm_counters* cnt)
+                                               float* __restrict__ gamma, float* acc, int det, const GridState* gs,
+                                               vrm_counters* cnt, float* __restrict__ sum,
+                                               const float* __restrict__ g0, float a, float b, float dt, float lam)
 {
     if (n_dev) n = *n_dev;
     cnt = counter_stripe(cnt);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     bool ok = false;
+    float g_now = 0.0f;
+    if (i < n) {
+        if (COMBINE) {
+            const float s = sum[i];
+            sum[i] = 0.0f;
+            if (!gs->bad) {
+                g_now = combined_gamma(a, b, dt, lam * s, gamma[i], a != 0.0f ? g0[i] : 0.0f);
+                gamma[i] = g_now;
+            }
+        } else {
+            g_now = gamma[i];
+        }
+    }
     if (i < n && !gs->bad && diffused[i]) {
         int idx[kStenRow];
         float f[kStenRow];
@@ -1563,15 +1581,15 @@ __global__ __launch_bounds__(256) void k_apply(int n, const int32_t* __restrict_
         const float4* rf = reinterpret_cast<const float4*>(sten_f + (size_t)i * kStenRow);
 #pragma unroll
         for (int q = 0; q < kStenRow / 4; ++q) {
-            const int4 a = ri[q];
-            const float4 b = rf[q];
-            idx[4 * q] = a.x, idx[4 * q + 1] = a.y, idx[4 * q + 2] = a.z, idx[4 * q + 3] = a.w;
-            f[4 * q] = b.x, f[4 * q + 1] = b.y, f[4 * q + 2] = b.z, f[4 * q + 3] = b.w;
+            const int4 vi = ri[q];
+            const float4 vf = rf[q];
+            idx[4 * q] = vi.x, idx[4 * q + 1] = vi.y, idx[4 * q + 2] = vi.z, idx[4 * q + 3] = vi.w;
+            f[4 * q] = vf.x, f[4 * q + 1] = vf.y, f[4 * q + 2] = vf.z, f[4 * q + 3] = vf.w;
         }
         const int count = idx[kStenRow - 1];
         ok = count >= 0;
         if (ok) {
-            const float g = gamma[i];
+            const float g = g_now;
             const double dsc = det ? det_scale(gs->gmax_bits) : 0.0;
 #pragma unroll
             for (int e = 0; e < kStenRow - 1; ++e)
@@ -1620,6 +1638,7 @@ int lp_group_blocks(const vrm_ctx* c, int m) { return min(c->tuning.lp_full_bloc
 // kernels have fewer waves than the chip has SIMDs and last as long as their slowest
 // wave.  Collection and LPs per launch, sixteen lanes against one: 143 and 365 us for
 // 14k LPs, 270 and 510 us for 57k, 610 and 640 us for 143k.
+constexpr int kSmallCoopMaxN = 1 << 15;
 constexpr int kGroupMaxN = 1 << 17;
 // LPs left by a check of known bases up to which they take sixteen lanes each (4.3 ns an
 // LP; the one-thread launches take 2.0 ns an LP and at least 0.6 ms)
@@ -1730,8 +1749,11 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
     if (lp.m == 5) {
         {
             ScopedTimer tm(c, VRM_T_LP_SMALL);
-            // (always for the few LPs that a check of known bases leaves: a launch's latency)
-            if (!warm_small && (c->tuning.lp_small_coop || verify) && !feat_out && lp.phase1 != 2) {
+            // (always for the few LPs that a check of known bases leaves: a launch's latency;
+            // and for small clouds, whose launch is one LP's chain: 1681 LPs 24 us with eight
+            // lanes each, 39 with one; 10k 42 and 72; 40k 67 and 70; 80k 130 and 70)
+            if (!warm_small && (c->tuning.lp_small_coop || verify || n <= kSmallCoopMaxN) && !feat_out &&
+                lp.phase1 != 2) {
                 // eight lanes per LP (plain or phase-I pass)
                 const int per_block = kSmallBlock / 8;
                 const int grid = min((n + per_block - 1) / per_block, c->tuning.lp_small_blocks);
@@ -1845,8 +1867,25 @@ int vrm_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams
     if (n <= 0) return VRM_OK;
     ScopedTimer tm(c, lp.m == 5 ? VRM_T_LP_SMALL : VRM_T_LP_FULL);
     const StenRows rows = sten_rows(c, lp.m);
-    hipLaunchKernelGGL(k_apply, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->diffused, rows.idx,
-                       rows.f, cl->gamma_dev, c->acc, lp.det, c->grid, c->counters);
+    hipLaunchKernelGGL(k_apply<false>, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->diffused,
+                       rows.idx, rows.f, cl->gamma_dev, c->acc, lp.det, c->grid, c->counters, (float*)nullptr,
+                       (const float*)nullptr, 0.0f, 0.0f, 0.0f, 0.0f);
+    VRM_HIP(hipGetLastError());
+    return VRM_OK;
+}
+
+// Stage `stage` combined from the accumulator's half `half`, and the next stage's update
+// into the other half (FP32 sums).
+int vrm_combine_apply_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchParams& lp, int stage, double dt,
+                          int half)
+{
+    if (n <= 0) return VRM_OK;
+    const StenRows rows = sten_rows(c, lp.m);
+    float* in = c->acc + (half ? (size_t)c->capacity : 0);
+    float* to = c->acc + (half ? 0 : (size_t)c->capacity);
+    hipLaunchKernelGGL(k_apply<true>, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, cl->n_dev, c->diffused,
+                       rows.idx, rows.f, cl->gamma_dev, to, 0, c->grid, c->counters, in, c->g0, kStageA[stage],
+                       kStageB[stage], (float)dt, lp.lam);
     VRM_HIP(hipGetLastError());
     return VRM_OK;
 }

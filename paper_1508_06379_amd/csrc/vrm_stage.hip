@@ -38,11 +38,7 @@ __global__ __launch_bounds__(256) void k_combine(int n, const int32_t* __restric
         acc[i] = 0.0f;
     }
     if (gs->bad) return;
-    float dg = lam * sum;
-    float gn = __builtin_fmaf(dt, dg, g[i]);
-    float gst = b * gn;
-    if (a != 0.0f) gst = __builtin_fmaf(a, g0[i], gst);
-    g[i] = gst;
+    g[i] = combined_gamma(a, b, dt, lam * sum, g[i], a != 0.0f ? g0[i] : 0.0f);
     if (u) {
         float xn = __builtin_fmaf(dt, u[i], x[i]);
         float yn = __builtin_fmaf(dt, v[i], y[i]);
@@ -231,10 +227,8 @@ int blocks_for(int n) { return n > 0 ? (n + 255) / 256 : 1; }
 int vrm_combine_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const float* u, const float* v, double dt, float lam,
                     int stage, int det)
 {
-    static const float A[3] = {0.0f, 0.75f, 1.0f / 3.0f};
-    static const float B[3] = {1.0f, 0.25f, 2.0f / 3.0f};
     if (n <= 0) return VRM_OK;
-    hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(256), 0, c->stream, n, cl->n_dev, A[stage], B[stage],
+    hipLaunchKernelGGL(k_combine, dim3(blocks_for(n)), dim3(256), 0, c->stream, n, cl->n_dev, kStageA[stage], kStageB[stage],
                        (float)dt, lam, c->x0, c->y0, c->g0, cl->x_dev, cl->y_dev, cl->gamma_dev, u, v, c->acc, c->grid,
                        det);
     VRM_HIP(hipGetLastError());
