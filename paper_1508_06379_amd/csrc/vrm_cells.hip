@@ -536,37 +536,38 @@ __global__ __launch_bounds__(256) void k_candidates(int n, const int32_t* __rest
     if (lane_id() == 0 && members) atomicAdd(&counter_stripe(cnt)->n_diffused, __popcll(members));
     if (dif) {
         occupied = 0;
-        GridState g = *gs;
+        const GridState g = *gs;
         xi = xs[t];
         yi = ys[t];
-        int c0 = cell_index(g, xi, yi);
-        int cxi = c0 % g.nx, cyi = c0 / g.nx;
-        for (int oy = -1; oy <= 1; ++oy) {
-            int yy = cyi + oy;
-            if (yy < 0 || yy >= g.ny) continue;
-            {
-                // the three cells of this row are contiguous in slot order
-                int c0 = yy * g.nx + max(cxi - 1, 0), c1 = yy * g.nx + min(cxi + 1, g.nx - 1);
-                int u0 = cell_start[c0], u1 = cell_start[c1 + 1];
-                // positions read eight at a time: one memory latency per eight candidates
-                for (int ub = u0 + sub; ub < u1; ub += 8 * L) {
-                    float bx[8], by[8];
+        // the cells that the square around the particle touches (an upper bound of the
+        // offsets whose FP32 squared length is within hi2; cell indices are monotone)
+        const float rad = sqrtf(P.hi2) * (1.0f + 9.5367431640625e-7f);
+        const float xa = xi - rad, xb = xi + rad, ya = yi - rad, yb = yi + rad;
+        int cx0, cy0, cx1, cy1;
+        cell_xy(g, xa - fabsf(xa) * 2.384185791015625e-7f, ya - fabsf(ya) * 2.384185791015625e-7f, cx0, cy0);
+        cell_xy(g, xb + fabsf(xb) * 2.384185791015625e-7f, yb + fabsf(yb) * 2.384185791015625e-7f, cx1, cy1);
+        // until every segment is occupied (inside a cloud: after about half of them)
+        for (int yy = cy0; yy <= cy1 && occupied != 0xff; ++yy) {
+            // the cells of a row are contiguous in slot order
+            const int u0 = cell_start[yy * g.nx + cx0], u1 = cell_start[yy * g.nx + cx1 + 1];
+            // positions read eight at a time: one memory latency per eight candidates
+            for (int ub = u0 + sub; ub < u1 && occupied != 0xff; ub += 8 * L) {
+                float bx[8], by[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int v = min(ub + L * e, u1 - 1);   // past the end: a repeat, not visited
-                        bx[e] = xs[v];
-                        by[e] = ys[v];
-                    }
+                for (int e = 0; e < 8; ++e) {
+                    const int v = min(ub + L * e, u1 - 1);   // past the end: a repeat, not visited
+                    bx[e] = xs[v];
+                    by[e] = ys[v];
+                }
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int u = ub + L * e;
-                        if (u >= u1 || u == t) continue;
-                        float dx = bx[e] - xi;
-                        float dy = by[e] - yi;
-                        float d2 = d2_f32(dx, dy);
-                        if (d2 < P.lo2 || d2 > P.hi2) continue;
-                        occupied |= 1 << segment_f32(dx, dy);
-                    }
+                for (int e = 0; e < 8; ++e) {
+                    const int u = ub + L * e;
+                    if (u >= u1 || u == t) continue;
+                    float dx = bx[e] - xi;
+                    float dy = by[e] - yi;
+                    float d2 = d2_f32(dx, dy);
+                    if (d2 < P.lo2 || d2 > P.hi2) continue;
+                    occupied |= 1 << segment_f32(dx, dy);
                 }
             }
         }

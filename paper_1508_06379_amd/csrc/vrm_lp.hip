@@ -88,6 +88,55 @@ __global__ __launch_bounds__(256) void k_small_nbhd(int n, const int32_t* __rest
     }
 }
 
+// The queue of the complete LPs where there are no others (nine rows): the diffused
+// particles in slot order, eight per thread and one atomic per 8192 slots.  (One atomic per
+// 256 slots, on the one counter, was the launch's time: 1020 us for 16M particles, now 73.)
+constexpr int kQueueBlock = 1024, kQueuePer = 8;
+__global__ __launch_bounds__(kQueueBlock) void k_queue_full(int n, const int32_t* __restrict__ n_dev,
+                                                            const int32_t* __restrict__ perm,
+                                                            const uint8_t* __restrict__ diffused, const GridState* gs,
+                                                            int32_t* __restrict__ q_full, Queues* qs)
+{
+    constexpr int W = kQueueBlock / 64;
+    __shared__ int s_cnt[kQueuePer * W];   // by row of 1024 slots, then by wave
+    __shared__ int s_at;
+    if (n_dev) n = *n_dev;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    const bool live = !gs->bad;   // no cell list while a value is not finite
+    const long base = (long)blockIdx.x * (kQueueBlock * kQueuePer) + tid;
+    int i[kQueuePer];
+    uint64_t m[kQueuePer];
+#pragma unroll
+    for (int e = 0; e < kQueuePer; ++e) {
+        const long t = base + (long)e * kQueueBlock;
+        i[e] = live && t < n ? perm[t] : -1;
+    }
+#pragma unroll
+    for (int e = 0; e < kQueuePer; ++e) m[e] = __ballot(i[e] >= 0 && diffused[max(i[e], 0)] != 0);
+    if (lane == 0)
+#pragma unroll
+        for (int e = 0; e < kQueuePer; ++e) s_cnt[e * W + w] = __popcll(m[e]);
+    __syncthreads();
+    if (tid < 64) {
+        static_assert(kQueuePer * W == 128, "two counts per lane");
+        const int a = s_cnt[2 * lane], b = s_cnt[2 * lane + 1];
+        int incl = a + b;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(incl, o, VRM_WAVE);
+            if (lane >= o) incl += v;
+        }
+        s_cnt[2 * lane] = incl - a - b;
+        s_cnt[2 * lane + 1] = incl - b;
+        if (lane == 63) s_at = incl ? atomicAdd(&qs->n_full, incl) : 0;
+    }
+    __syncthreads();
+    const int at = s_at;
+#pragma unroll
+    for (int e = 0; e < kQueuePer; ++e)
+        if (m[e] >> lane & 1ull)
+            q_full[at + s_cnt[e * W + w] + __popcll(m[e] & ((1ull << lane) - 1ull))] = (int)(base + (long)e * kQueueBlock);
+}
+
 // Small neighbourhoods with kNbL lanes per particle (aligned lane groups), for
 // clouds too small to fill the chip with one lane per particle, where the chain
 // of loads of one particle's scan sets the time.  The lanes of a group scan
@@ -1721,10 +1770,16 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         if (r) return r;
     } else {
         ScopedTimer tm(c, VRM_T_NBHD);
-        const bool coop = n <= kNbhdCoopMaxN;
-        hipLaunchKernelGGL(coop ? k_small_nbhd_coop : k_small_nbhd, dim3(nbhd_blocks(n)), dim3(256), 0, c->stream, n,
-                           cl->n_dev, c->perm, c->xs, c->ys, c->ids, c->cell_start, c->diffused, c->grid, lp, c->srec,
-                           c->q_small, c->q_full, c->queues, (int32_t*)nullptr, (int32_t*)nullptr, 0);
+        if (lp.m > VRM_NSEG) {
+            hipLaunchKernelGGL(k_queue_full, dim3((n + kQueueBlock * kQueuePer - 1) / (kQueueBlock * kQueuePer)),
+                               dim3(kQueueBlock), 0, c->stream, n, cl->n_dev, c->perm, c->diffused, c->grid, c->q_full,
+                               c->queues);
+        } else {
+            const bool coop = n <= kNbhdCoopMaxN;
+            hipLaunchKernelGGL(coop ? k_small_nbhd_coop : k_small_nbhd, dim3(nbhd_blocks(n)), dim3(256), 0, c->stream, n,
+                               cl->n_dev, c->perm, c->xs, c->ys, c->ids, c->cell_start, c->diffused, c->grid, lp, c->srec,
+                               c->q_small, c->q_full, c->queues, (int32_t*)nullptr, (int32_t*)nullptr, 0);
+        }
     }
     VRM_HIP(hipGetLastError());
     const bool net = c->warm == 1 && c->mlp && c->mlp->loaded && !feat_out;
