@@ -1720,6 +1720,12 @@ auto full_kernel(int obj) -> decltype(&k_lp_full<M, SC, 0, false>)
 {
     return by_objective(obj, k_lp_full<M, SC, 0, false>, k_lp_full<M, SC, 1, false>, k_lp_full<M, SC, 2, false>);
 }
+// the same where the canonical objective has taken sixteen lanes per LP
+template <int M, bool SC>
+auto full_kernel_other(int obj) -> decltype(&k_lp_full<M, SC, 1, false>)
+{
+    return obj == 2 ? k_lp_full<M, SC, 2, false> : k_lp_full<M, SC, 1, false>;
+}
 
 }  // namespace
 
@@ -1844,7 +1850,7 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         ScopedTimer tm(c, VRM_T_LP_FULL);
         const bool stored = full_stored_costs(c, n);
         if (lp.phase1 == 0) return vrm_lp_group_run(c, cl, n, lp, o2, apply, stored, INT_MAX, lp_group_blocks(c, lp.m));
-        hipLaunchKernelGGL((stored ? full_kernel<5, true>(lp.phase1) : full_kernel<5, false>(lp.phase1)),
+        hipLaunchKernelGGL((stored ? full_kernel_other<5, true>(lp.phase1) : full_kernel_other<5, false>(lp.phase1)),
                            dim3(min(lp_grid_full(c, n), 64)), dim3(kFullBlock), 0, c->stream, c->perm,
                            c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp,
                            o2, apply, c->counters, kLpPlain, c->q_retry, 1);
@@ -1909,7 +1915,7 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
         if (obj == 0)
             return vrm_lp_group_run(c, cl, n, lp, out, apply, false, verify ? min_items : -1,
                                     lp_group_blocks(c, verify ? 9 : 5));
-        hipLaunchKernelGGL((full_kernel<9, false>(lp.phase1)), dim3(1), dim3(kFullBlock), 0, c->stream, c->perm, c->xs,
+        hipLaunchKernelGGL((full_kernel_other<9, false>(lp.phase1)), dim3(1), dim3(kFullBlock), 0, c->stream, c->perm, c->xs,
                            c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp, out,
                            apply, c->counters, kLpRetry, c->q_retry, 1);
         VRM_HIP(hipGetLastError());
