@@ -556,8 +556,8 @@ __global__ __launch_bounds__(256) void k_candidates(int n, const int32_t* __rest
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int v = min(ub + L * e, u1 - 1);   // past the end: a repeat, not visited
-                    bx[e] = xs[v];
-                    by[e] = ys[v];
+                    bx[e] = load32(xs, v);
+                    by[e] = load32(ys, v);
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {

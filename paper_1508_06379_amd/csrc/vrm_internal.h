@@ -101,6 +101,13 @@ __device__ __forceinline__ float combined_gamma(float a, float b, float dt, floa
     return a != 0.0f ? __builtin_fmaf(a, g0, s) : s;
 }
 
+// p[i] by a 32-bit byte offset from the (uniform) base: fewer address instructions than
+// a 64-bit one per lane; indices of slots and particles are below 2^26
+__device__ __forceinline__ float load32(const float* __restrict__ p, int i)
+{
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + 4u * (uint32_t)i);
+}
+
 // Queue counters of a stage (device side).
 struct Queues {
     int32_t n_small;       // items in the small-LP queue

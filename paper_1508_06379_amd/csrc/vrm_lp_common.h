@@ -149,44 +149,52 @@ __device__ __forceinline__ void scan_segments(int t, float xi, float yi, const G
 {
     int cx, cy;
     cell_of_pos(g, xi, yi, cx, cy);
-    for (int oy = -1; oy <= 1; ++oy) {
-        int yy = cy + oy;
-        if (yy < 0 || yy >= g.ny) continue;
-        // the three cells of this row are contiguous in slot order
-        int c0 = yy * g.nx + max(cx - 1, 0), c1 = yy * g.nx + min(cx + 1, g.nx - 1);
-        int u0 = cell_start[c0], u1 = cell_start[c1 + 1];
-        // positions read eight at a time: one memory latency per eight candidates
-        for (int ub = u0; ub < u1; ub += 8) {
-            float bx[8], by[8];
+    // the rows of three cells are contiguous in slot order: one list of the three
+    int base[3], end[3], total = 0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int v = min(ub + e, u1 - 1);   // past the end: a repeat, not visited
-                bx[e] = xs[v];
-                by[e] = ys[v];
-            }
+    for (int o = 0; o < 3; ++o) {
+        const int yy = cy + o - 1;
+        const bool in = yy >= 0 && yy < g.ny;
+        const int yc = in ? yy : cy;
+        const int u0 = cell_start[yc * g.nx + max(cx - 1, 0)];
+        const int u1 = cell_start[yc * g.nx + min(cx + 1, g.nx - 1) + 1];
+        base[o] = u0 - total;
+        total += in ? u1 - u0 : 0;
+        end[o] = total;
+    }
+    // positions read eight at a time: one memory latency per eight candidates
+    for (int k0 = 0; k0 < total; k0 += 8) {
+        float bx[8], by[8];
+        int bu[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int u = ub + e;
-                if (u >= u1 || u == t) continue;
-                float dx = bx[e] - xi;
-                float dy = by[e] - yi;
-                float d2 = d2_f32(dx, dy);
-                if (d2 < P.lo2) continue;
-                if (d2 <= P.hi2f) ++kfull;
-                if (d2 > P.hi2) continue;
-                const int at = segment_f32(dx, dy) * 256 + tid;
-                const float cur = s_bd[at];
-                if (d2 <= cur) {
-                    bool take = d2 < cur;
-                    if (!take) {
-                        // equal distance: the smaller id wins
-                        const int cb = s_best[at];
-                        take = cb >= 0 && ids[u] < ids[cb];
-                    }
-                    if (take) {
-                        s_bd[at] = d2;
-                        s_best[at] = u;
-                    }
+        for (int e = 0; e < 8; ++e) {
+            const int k = min(k0 + e, total - 1);   // past the end: a repeat, not visited
+            bu[e] = k + (k < end[0] ? base[0] : k < end[1] ? base[1] : base[2]);
+            bx[e] = load32(xs, bu[e]);
+            by[e] = load32(ys, bu[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int u = bu[e];
+            if (k0 + e >= total || u == t) continue;
+            float dx = bx[e] - xi;
+            float dy = by[e] - yi;
+            float d2 = d2_f32(dx, dy);
+            if (d2 < P.lo2) continue;
+            if (d2 <= P.hi2f) ++kfull;
+            if (d2 > P.hi2) continue;
+            const int at = segment_f32(dx, dy) * 256 + tid;
+            const float cur = s_bd[at];
+            if (d2 <= cur) {
+                bool take = d2 < cur;
+                if (!take) {
+                    // equal distance: the smaller id wins
+                    const int cb = s_best[at];
+                    take = cb >= 0 && ids[u] < ids[cb];
+                }
+                if (take) {
+                    s_bd[at] = d2;
+                    s_best[at] = u;
                 }
             }
         }

@@ -102,9 +102,8 @@ __global__ __launch_bounds__(kCandBlock) void k_rm_candidates(int n, const float
                     for (int e = 0; e < 8; ++e) {
                         const int k = min(k0 + e, total - 1);
                         v[e] = k + (k < len0 ? u0 : v0);
-                        // 32-bit offsets: slots are below 2^26
-                        bx[e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(xs) + 4u * (uint32_t)v[e]);
-                        by[e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(ys) + 4u * (uint32_t)v[e]);
+                        bx[e] = load32(xs, v[e]);
+                        by[e] = load32(ys, v[e]);
                     }
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
