@@ -303,7 +303,9 @@ int vrm_read_counters(vrm_ctx* ctx, vrm_counters* out_host);
  * in FP32: by a direct sum over all N^2 pairs up to 14000 particles, above by
  * boxes (near ones pair by pair, the others by multipole expansions truncated
  * below the rounding of the sums; the paper evaluates it with a fast multipole
- * method), or directly where a cloud's boxes would save little.
+ * method), or directly where a cloud's boxes would save little or one of them
+ * would hold more than 4096 particles (a cloud of some 10^5 or more that is many
+ * times denser in places than over its bounding box).
  * u_dev, v_dev: device floats [capacity], caller-owned; the first N entries
  * are overwritten.  eps > 0 (the paper: eps = 3h).  Enqueued on the context's
  * stream; no synchronisation. */

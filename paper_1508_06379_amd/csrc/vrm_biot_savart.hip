@@ -22,12 +22,17 @@ __device__ __forceinline__ void pair(float dx, float dy, float g, float& u, floa
     v = __builtin_fmaf(dx, f, v);
 }
 
-// Whether the boxes do the sum: their instruction slots (16 per pair, about 48 per target and
-// far box) clearly below those of all pairs.  A cloud of a few boxes (eps of its size), or
-// with most particles in a few boxes (an outlier stretches the grid), is summed directly.
+// Particles that a box may hold.  A fuller one leaves the cloud to the direct sum: it has no
+// expansion (one wave forms a box's, and would be the launch's time).
+constexpr int kBoxMost = 4096;
+
+// Whether the boxes do the sum: every box has its expansion, and their instruction slots (16
+// per pair, about 48 per target and far box) are clearly below those of all pairs.  A cloud of
+// a few boxes (eps of its size), or with most particles in a few boxes (an outlier stretches
+// the grid), is summed directly.
 __device__ __forceinline__ bool by_boxes(const BoxState& st)
 {
-    return (double)st.work < 0.7 * (double)st.all_pairs;
+    return (st.fullest >> 32) <= (unsigned long long)kBoxMost && (double)st.work < 0.7 * (double)st.all_pairs;
 }
 
 // ------------------------------------------------------------ Biot-Savart (direct sum)
@@ -283,10 +288,10 @@ __device__ __forceinline__ float2 box_centre(const GridState& g, int bx, int by)
     return make_float2(__builtin_fmaf((float)bx + 0.5f, g.cs, g.x0), __builtin_fmaf((float)by + 0.5f, g.cs, g.y0));
 }
 
-// A wave per box: its expansion, its work items to the list, and its share of the work.
-// A box of more than kBoxMost particles leaves the cloud to the direct sum (its wave would
-// be the launch's time, and its neighbours' pairs most of the work).
-constexpr int kMpWaves = 8, kBoxMost = 4096;
+// A wave per box: its expansion (unless it holds more than kBoxMost particles: then the
+// direct sum does the cloud), its work items to the list, and its share of the work.  The
+// shares sum to at most N (N + 3 boxes), below 2^53 for the largest cloud.
+constexpr int kMpWaves = 8;
 __global__ __launch_bounds__(64 * kMpWaves) void k_bs_multipoles(const int32_t* __restrict__ start,
                                                                  const float4* __restrict__ src,
                                                                  float* __restrict__ coef, int2* __restrict__ items,
@@ -316,8 +321,7 @@ __global__ __launch_bounds__(64 * kMpWaves) void k_bs_multipoles(const int32_t* 
         s_want[w] = want;
         s_full[w] = ((unsigned long long)(j1 - j0) << 32) | (unsigned)box;
         // pairs, a far box being worth three
-        s_work[w] = most ? 1ull << 56
-                         : (unsigned long long)(j1 - j0) * (unsigned long long)(near + 3 * (g.ncells - boxes));
+        s_work[w] = (unsigned long long)(j1 - j0) * (unsigned long long)(near + 3 * (g.ncells - boxes));
     }
     __syncthreads();
     int before = 0, total = 0;
