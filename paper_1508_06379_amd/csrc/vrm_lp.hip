@@ -1177,6 +1177,7 @@ __global__ __launch_bounds__(kCollBlock) __attribute__((amdgpu_waves_per_eu(8)))
                 }
             }
         }
+        separate_equal_keys(s_key[grp], nm, sub, mk, pos);
         const int k = min(nm, VRM_KMAX);
         if (nm > VRM_KMAX) {
             // ranks among the VRM_KMAX nearest only

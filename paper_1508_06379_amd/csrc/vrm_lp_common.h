@@ -137,6 +137,29 @@ __device__ __forceinline__ uint64_t member_key(float d2, int id)
     return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)id;
 }
 
+// Positions of a group's list (sixteen lanes, one DPP row; a lane's members e = sub + 16 q
+// with keys mk[q], their counts of smaller keys in pos[q]) where keys are equal: equal
+// distance and equal id, which a cloud with distinct ids does not have.  Such members would
+// share a position and leave the next one unwritten; the one later in the list goes first.
+template <int Q>
+__device__ __forceinline__ void separate_equal_keys(const uint64_t* keys, int nm, int sub, const uint64_t (&mk)[Q],
+                                                    int (&pos)[Q])
+{
+    int sum = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) sum += sub + 16 * q < nm ? pos[q] : 0;
+    sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);
+    sum += __builtin_amdgcn_mov_dpp(sum, 0x4E, 0xF, 0xF, true);
+    sum += __builtin_amdgcn_mov_dpp(sum, 0x141, 0xF, 0xF, true);
+    sum += __builtin_amdgcn_mov_dpp(sum, 0x140, 0xF, 0xF, true);
+    if (!__any(sum != nm * (nm - 1) / 2)) return;   // 0, 1, ..., nm - 1: all different
+    for (int o = 0; o < 16 * Q; ++o) {
+        const uint64_t k = keys[o];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) pos[q] += o < nm && k == mk[q] && o > sub + 16 * q ? 1 : 0;
+    }
+}
+
 constexpr int kSiftW = 24;
 
 // The closest member of each 45-degree segment around slot t (Sec. 4.3, ties by the

@@ -675,6 +675,7 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(M == 3 
                 }
             }
         }
+        separate_equal_keys(L.list.key, nm, s, mk, pos);
         const int k = min(nm, VRM_KMAX);
         if (nm > VRM_KMAX) {
             // id ranks among the VRM_KMAX nearest only
