@@ -26,6 +26,9 @@ namespace {
 // flight at once, and every workgroup leaves its box in a slot of its own (four atomics
 // of every workgroup on one address each were 18 of 35 us at 2.7M particles).
 constexpr int kBoxPer = 8;
+// cells of a side: a position past the last is given that one's index as a float, which
+// holds whole numbers up to 2^24 (a longer side's last index may round to one past it)
+constexpr long long kMaxSide = 1ll << 24;
 __global__ __launch_bounds__(256) void k_grid(const float* __restrict__ x, const float* __restrict__ y, int n,
                                               const int32_t* __restrict__ n_dev, GridState* g, CellScratch* sc, float cs,
                                               int ncell_cap, vrm_counters* cnt)
@@ -117,12 +120,12 @@ __global__ __launch_bounds__(256) void k_grid(const float* __restrict__ x, const
     long long nx = (long long)fmin(fx, 1.0e9) + 2;
     long long ny = (long long)fmin(fy, 1.0e9) + 2;
     int clamped = 0;
-    if (nx * ny > ncell_cap) {
+    if (nx * ny > ncell_cap || max(nx, ny) > kMaxSide) {
         // keep the aspect ratio; far particles share the edge cells (still exact, slower)
-        double f = sqrt((double)ncell_cap / (double)(nx * ny));
+        const double f = fmin(sqrt((double)ncell_cap / (double)(nx * ny)), 1.0);
         // (a side alone may exceed the capacity: a few particles in a long, thin box)
-        nx = min(max((long long)(nx * f), 1ll), (long long)ncell_cap);
-        ny = min(ny, ncell_cap / nx);
+        nx = min(max((long long)(nx * f), 1ll), min((long long)ncell_cap, kMaxSide));
+        ny = min(min(ny, ncell_cap / nx), kMaxSide);
         clamped = 1;
     }
     g->nx = (int)nx;
