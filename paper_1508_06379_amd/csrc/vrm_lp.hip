@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_eu(3))
                                                           int32_t* q_full, const float* __restrict__ gamma,
                                                           float* acc, LaunchParams P, StencilOut out, int apply,
                                                           vrm_counters* cnt, int mode, int32_t* q_retry, int lanes,
-                                                          const GridState* gs)
+                                                          const GridState* gs, int above)
 {
     __shared__ float s_rx[8 * kSmallBlock];
     __shared__ float s_ry[8 * kSmallBlock];
@@ -537,7 +537,8 @@ __global__ __launch_bounds__(kSmallBlock) __attribute__((amdgpu_waves_per_eu(3))
     __shared__ int s_meta[8 * kSmallBlock];
     cnt = counter_stripe(cnt);
     const int tid = threadIdx.x;
-    const int nitems = mode == kLpRetry ? qs->n_retry : qs->n_small;
+    // a queue of at most `above` is k_lp_small_coop's
+    const int nitems = mode == kLpRetry ? qs->n_retry : qs->n_small > above ? qs->n_small : 0;
     const size_t cap = (size_t)rec.cap;
     // `lanes` LPs per wave (a power of two <= 64): fewer per wave shortens a wave,
     // which lasts as long as its slowest LP, where the launch has SIMDs to spare
@@ -676,14 +677,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_lp_small_coop(const float* __re
                                                                SmallRec rec, const int32_t* __restrict__ q_small,
                                                                Queues* qs, int32_t* q_full, float* acc,
                                                                LaunchParams P, StencilOut out, int apply,
-                                                               vrm_counters* cnt, const GridState* gs)
+                                                               vrm_counters* cnt, const GridState* gs, int limit)
 {
     cnt = counter_stripe(cnt);
     const double dsc = P.det && apply ? det_scale(gs->gmax_bits) : 0.0;
     const int lane = threadIdx.x & 63;
     const int s = lane & 7, base = lane & ~7;
     const bool lead = s == 0;
-    const int nitems = qs->n_small;
+    const int nitems = qs->n_small <= limit ? qs->n_small : 0;   // a longer queue: k_lp_small
     const size_t cap = (size_t)rec.cap;
     const int group = (blockIdx.x * blockDim.x + threadIdx.x) >> 3;
     const int ngroups = (gridDim.x * blockDim.x) >> 3;
@@ -1694,11 +1695,15 @@ int lp_grid_full(const vrm_ctx* c, int n)
 // workgroups of the sixteen-lane complete-LP kernel: three fit on a CU; one each where
 // it solves what the small LPs left, mostly few
 int lp_group_blocks(const vrm_ctx* c, int m) { return min(c->tuning.lp_full_blocks, m == 9 ? 768 : 256); }
+// Five-row LPs of a launch up to which they take eight lanes each: a short launch is one
+// LP's chain.  Eight lanes against one: 24 and 39 us for 1681 LPs, 42 and 72 for 10k, 67 and
+// 70 for 40k, 130 and 70 for 80k.  A flow on an exact lattice, where the check of the stage
+// before settles nothing (2.56M particles): 6983 us a step with eight lanes for all, now 3427.
+constexpr int kSmallCoopMaxN = 1 << 15;
 // Particles up to which complete LPs take sixteen lanes each: below, the one-thread
 // kernels have fewer waves than the chip has SIMDs and last as long as their slowest
 // wave.  Collection and LPs per launch, sixteen lanes against one: 143 and 365 us for
 // 14k LPs, 270 and 510 us for 57k, 610 and 640 us for 143k.
-constexpr int kSmallCoopMaxN = 1 << 15;
 constexpr int kGroupMaxN = 1 << 17;
 // LPs left by a check of known bases up to which they take sixteen lanes each (4.3 ns an
 // LP; the one-thread launches take 2.0 ns an LP and at least 0.6 ms)
@@ -1821,27 +1826,28 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
     if (lp.m == 5) {
         {
             ScopedTimer tm(c, VRM_T_LP_SMALL);
-            // (always for the few LPs that a check of known bases leaves: a launch's latency;
-            // and for small clouds, whose launch is one LP's chain: 1681 LPs 24 us with eight
-            // lanes each, 39 with one; 10k 42 and 72; 40k 67 and 70; 80k 130 and 70)
-            if (!warm_small && (c->tuning.lp_small_coop || verify || n <= kSmallCoopMaxN) && !feat_out &&
-                lp.phase1 != 2) {
+            auto coop = [&](int most, int limit) {
                 // eight lanes per LP (plain or phase-I pass)
                 const int per_block = kSmallBlock / 8;
-                const int grid = min((n + per_block - 1) / per_block, c->tuning.lp_small_blocks);
+                const int grid = min((most + per_block - 1) / per_block, c->tuning.lp_small_blocks);
                 hipLaunchKernelGGL((lp.phase1 == 1 ? k_lp_small_coop<1> : k_lp_small_coop<0>), dim3(max(grid, 1)),
                                    dim3(kSmallBlock), 0, c->stream, cl->gamma_dev, c->srec, c->q_small, c->queues,
-                                   c->q_full, c->acc, lp, out, apply, c->counters, c->grid);
-                VRM_HIP(hipGetLastError());
+                                   c->q_full, c->acc, lp, out, apply, c->counters, c->grid, limit);
+            };
+            if (!warm_small && (c->tuning.lp_small_coop || n <= kSmallCoopMaxN) && !feat_out && lp.phase1 != 2) {
+                coop(n, INT_MAX);
             } else {
-                for (int mode = first; mode <= (warm_small ? kLpRetry : kLpPlain); ++mode) {
+                // what a check of known bases leaves may be a few LPs or all of them: two
+                // launches, one of which finds its queue
+                const int above = verify ? kSmallCoopMaxN : 0;
+                if (verify) coop(kSmallCoopMaxN, kSmallCoopMaxN);
+                for (int mode = first; mode <= (warm_small ? kLpRetry : kLpPlain); ++mode)
                     hipLaunchKernelGGL((by_objective(lp.phase1, k_lp_small<0>, k_lp_small<1>, k_lp_small<2>)), dim3(lp_grid_small(c, n)),
                                        dim3(kSmallBlock), 0, c->stream, c->perm, c->xs, c->ys, c->ids, c->srec,
                                        c->q_small, c->queues, c->q_full, cl->gamma_dev, c->acc, lp, out, apply,
-                                       c->counters, mode, c->q_retry, c->tuning.lp_small_lanes, c->grid);
-                    VRM_HIP(hipGetLastError());
-                }
+                                       c->counters, mode, c->q_retry, c->tuning.lp_small_lanes, c->grid, above);
             }
+            VRM_HIP(hipGetLastError());
         }
         // fallbacks of the small LPs: no network input for them
         StencilOut o2 = out;
