@@ -264,11 +264,15 @@ typedef struct vrm_tuning {
     int32_t full_stored_cost_n;  /* clouds with N up to this keep complete-LP costs in LDS; default 200000;
                                     -1: never */
     int32_t infer_blocks;        /* most workgroups (256 threads) of the network's inference; default 768 */
-    int32_t lp_small_lanes;      /* small LPs per wave of the small-LP launch (1, 2, 4, ..., 64); default 64 */
+    int32_t lp_small_lanes;      /* small LPs per wave of the small-LP launch (1, 2, 4, ..., 64); default 64.
+                                    Less than 64 also means one thread per LP whatever the launch holds
+                                    (unless lp_small_coop is 1). */
     int32_t lp_small_coop;       /* 1: the plain and phase-I small-LP passes give each LP eight lanes, one
-                                    column each (shorter chains for latency-bound launches); 0 (default):
-                                    one thread per LP.  Warm-start and training-collection passes always use
-                                    one thread per LP.  Results are the same either way. */
+                                    column each (shorter chains for latency-bound launches); 0 (default): they
+                                    do so for clouds of at most 32768 particles and, in a stage that starts
+                                    from known bases, for at most 32768 LPs; one thread per LP otherwise.
+                                    Warm-start and training-collection passes always use one thread per LP.
+                                    Results are the same either way. */
     int32_t cert_rounds;         /* test hook, not a launch shape: repair rounds of an LP's exact
                                     certification (default 8, at most 64).  An LP still not certified
                                     after them keeps its basis only if the basis's exact values satisfy

@@ -1808,6 +1808,8 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
     const bool warm = net || (c->warm == 2 && !feat_out);
     // the five-row LPs that a check of known bases leaves are solved cold
     const bool warm_small = warm && !verify;
+    // the lanes per LP follow the cloud's count (n may be the larger bound of a recorded step)
+    const int count = min(c->n, n);
     out.cloud_id = cl->id_dev;
     if (c->warm == 2 && c->prev && !feat_out) {
         out.prev = c->prev;
@@ -1834,13 +1836,16 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
                                    dim3(kSmallBlock), 0, c->stream, cl->gamma_dev, c->srec, c->q_small, c->queues,
                                    c->q_full, c->acc, lp, out, apply, c->counters, c->grid, limit);
             };
-            if (!warm_small && (c->tuning.lp_small_coop || n <= kSmallCoopMaxN) && !feat_out && lp.phase1 != 2) {
+            const bool can = !warm_small && !feat_out && lp.phase1 != 2;
+            // (the caller's number of LPs per wave is a matter of one thread per LP)
+            const bool may = can && c->tuning.lp_small_lanes == 64;
+            if ((can && c->tuning.lp_small_coop) || (may && count <= kSmallCoopMaxN)) {
                 coop(n, INT_MAX);
             } else {
                 // what a check of known bases leaves may be a few LPs or all of them: two
                 // launches, one of which finds its queue
-                const int above = verify ? kSmallCoopMaxN : 0;
-                if (verify) coop(kSmallCoopMaxN, kSmallCoopMaxN);
+                const int above = verify && may ? kSmallCoopMaxN : 0;
+                if (above) coop(kSmallCoopMaxN, kSmallCoopMaxN);
                 for (int mode = first; mode <= (warm_small ? kLpRetry : kLpPlain); ++mode)
                     hipLaunchKernelGGL((by_objective(lp.phase1, k_lp_small<0>, k_lp_small<1>, k_lp_small<2>)), dim3(lp_grid_small(c, n)),
                                        dim3(kSmallBlock), 0, c->stream, c->perm, c->xs, c->ys, c->ids, c->srec,
@@ -1861,7 +1866,7 @@ int vrm_stencil_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const LaunchPara
                            dim3(min(lp_grid_full(c, n), 64)), dim3(kFullBlock), 0, c->stream, c->perm,
                            c->xs, c->ys, c->ids, c->cell_start, c->grid, c->q_full, c->queues, cl->gamma_dev, c->acc, lp,
                            o2, apply, c->counters, kLpPlain, c->q_retry, 1);
-    } else if (!feat_out && lp.phase1 == 0 && n <= kGroupMaxN && (!warm || verify)) {
+    } else if (!feat_out && lp.phase1 == 0 && count <= kGroupMaxN && (!warm || verify)) {
         ScopedTimer tm(c, VRM_T_LP_FULL);
         return vrm_lp_group_run(c, cl, n, lp, out, apply, false, INT_MAX, lp_group_blocks(c, lp.m));
     } else if (!feat_out) {
