@@ -806,6 +806,9 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(M == 3 
         }
         if (s == 0) {
             if (out.sten_idx) keep_end(out, i, st == 0 ? nz : -1, fii);
+            // no basis of the small neighbourhood: a mask of an earlier step must not
+            // decide how the next stage solves this LP (its last bits depend on that)
+            if (M == 5 && out.seg_mask) out.seg_mask[i] = 0;
             if (piv) atomicAdd(&s_cnt[kPiv], piv);
             if (st == 0) {
                 atomicAdd(&s_cnt[kCols], k);
