@@ -200,16 +200,21 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     int r = VRM_OK;
 #define A(ptr, n)                                \
     if (r == VRM_OK) r = alloc(&c->ptr, (n));
-    A(grid, 1);
-    A(queues, 1);
-    A(sel, 1);
-    A(sel_bins, vrm::kSelBins);
-    A(counters, (vrm::kCounterStripes * vrm::kCounterStride + sizeof(vrm_counters) - 1) / sizeof(vrm_counters));
+    A(fixed, 1);
+    if (r == VRM_OK) {
+        vrm::FixedState* f = c->fixed;
+        c->grid = &f->grid;
+        c->queues = &f->queues;
+        c->sel = &f->sel;
+        c->sel_bins = f->sel_bins;
+        c->counters = reinterpret_cast<vrm_counters*>(f->counters);
+        c->cell_scratch = &f->cell_scratch;
+        c->bs_state = &f->bs_state;
+        c->khist = f->khist;
+    }
     A(cell_count, nc + 7);
     A(rank, cap);
     A(cell_start, nc);
-    A(cell_scratch, 1);
-    A(bs_state, 1);
     A(perm, cap);
     A(xs, cap);
     A(ys, cap);
@@ -239,11 +244,9 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     A(tmp_f, 3 * cap);
     A(tmp_i, cap);
     A(tmp_u8, cap);
-    A(verify_buf, 8);
     A(full_cols, cap * VRM_KMAX);
     A(full_k, cap);
     A(full_order, cap);
-    A(khist, 2 * (VRM_KMAX + 1));
     A(lkey, cap);
     A(pivhist, cap);
     A(q_defer, cap);
@@ -265,15 +268,9 @@ int vrm_create(vrm_ctx** out, int device, void* stream, int32_t capacity)
     }
     if (r == VRM_OK) {
         hipError_t e = hipMemsetAsync(c->acc, 0, 2 * cap * sizeof(float), c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(c->counters, 0, vrm::kCounterStripes * vrm::kCounterStride, c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(c->queues, 0, sizeof(vrm::Queues), c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(c->sel, 0, sizeof(vrm::SelectState), c->stream);
+        if (e == hipSuccess) e = hipMemsetAsync(c->fixed, 0, sizeof(vrm::FixedState), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->cell_count, 0, (nc + 7) * sizeof(int32_t), c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(c->cell_scratch, 0, sizeof(vrm::CellScratch), c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(c->bs_state, 0, sizeof(vrm::BoxState), c->stream);
         if (e == hipSuccess) r = vrm_select_init(c);
-        if (e == hipSuccess) e = hipMemsetAsync(c->grid, 0, sizeof(vrm::GridState), c->stream);
-        if (e == hipSuccess) e = hipMemsetAsync(c->khist, 0, 2 * (VRM_KMAX + 1) * sizeof(int32_t), c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(c->pivhist, 0xff, cap, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) r = vrm_hip_check(e, "initialisation");
@@ -293,11 +290,11 @@ int vrm_destroy(vrm_ctx* c)
     if (!c) return VRM_OK;
     (void)hipSetDevice(c->device);
     if (c->stream) (void)hipStreamSynchronize(c->stream);
-    void* ptrs[] = {c->grid, c->queues, c->sel, c->sel_bins, c->counters, c->cell_count, c->rank, c->cell_start, c->cell_scratch, c->bs_state,
+    void* ptrs[] = {c->fixed, c->cell_count, c->rank, c->cell_start,
                     c->perm, c->xs, c->ys, c->ids, c->diffused, c->acc, c->x0, c->y0, c->g0, c->q_small, c->q_full, c->q_retry,
                     c->srec.i, c->srec.rank, c->srec.pj, c->srec.off, c->cx, c->cy, c->ckey, c->cstate, c->crank, c->cstart, c->cperm,
-                    c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->verify_buf, c->sort_tmp, c->full_cols,
-                    c->full_k, c->full_order, c->khist, c->lkey, c->pivhist, c->q_defer, c->pmask};
+                    c->akey, c->aidx, c->tmp_f, c->tmp_i, c->tmp_u8, c->sort_tmp, c->full_cols,
+                    c->full_k, c->full_order, c->lkey, c->pivhist, c->q_defer, c->pmask};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (c->q_host) (void)hipHostFree(c->q_host);
