@@ -15,7 +15,9 @@
  *     caller owns them and keeps them alive until the stream has drained.
  *     Host pointers are named *_host.
  *   - Every call enqueues work on the context's stream and returns without
- *     waiting, except where "synchronises" is stated.
+ *     waiting, except where "synchronises" is stated: such a call waits until its
+ *     result on the host (a count, an error) is known.  Device arrays are complete
+ *     in stream order, also after it.
  *   - Return value: VRM_OK (0) or a negative VRM_E_* code; vrm_last_error()
  *     then describes the failure (thread-local).  Argument errors are found
  *     before anything is enqueued and leave all buffers untouched.
@@ -212,9 +214,10 @@ int vrm_solve_fractions(vrm_ctx* ctx, const vrm_cloud* cloud, const vrm_params* 
  * with L = (u, v, nu sum_j f_ji Gamma_j) evaluated at the current state.
  * u_dev, v_dev [N]: caller-supplied velocity at the current positions (NULL
  * for zero velocity).  Stage 0 records y^n.  Uses the diffused set of the
- * step.  With q = 3 and the canonical objective a stage leaves the bases of its
- * stencils in the context; the next stage checks them against its own LPs and
- * solves only those the check does not settle (the same stencils either way). */
+ * step.  With the canonical objective a stage leaves the bases of its stencils in
+ * the context (q = 3: the columns; q = 2: the segments of small stencils); the
+ * next stage checks them against its own LPs and solves only those the check does
+ * not settle (the same stencils either way). */
 int vrm_rk_stage(vrm_ctx* ctx, vrm_cloud* cloud, const float* u_dev, const float* v_dev,
                  const vrm_params* p, int stage);
 
@@ -377,7 +380,8 @@ int vrm_warm_predictions(vrm_ctx* ctx, const vrm_cloud* cloud, const vrm_params*
                          int32_t* particle_dev, int32_t max_rows, int32_t* rows_host);
 /* Forward pass: y_dev[rows][64] from x_dev[rows][128]. */
 int vrm_mlp_infer(vrm_ctx* ctx, const uint16_t* x_dev, int32_t rows, float* y_dev);
-/* Matrix product on the BF16 matrix cores (test hook): C[M][N] (FP32, zeroed
+/* Matrix product on the BF16 matrix cores (test hook; a kernel of its own, which
+ * inference and training do not use): C[M][N] (FP32, zeroed
  * by the caller) += op(A) op(B) with A[M][K] (or [K][M] if transA) and B[K][N]
  * (or [N][K] if transB), BF16 row-major. */
 int vrm_gemm_bf16(vrm_ctx* ctx, const uint16_t* a_dev, const uint16_t* b_dev, float* c_dev, int32_t M, int32_t N,

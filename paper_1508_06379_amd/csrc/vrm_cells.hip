@@ -286,7 +286,8 @@ __global__ __launch_bounds__(256) void k_scatter(const float* __restrict__ x, co
 // ------------------------------------------------------ reduced operator
 // Ranking key (Sec. 3.5): the bits of |Gamma| in FP32, monotone in the value
 // for non-negative floats; particles with equal keys form one group, left out
-// together.  Four 8-bit radix passes resolve the whole key.
+// together.  Radix passes resolve the whole key: 11, 11 and 10 bits with a context's bins,
+// four of 8 bits with those of the selection without a context.
 __device__ __forceinline__ uint32_t selection_key(float a) { return __float_as_uint(a); }
 
 // The state before a selection: nothing picked, every bin zero.  The last pass leaves
@@ -1094,8 +1095,9 @@ int vrm_select_init(vrm_ctx* c)
     return VRM_OK;
 }
 
-// Insertion; the cell list of the cloud must be current.  Returns once the
-// stream has run the work enqueued here (the host reads the queue record).
+// Insertion; the cell list of the cloud must be current.  Returns once the new count is
+// known (the host reads the record that the deciding kernel publishes): the arrays are
+// complete in stream order.
 int vrm_insert_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp)
 {
     hipStream_t s = c->stream;

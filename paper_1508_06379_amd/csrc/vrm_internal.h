@@ -196,7 +196,7 @@ struct SmallRec {
 struct FullRec {
     const int32_t* rec;      // [item][row] (slot << 6) | id rank per column, nearest first
     int32_t row;             // record row stride
-    const int32_t* kcol;     // [item] column count; -1: the list is left for the one-thread kernel
+    const int32_t* kcol;     // [item] column count; -1: the list is left for the run's last launch
     const int32_t* q_full;   // [item] sorted-cloud index of the particle
     const float* xs;         // sorted positions
     const float* ys;

@@ -1050,7 +1050,8 @@ constexpr int kRecRow = VRM_KMAX;
 // smaller (d2, id), id rank = number with a smaller id (among the VRM_KMAX
 // nearest if there are more).  No sort, no rescans; a list longer than
 // kMemCap (rare: an LP keeps at most VRM_KMAX = 48 columns) goes to the retry queue and
-// is solved by the one-thread kernel, which collects on its own.
+// is solved by the run's last launch, which collects on its own (sixteen lanes per LP for
+// the canonical objective, one thread for the others).
 // The previous-basis warm start (WM 2) takes its input here as well: the
 // columns whose ids form the particle's previous basis, as a mask per LP
 // (pmask).  The network's inputs are read from the records by its inference.
@@ -1247,9 +1248,9 @@ __global__ __launch_bounds__(kCollBlock) __attribute__((amdgpu_waves_per_eu(8)))
         }
         if (over && sub == 0) {
             kcol[r] = -1;
-            key[r] = -1;   // not binned: the one-thread kernel solves it
+            key[r] = -1;   // not binned: the run's last launch solves it
         }
-        // lists too long for the group: the one-thread kernel solves them from the retry queue
+        // lists too long for the group: the run's last launch solves them from the retry queue
         const int pr = wave_append(&qs->n_retry, over && sub == 0);
         if (over && sub == 0) q_retry[pr] = t;
         count_add(&cnt->n_truncated, live && sub == 0 && nm > VRM_KMAX);
@@ -1295,7 +1296,7 @@ __global__ __launch_bounds__(kBinBlock) void k_full_bin_scatter(const int32_t* _
 #pragma unroll
     for (int e = 0; e < kBinPer; ++e) {
         const int r = first + e * kBinBlock + tid;
-        k[e] = r < nitems ? kcol[r] : -1;   // -1: left for the one-thread kernel
+        k[e] = r < nitems ? kcol[r] : -1;   // -1: left for the run's last launch
     }
     __syncthreads();
 #pragma unroll
@@ -1394,7 +1395,7 @@ __global__ __launch_bounds__(256) void k_top_mask(const float* __restrict__ pred
 {
     const int nitems = qs->n_full;
     for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nitems; r += gridDim.x * blockDim.x) {
-        const int k = kcol[r];   // -1: a list left for the one-thread kernel
+        const int k = kcol[r];   // -1: a list left for the run's last launch
         if (k < 0) continue;
         const int kk = min(k, kMlpSlots);
         float v[kMlpSlots];

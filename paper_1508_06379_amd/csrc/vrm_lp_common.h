@@ -277,6 +277,7 @@ int vrm_verify_bases_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::
 int vrm_verify_small_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, int32_t* prev,
                          bool from_prev);
 // the kept rows from the bases recorded by particle id (c->prev)
+int vrm_bases_from_prev_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n);
+// launcher (vrm_lp_group.hip): the removal's identity LPs of the slots in `taken`
 int vrm_rm_lp_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n, const vrm::LaunchParams& lp, const int32_t* taken,
                   uint8_t* removed, bool stored);
-int vrm_bases_from_prev_run(vrm_ctx* c, const vrm_cloud* cl, int32_t n);

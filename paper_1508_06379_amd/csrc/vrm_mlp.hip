@@ -102,7 +102,8 @@ __device__ __forceinline__ void stage_tile(uint16_t (*T)[TK + KPAD], const uint1
     }
 }
 
-// C(m, n) = sum_k A(m, k) B(k, n);  A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn].
+// The stand-alone product of vrm_gemm_bf16 (the network's inference and training have
+// kernels of their own): C(m, n) = sum_k A(m, k) B(k, n);  A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn].
 // Tile 64 x 64 per block of 4 waves (each 32 x 32 = 2 x 2 MFMA blocks); K in steps of 32.
 // gridDim.z > 1 splits K; the partial sums are added atomically.
 __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const uint16_t* __restrict__ A, long sam, long sak,
@@ -441,8 +442,9 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p) { return *reinterpret_
 // through LDS; pre-activations stay in registers until the backward pass needs them.
 // Before (17 launches: a tiled product per layer and direction, the loss, column sums,
 // clears and copies) a step of 4096 rows took 149 us, of 64 rows 85, of 65536 rows 1263;
-// now 22.7, 12.5 and 130 us (this kernel 16, 10 and 75 us of them).  Two workgroups per CU
-// (256 VGPRs, 19 of them spilled) measured 23.1 us, 13.5 us and 119 us.
+// now 22.2, 12.5 and 129 us (this kernel 15.5, 10.3 and 71 us of them); rows of normal
+// offsets in every slot.  (The trainer's own 4096 rows: 150 us, now 17.9.)  Two workgroups
+// per CU (256 VGPRs, 19 of them spilled) measured 23.1 us, 13.5 us and 119 us.
 constexpr int kTrainTile = 16;
 constexpr int kTrainBlocks = 256;              // one per CU; more rows: loop
 constexpr int kBiasCols = 2 * kMlpHid + kMlpOut;

@@ -341,8 +341,9 @@ __global__ void k_rm_reset_rounds(Queues* q)
 
 }  // namespace
 
-// Particle removal over the current cell list (slot order); waits for its result.
-// Returns the new particle count or a negative error.
+// Particle removal over the current cell list (slot order).  Waits for the counts (the last
+// tile of the compaction publishes them): the arrays are complete in stream order.  Returns
+// the new particle count or a negative error.
 int vrm_remove_run(vrm_ctx* c, vrm_cloud* cl, int32_t n, const LaunchParams& lp, bool stored, int32_t* n_candidates)
 {
     hipStream_t s = c->stream;
