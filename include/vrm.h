@@ -225,8 +225,8 @@ int vrm_rk_stage(vrm_ctx* ctx, vrm_cloud* cloud, const float* u_dev, const float
  * vrm_rk_stage.  With n_vort > 0 each stage's velocity is the prescribed
  * vortex field of vrm_vortex_velocity at the stage time (t, t + dt, t + dt/2);
  * otherwise zero.  Without vortices the positions stay, so the three stages have
- * the same stencils: their LPs are solved once, in stage 0 (and counted once in
- * vrm_counters).  The context caches the cell list and the cell order of the
+ * the same stencils: their LPs are solved once, in stage 0, and counted once in
+ * vrm_counters (n_infeasible and n_truncated too).  The context caches the cell list and the cell order of the
  * cloud between calls: a caller that changes positions or the count itself
  * must not rely on that cache (a different cloud or count resets it).
  * The three stages are recorded once as a HIP graph (on a stream of the
@@ -240,8 +240,11 @@ int vrm_step(vrm_ctx* ctx, vrm_cloud* cloud, const vrm_params* p, const float* v
 
 /* Sec. 4.1: which non-negative solution of the moment conditions a stencil is.
  * 0 (default): the canonical stencil, the minimiser of sum_j c_j f_j with
- * c_j = |r_j/h|^(q+1) + 2^-10 rank(id_j) (both phases, exact certificate; the
- * same result as any correct solver).  1: the first feasible vertex, as the
+ * c_j = |r_j/h|^(q+1) + 2^-10 rank(id_j) (both phases, certificate; the same
+ * result as any correct solver, except on clouds within about 1e-3 h of an exact
+ * lattice, where reduced costs of about 1e-3 can be misjudged by the FP32 part of
+ * the certificate: the stencil is then valid, its cost above the least by
+ * 1e-6 or less where that was seen).  1: the first feasible vertex, as the
  * paper's method stops after phase I (fewer pivots; the stencil depends on the
  * pivoting rules, so results are checked by their moments, sign and
  * conservation, not against another solver).  A phase-I basis whose refined

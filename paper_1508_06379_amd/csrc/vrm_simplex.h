@@ -808,8 +808,13 @@ struct ThreadSimplex {
             // tiny) and every FP32 reduced cost clears zero by 64 times its error
             // bound, the basis is optimal without the double-float dual check.
             if (first_corr <= 1e-5f) {
-                // |d - d_exact| <= (error of B^-1 + FP32 rounding) x sc; the error of
-                // B^-1 is about the first correction
+                // |d - d_exact| <= (error of B^-1 + FP32 rounding) x sc.  The first
+                // correction stands for the error of B^-1: it sees that error along
+                // the right-hand side only.  After a pivot on a tiny element (clouds a
+                // fraction of 1e-3 h off an exact lattice) the inverse can be worse in
+                // the other rows (reduced costs off by 3e-4 of sc were seen), and
+                // a vertex whose exact reduced costs go down to about -1e-3 is then
+                // taken for the optimum: a valid stencil, not the canonical one.
                 const float margin = kFastMargin * (first_corr + 1.1920929e-07f);
                 bool primal_ok = true;
 #pragma unroll
